@@ -36,14 +36,9 @@ int g_batch_streams = 0;  // 0: default (every extra stream)
 unsigned g_spin_limit = msl::kDefaultSpinLimit;
 
 // LDS of a line-pass workgroup of G n-point lines: two exchange buffers per
-// line (msl::LineLds), the first buffers of all G lines, then the second ones.
+// line (msl::line_buffers).
 constexpr int kMaxLdsBytes = 64 * 1024;
-int line_pass_lds_bytes(int n, int G) { return 2 * G * (n + n / 8 + 1) * (int)sizeof(float2); }  // msl::line_lds<n>()
-
-template <int N>
-__device__ __forceinline__ msl::LineLds line_buffers(float2* lds, int g, int G) {
-  return msl::LineLds{lds + g * msl::line_lds<N>(), lds + (G + g) * msl::line_lds<N>()};
-}
+int line_pass_lds_bytes(int n, int G) { return 2 * G * n * (int)sizeof(float2); }
 
 constexpr size_t kAlign = 256;
 size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -382,10 +377,10 @@ __global__ void __launch_bounds__(256) k_pass(Ctx c, PassDesc pd) {
     // 256-point passes; at 512 points the interleaved mapping below is faster
     // except in the forward sweep's row passes)
     const int g = threadIdx.x / L, j = threadIdx.x % L;
-    msl::run_line<N, AXIS, false, KIND, TS, P, true>(c, pd, group * G + g, j, line_buffers<N>(lds, g, G));
+    msl::run_line<N, AXIS, false, KIND, TS, P, true>(c, pd, group * G + g, j, msl::line_buffers<N, P>(lds, g, G));
   } else {
     const int g = threadIdx.x % G, j = threadIdx.x / G;
-    msl::run_line<N, AXIS, false, KIND, TS, P>(c, pd, group * G + g, j, line_buffers<N>(lds, g, G));
+    msl::run_line<N, AXIS, false, KIND, TS, P>(c, pd, group * G + g, j, msl::line_buffers<N, P>(lds, g, G));
   }
 }
 
@@ -733,7 +728,7 @@ __global__ void __launch_bounds__(256) k_pass_batch(const BatchRec* __restrict__
   pd.src = field;
   pd.dst = field;
   msl::run_line<N, AXIS, false, msl::KIND_FWD_MID, msl::TS_PACK, P>(c, pd, (gb % groups_per_inst) * G + g, j,
-                                                                   line_buffers<N>(lds, g, G));
+                                                                   msl::line_buffers<N, P>(lds, g, G));
 }
 
 template <int N, int P, int AXIS>

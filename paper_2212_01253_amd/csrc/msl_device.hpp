@@ -191,8 +191,6 @@ __device__ __forceinline__ void dft2(float2& a, float2& b) {
   b = d;
 }
 
-__device__ __forceinline__ int lds_pad(int i) { return i + (i >> 3); }
-
 constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c(n >> 1); }
 
 // Points per lane of an N-point line: 8 (one radix-8 butterfly per lane per
@@ -270,21 +268,71 @@ __device__ __forceinline__ void load_tw(LineTw<N, P>& tw, const float2* __restri
   tw.rs2 = rs2_at(tab);
 }
 
-// The two LDS exchange buffers of one line.  Consecutive exchanges of a
-// workgroup alternate between them, so a stage can write its output while
-// other waves still read that stage's input, and each exchange needs one
-// barrier (after the writes) instead of two.
+// Where element e of an N-point line lies in its LDS exchange buffer: slot
+// e ^ lds_swz(e) ^ line_swz(g), g the line's place in the workgroup.  gfx950
+// writes 8-byte slots 16 lanes a cycle over 16 slots (128 bytes) and reads
+// them 32 lanes a cycle over 32 slots, so a butterfly's strided writes need
+// the index bits that differ among 16 neighbouring lanes (line bits first
+// where lines interleave, then bits of the lane's place in the line) to give
+// independent combinations of the slot's low four bits, and the contiguous
+// reads of 32 lanes independent combinations of its low five.  Each index bit
+// above the third is therefore xored onto a pattern of the low five bits
+// chosen for that: no access of the default launch shapes conflicts.  (One
+// slot of padding in eight, the layout before, made 59 % of the LDS cycles of a
+// 256-point batch pass conflicts: 706 LDS cycles per wavefront against 386
+// now, SQ_LDS_IDX_ACTIVE; 48 forwards of 256x256x1024 in a batch 24.8 -> 22.6 ms.)
+template <int N, int P>
+__host__ __device__ constexpr uint32_t lds_swz(uint32_t e) {
+  const uint32_t b4 = (e >> 4) & 1u, b5 = (e >> 5) & 1u, b6 = (e >> 6) & 1u;
+  if constexpr (P == 8) return N >= 128 ? b4 ^ (b5 << 1) ^ (b6 * 12u) : b4 ^ (b5 << 1);
+  if constexpr (N >= 256) return (b4 * 5u) ^ (b5 * 10u);
+  if constexpr (N == 128) return b4 * 5u;
+  return 0u;
+}
+template <int N, int P>
+__host__ __device__ constexpr uint32_t line_swz(uint32_t g) {
+  const uint32_t g0 = g & 1u, g1 = (g >> 1) & 1u, g2 = (g >> 2) & 1u, g3 = (g >> 3) & 1u;
+  if constexpr (P == 8) return g0 * 28u;
+  if constexpr (N >= 128) return (g0 * 26u) ^ (g1 * 21u);
+  if constexpr (N == 64) return (g0 * 21u) ^ (g1 * 10u);
+  if constexpr (N == 32) return (g0 * 18u) ^ (g1 * 8u) ^ (g2 * 5u);
+  return g0 ^ (g1 << 1) ^ (g2 << 2) ^ (g3 << 3);
+}
+
+// The two LDS exchange buffers of one line, N slots each, and the line's part
+// of the slot number.  Consecutive exchanges of a workgroup alternate between
+// the buffers, so a stage can write its output while other waves still read
+// that stage's input, and each exchange needs one barrier (after the writes)
+// instead of two.
 struct LineLds {
   float2* a;
   float2* b;
+  uint32_t x;
 };
+
+// The buffers of line g of G in a workgroup's LDS (2 G N slots): the first
+// buffers of all lines, then the second ones.
+template <int N, int P>
+__device__ __forceinline__ LineLds line_buffers(float2* lds, int g, int G) {
+  return LineLds{lds + g * N, lds + (G + g) * N, line_swz<N, P>((uint32_t)g)};
+}
+
+// Slot of element e + c, given base = lds_base(e): c a constant whose bits are
+// clear in e.  Bits above the fifth only add, so they become the LDS
+// instruction's offset.
+template <int N, int P>
+__device__ __forceinline__ uint32_t lds_base(const LineLds& sh, uint32_t e) { return e ^ lds_swz<N, P>(e) ^ sh.x; }
+template <int N, int P>
+__device__ __forceinline__ uint32_t lds_slot(uint32_t base, uint32_t c) {
+  const uint32_t s = c ^ lds_swz<N, P>(c);
+  return (base ^ (s & 31u)) + (s & ~31u);
+}
 
 // Line FFT of N points held by L = N/P lanes, P points per lane.  On entry
 // and on exit lane j holds element j + t*L in v[t] ("t-layout", natural
-// order).  Stockham autosort: a first stage of radix R0 <= P without
-// twiddles, then radix-P stages; every stage but the last exchanges through
-// LDS (padded one slot in eight to spread the strided writes over the
-// banks), exchange e in buffer a for even e, b for odd e.  All threads of the
+// order).  Stockham autosort: radix-P stages, the first without twiddles, and
+// where N is no power of P one of radix R0 < P last; every stage but the last exchanges through
+// LDS, exchange e in buffer a for even e, b for odd e.  All threads of the
 // block call it together (it has block barriers).
 //
 // Why one barrier per exchange suffices: the writes of exchange e reuse the
@@ -312,94 +360,55 @@ __device__ __forceinline__ void fft_line(float2 (&v)[P], const LineLds& sh, int 
   constexpr int R0 = LineTw<N, P>::R0;
   constexpr int NX = LineTw<N, P>::NST;  // exchanges: after every stage but the last
   if constexpr (NX % 2 == 1) line_sync<WAVE>();
-  if constexpr (LineTw<N, P>::R0LAST) {
-    // ---- radix R0 last: stage 0 radix P, sub-length 1, no twiddles; writes exchange 0 (buffer a)
-    constexpr int NPW = LineTw<N, P>::NPW, Q = LineTw<N, P>::Q;
-    dft_p<P, INV>(v, tw.rs2);
+  const uint32_t rb = lds_base<N, P>(sh, (uint32_t)j);
+  // ---- stage 0: radix P, sub-length 1, no twiddles; writes exchange 0 (buffer a)
+  dft_p<P, INV>(v, tw.rs2);
+  {
+    const uint32_t wb = lds_base<N, P>(sh, (uint32_t)(P * j));
 #pragma unroll
-    for (int r = 0; r < P; ++r) sh.a[lds_pad(P * j + r)] = v[r];
-    line_sync<WAVE>();
-    // ---- twiddled radix-P stages, sub-length NS = P, P^2, ...; stage s reads exchange s, writes s + 1
-#pragma unroll
-    for (int s = 0, NS = P; s < NPW; ++s, NS *= P) {
-      const float2* const rd = (s & 1) ? sh.b : sh.a;
-#pragma unroll
-      for (int t = 0; t < P; ++t) v[t] = rd[lds_pad(j + t * L)];
-#pragma unroll
-      for (int r = 1; r < P; ++r) v[r] = cmul<INV>(v[r], tw.w[s][r - 1]);
-      dft_p<P, INV>(v, tw.rs2);
-      float2* const wr = (s & 1) ? sh.a : sh.b;
-      const int base = (j / NS) * NS * P + (j % NS);
-#pragma unroll
-      for (int r = 0; r < P; ++r) wr[lds_pad(base + r * NS)] = v[r];
-      line_sync<WAVE>();
-    }
-    // ---- radix-R0 stage, sub-length N / R0: butterfly q of the lane is element j + L q and
-    // its partners at + r N / R0, i.e. v[q + Q r]; outputs land in the same slots (natural order)
-    {
-      const float2* const rd = (NPW & 1) ? sh.b : sh.a;
-#pragma unroll
-      for (int t = 0; t < P; ++t) v[t] = rd[lds_pad(j + t * L)];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-#pragma unroll
-        for (int r = 1; r < R0; ++r) v[q + Q * r] = cmul<INV>(v[q + Q * r], tw.wl[q][r - 1]);
-        if constexpr (R0 == 4) {
-          float2 y0, y1, y2, y3;
-          dft4<INV>(v[q], v[q + Q], v[q + 2 * Q], v[q + 3 * Q], y0, y1, y2, y3);
-          v[q] = y0;
-          v[q + Q] = y1;
-          v[q + 2 * Q] = y2;
-          v[q + 3 * Q] = y3;
-        } else {
-          dft2<INV>(v[q], v[q + Q]);
-        }
-      }
-    }
-    return;
-  }
-  // ---- stage 0: radix R0 = P, sub-length 1, trivial twiddles; writes exchange 0 (buffer a)
-  float2* const w0 = sh.a;
-  if constexpr (R0 == P) {
-    dft_p<P, INV>(v, tw.rs2);
-#pragma unroll
-    for (int r = 0; r < P; ++r) w0[lds_pad(P * j + r)] = v[r];
-  } else {
-    constexpr int Q = P / R0;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      if constexpr (R0 == 4) {
-        float2 y0, y1, y2, y3;
-        dft4<INV>(v[q], v[q + Q], v[q + 2 * Q], v[q + 3 * Q], y0, y1, y2, y3);
-        const int b = R0 * (j + q * L);
-        w0[lds_pad(b)] = y0;
-        w0[lds_pad(b + 1)] = y1;
-        w0[lds_pad(b + 2)] = y2;
-        w0[lds_pad(b + 3)] = y3;
-      } else {
-        float2 a = v[q], c = v[q + Q];
-        dft2<INV>(a, c);
-        w0[lds_pad(2 * (j + q * L))] = a;
-        w0[lds_pad(2 * (j + q * L) + 1)] = c;
-      }
-    }
+    for (int r = 0; r < P; ++r) sh.a[lds_slot<N, P>(wb, (uint32_t)r)] = v[r];
   }
   line_sync<WAVE>();
-  // ---- radix-P stages with sub-length NS = R0, P R0, ...; stage s reads exchange s
+  // ---- twiddled radix-P stages, sub-length NS = P, P^2, ...; stage s reads exchange s and, unless
+  // it is the transform's last stage, writes exchange s + 1
+  constexpr int NPW = LineTw<N, P>::NPW;
 #pragma unroll
-  for (int s = 0, NS = R0; s < NX; ++s, NS *= P) {
+  for (int s = 0, NS = P; s < NPW; ++s, NS *= P) {
     const float2* const rd = (s & 1) ? sh.b : sh.a;
 #pragma unroll
-    for (int t = 0; t < P; ++t) v[t] = rd[lds_pad(j + t * L)];
+    for (int t = 0; t < P; ++t) v[t] = rd[lds_slot<N, P>(rb, (uint32_t)(t * L))];
 #pragma unroll
     for (int r = 1; r < P; ++r) v[r] = cmul<INV>(v[r], tw.w[s][r - 1]);
     dft_p<P, INV>(v, tw.rs2);
     if (s + 1 < NX) {
       float2* const wr = (s & 1) ? sh.a : sh.b;
-      const int base = (j / NS) * NS * P + (j % NS);
+      const uint32_t wb = lds_base<N, P>(sh, (uint32_t)((j / NS) * NS * P + (j % NS)));
 #pragma unroll
-      for (int r = 0; r < P; ++r) wr[lds_pad(base + r * NS)] = v[r];
+      for (int r = 0; r < P; ++r) wr[lds_slot<N, P>(wb, (uint32_t)(r * NS))] = v[r];
       line_sync<WAVE>();
+    }
+  }
+  if constexpr (LineTw<N, P>::R0LAST) {
+    // ---- radix-R0 stage last, sub-length N / R0: butterfly q of the lane is element j + L q and
+    // its partners at + r N / R0, i.e. v[q + Q r]; outputs land in the same slots (natural order)
+    constexpr int Q = LineTw<N, P>::Q;
+    const float2* const rd = (NPW & 1) ? sh.b : sh.a;
+#pragma unroll
+    for (int t = 0; t < P; ++t) v[t] = rd[lds_slot<N, P>(rb, (uint32_t)(t * L))];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+#pragma unroll
+      for (int r = 1; r < R0; ++r) v[q + Q * r] = cmul<INV>(v[q + Q * r], tw.wl[q][r - 1]);
+      if constexpr (R0 == 4) {
+        float2 y0, y1, y2, y3;
+        dft4<INV>(v[q], v[q + Q], v[q + 2 * Q], v[q + 3 * Q], y0, y1, y2, y3);
+        v[q] = y0;
+        v[q + Q] = y1;
+        v[q + 2 * Q] = y2;
+        v[q + 3 * Q] = y3;
+      } else {
+        dft2<INV>(v[q], v[q + Q]);
+      }
     }
   }
 }
@@ -529,12 +538,6 @@ template <int AXIS>
 __device__ __forceinline__ int pack_lay(const Ctx& c) {
   return (AXIS == COL && !c.slice_index) ? (int)LAY_C : (int)LAY_T;
 }
-
-// Float2 slots of one line's exchange buffer in LDS: a radix-8 pad every
-// eight slots, and an odd length so that neighbouring lines start on
-// different banks.
-template <int N>
-constexpr int line_lds() { return N + N / 8 + 1; }
 
 // Where a pass takes the transmission T - 1 of its slice from: the slice pack
 // when the caller built one, else the caller's delta and beta stacks (decided
