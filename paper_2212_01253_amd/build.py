@@ -4,6 +4,8 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -12,7 +14,7 @@ OUT = os.path.join(HERE, "libmsl.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
-    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
+    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
     # no implicit multiply-add contraction: the kernels place every FMA explicitly
     "-ffp-contract=off",
     # keep the compiler from emitting packed FP32 instructions
@@ -22,13 +24,22 @@ FLAGS = [
 
 
 def build(verbose: bool = True) -> str:
-    tmp = OUT + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-o", tmp, *SRCS]
-    r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
-    err = "\n".join(l for l in (r.stdout + r.stderr).splitlines() if noise not in l and "(ignoring feature)" not in l)
-    if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({r.returncode}):\n{' '.join(cmd)}\n{err}")
+
+    def run(cmd):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        out = "\n".join(l for l in (r.stdout + r.stderr).splitlines() if noise not in l and "(ignoring feature)" not in l)
+        if r.returncode != 0:
+            raise RuntimeError(f"hipcc failed ({r.returncode}):\n{' '.join(cmd)}\n{out}")
+        return out
+
+    tmp = OUT + ".tmp"
+    with tempfile.TemporaryDirectory() as d:
+        objs = [os.path.join(d, os.path.basename(s) + ".o") for s in SRCS]
+        with ThreadPoolExecutor(len(SRCS)) as pool:   # the sources side by side, then one link
+            outs = list(pool.map(lambda so: run([HIPCC, *FLAGS, "-c", "-o", so[1], so[0]]), zip(SRCS, objs)))
+        outs.append(run([HIPCC, *FLAGS, "-shared", "-o", tmp, *objs]))
+    err = "\n".join(o for o in outs if o)
     os.replace(tmp, OUT)
     if verbose and err.strip():
         print(err, file=sys.stderr)
