@@ -83,7 +83,11 @@ typedef enum { MSL_PROP_PARAXIAL = 0, MSL_PROP_EXACT = 1 } msl_propagator;
 
 /* Execution schedule of the slice loop (msl_set_schedule). */
 typedef enum {
-  MSL_SCHED_AUTO = 0,        /* library choice */
+  MSL_SCHED_AUTO = 0,        /* library choice: one launch for the middle passes of a phase, the field
+                                handed over through memory element by element, where that serves
+                                (paraxial calls with a slice pack on grids up to 512 x 512, the
+                                default launch shape, a stream without a compute-unit mask); else one launch per line pass.  The
+                                results are bit for bit those of MSL_SCHED_PER_PASS. */
   MSL_SCHED_PER_PASS = 1,    /* one kernel launch per line pass */
   MSL_SCHED_PERSISTENT = 2   /* one cooperative launch per phase, grid barriers between passes
                                 (square grids, ny == nz; other shapes run per pass) */
@@ -211,13 +215,14 @@ int32_t msl_set_schedule(int32_t schedule);
 /* Outcome of the last msl_forward, msl_far_field, msl_far_field_adjoint or
  * msl_adjoint call on `workspace` (each of them restarts it): waits for
  * hip_stream, then returns MSL_OK, or MSL_ERR_HIP if a grid barrier of the
- * persistent schedule gave up waiting.  That wait is bounded (it polls at most
- * the spin limit below, then raises an error word and lets the grid drain);
- * the call's results are then not valid, and its working field is overwritten
- * with NaN.  Errors of the per-pass schedule surface as HIP errors instead. */
+ * persistent schedule or a pass of the one-launch schedule gave up waiting.
+ * That wait is bounded (it polls at most the spin limit below, then raises an
+ * error word and lets the grid drain); the call's results are then not valid,
+ * and its working field holds NaN.  Errors of the per-pass schedule surface as HIP errors instead. */
 msl_status msl_workspace_status(void* workspace, size_t ws_bytes, void* hip_stream);
 
-/* Polls the persistent schedule's barrier makes before it gives up
+/* Polls the persistent schedule's barrier, or a pass of the one-launch schedule,
+ * makes before it gives up
  * (process-wide, default 2^22, far beyond any healthy wait; >= 0).  Returns the
  * previous value, or MSL_ERR_ARG.  A small value forces the failure path. */
 int32_t msl_set_barrier_spin_limit(int32_t polls);

@@ -16,6 +16,7 @@
 #include "msl_device.hpp"
 #include "msl_passes.hpp"
 #include "msl_persistent.hpp"
+#include "msl_flow_host.hpp"
 
 using namespace msl_host;
 using msl::Ctx;
@@ -48,6 +49,7 @@ struct Layout {
   size_t twz, twy, hz, hy;  // line tables, [DITHER][n] float2
   size_t H_hi, H_lo;
   size_t bar, partials, tmp, dbT, W, G, seg, gT;
+  size_t xf[2];  // exchange fields of the dataflow schedule, four each: forward and reverse sweep, recompute
   size_t total;
 };
 
@@ -77,6 +79,8 @@ Layout layout(const msl_geometry& g, int k) {
     L.seg = take((size_t)(k > 1 ? k - 1 : 0) * m * 8 * 2);  // two tiled segment buffers
     L.gT = take(odd * m * 8);  // odd slices' gradients, same layout as dbT
   }
+  if (!exact && g.ny <= 512 && g.nz <= 512)
+    for (int q = 0; q < (k >= 1 ? 2 : 1); ++q) L.xf[q] = take(4 * m * 8);
   L.total = o;
   return L;
 }
@@ -497,6 +501,7 @@ struct Call {
   Ctx c;
   char* ws;
   hipStream_t st;
+  int* flow_rot;  // per exchange set, where its rotation stands (FlowArgs::rot), -1: not filled yet; or nullptr
 };
 
 Call make_call(const msl_geometry& g, const Layout& lay, void* ws, hipStream_t st) {
@@ -601,6 +606,56 @@ bool use_persistent(const Call& k, int np) {
          (g_schedule == MSL_SCHED_AUTO && msl::persistent_preferred(k.c, np));
 }
 
+// Whether kernels of the stream may run on every compute unit (hipExtStreamCreateWithCUMask).
+bool whole_device(hipStream_t st) {
+  int dev = 0, cus = 0;
+  uint32_t mask[32] = {};
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus > 1024 ||
+      hipExtStreamGetCUMask(st, (uint32_t)((cus + 31) / 32), mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int n = 0;
+  for (const uint32_t m : mask) n += __builtin_popcount(m);
+  return n >= cus;
+}
+
+// Whether the middle passes of the call's phases go to the dataflow schedule: the default schedule at
+// the default launch shape (a set one asks for the per-pass kernels it describes), a paraxial call
+// with a slice pack, a grid it serves, and a stream that may use every compute unit.
+bool use_flow(const Call& k) {
+  if (!k.flow_rot || g_schedule != MSL_SCHED_AUTO || !k.c.dbT || k.g.propagator != MSL_PROP_PARAXIAL) return false;
+  for (const int n : {k.c.ny, k.c.nz}) {
+    const int e = __builtin_ctz((unsigned)n);
+    if (n > 512 || g_lines_per_group[e] > 0 || g_points_per_lane[e] > 0) return false;
+  }
+  return msl::flow_serves(k.c.ny, k.c.nz) && whole_device(k.st);
+}
+
+// Passes p0 .. p0 + n - 1 of phase a, all of its middle kind, as one dataflow launch.
+msl_status run_flow(const Call& k, const PhaseSpec& a, int p0, int n) {
+  const int set = a.kind == msl::PH_FWD_RECOMP ? 1 : 0;   // the recompute runs beside the reverse sweep
+  unsigned* bar = reinterpret_cast<unsigned*>(k.ws + k.L.bar);
+  msl::FlowArgs f{};
+  f.ph = a;
+  f.p0 = p0;
+  f.n = n;
+  f.x = reinterpret_cast<float2*>(k.ws + k.L.xf[set]);
+  f.err = bar + 2 + set;
+  f.status = bar + 1;
+  f.spin_limit = g_spin_limit;
+  int& rot = k.flow_rot[set];
+  if (rot < 0) {
+    MSL_TRY(hip_check(msl::launch_flow_init(f.x, k.c.m, k.st), "exchange fill kernel"));
+    rot = 0;
+  }
+  f.rot = rot;
+  rot = (rot + n - 1) & 3;
+  return hip_check(msl::launch_flow(k.c, f, a.kind == msl::PH_REV ? msl::KIND_REV_MID : msl::KIND_FWD_MID, k.st),
+                   "dataflow kernel");
+}
+
 // Runs phase a, and phase b beside it when given (independent fields of a
 // square grid), either as one cooperative launch or as launches per pass.
 msl_status run_phases(const Call& k, const PhaseSpec& a, const PhaseSpec* b) {
@@ -615,10 +670,24 @@ msl_status run_phases(const Call& k, const PhaseSpec& a, const PhaseSpec* b) {
     if (g_schedule == MSL_SCHED_PERSISTENT) return hip_check(e, "persistent pass kernel");
     (void)hipGetLastError();  // AUTO: the per-pass schedule below does the same work
   }
-  for (int p = 0; p < np; ++p) {
-    hipError_t e;
-    if (p >= npa) break;
-    e = launch_pass(k.c, msl::phase_pass(a, p), k.st);
+  int f0 = 0, f1 = 0;   // passes [f0, f1): one dataflow launch
+  if (use_flow(k)) {
+    const int kind = a.kind == msl::PH_REV ? msl::KIND_REV_MID : msl::KIND_FWD_MID;
+    while (f0 < npa && msl::pass_kind(msl::phase_pass(a, f0)) != kind) ++f0;
+    if (f0 < npa && msl::phase_pass(a, f0).axis != msl::COL) ++f0;  // a dataflow launch begins with a column pass
+    f1 = f0;
+    while (f1 < npa && msl::pass_kind(msl::phase_pass(a, f1)) == kind) ++f1;
+    if (f1 - f0 < msl::kFlowMinPasses) f0 = f1 = npa;
+  } else {
+    f0 = f1 = npa;
+  }
+  for (int p = 0; p < npa; ++p) {
+    if (p == f0) {
+      MSL_TRY(run_flow(k, a, f0, f1 - f0));
+      p = f1 - 1;
+      continue;
+    }
+    const hipError_t e = launch_pass(k.c, msl::phase_pass(a, p), k.st);
     if (e != hipSuccess) return hip_check(e, "pass kernel");
   }
   for (int p = 0; p < npb; ++p) {
@@ -995,7 +1064,7 @@ msl_status msl_workspace_status(void* workspace, size_t ws_bytes, void* hip_stre
   unsigned w[2] = {0u, 0u};
   MSL_TRY(hip_check(hipMemcpy(w, workspace, sizeof w, hipMemcpyDeviceToHost), "hipMemcpy"));
   if (w[1] != 0u)
-    return fail(MSL_ERR_HIP, "a grid barrier of the persistent schedule gave up waiting (bounded spin) in the last "
+    return fail(MSL_ERR_HIP, "a grid barrier or a dataflow pass gave up waiting (bounded spin) in the last "
                              "call on this workspace; its results are not valid (the working field holds NaN)");
   return MSL_OK;
 }
@@ -1100,6 +1169,8 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
   if (flags & ~MSL_REUSE_SLICE_PACK) return fail(MSL_ERR_ARG, "unknown msl_forward flags");
   MSL_TRY(check_ws(*g, 0, workspace, ws_bytes));
   Call k = make_call(*g, 0, workspace, static_cast<hipStream_t>(hip_stream));
+  int rot[2] = {-1, -1};
+  k.flow_rot = rot;
   k.c.delta = delta;
   k.c.beta = beta;
   MSL_TRY(clear_status(k));
@@ -1248,6 +1319,8 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
   if (flags & ~MSL_REUSE_SLICE_PACK) return fail(MSL_ERR_ARG, "unknown msl_adjoint flags");
   MSL_TRY(check_ws(*g, ckpt_every, workspace, ws_bytes));
   Call k = make_call(*g, ckpt_every, workspace, static_cast<hipStream_t>(hip_stream));
+  int rot[2] = {-1, -1};
+  k.flow_rot = rot;
   k.c.delta = delta;
   k.c.beta = beta;
   k.c.gdelta = grad_delta;

@@ -677,35 +677,13 @@ __device__ __forceinline__ void prop_line(float2 (&v)[P], const LineLds& sh, int
   fft_line<N, true, P, WAVE>(v, sh, j, in.tw);
 }
 
-template <int N, int AXIS, bool COH = false, int KIND = KIND_GENERIC, int TS = TS_RUNTIME, int P = LinePts<N>::P,
-          bool WAVE = false>
-__device__ __forceinline__ void compute_line(const Ctx& c, const PassDesc& pd_, int line, int j, const LineLds& sh,
-                                             LineIn<N, P>& in) {
+// The middle step of a pass on the line in in.v: store it (psi_store), apply the
+// transmission or its adjoint (with the slice's gradients), or the far field's
+// output and seed.
+template <int N, int AXIS, int TS, int P>
+__device__ __forceinline__ void mid_line(const Ctx& c, const PassDesc& pd, int line, int j, LineIn<N, P>& in) {
   constexpr int L = N / P;
-  const float inv_n = 1.0f / (float)N;
   float2 (&v)[P] = in.v;
-  PassDesc pd = pd_;
-  if constexpr (KIND != KIND_GENERIC) {
-    pd.pre = PRE_PROP;
-    pd.post = POST_PROP;
-    pd.mid = KIND == KIND_FWD_MID ? MID_T_FWD : MID_T_ADJ;
-    pd.conj = KIND == KIND_REV_MID;
-    pd.src_lay = LAY_T;
-    pd.dst_lay = LAY_T;
-  }
-
-  switch (pd.pre) {
-    case PRE_PROP: prop_line<N, false, P, WAVE>(v, sh, j, in, pd.conj != 0); break;
-    case PRE_FFT: fft_line<N, false, P>(v, sh, j, in.tw); break;
-    case PRE_IFFT_N:
-      fft_line<N, true, P>(v, sh, j, in.tw);
-#pragma unroll
-      for (int t = 0; t < P; ++t) v[t] = make_float2(v[t].x * inv_n, v[t].y * inv_n);
-      break;
-    case PRE_IFFT_U: fft_line<N, true, P>(v, sh, j, in.tw); break;
-    default: break;
-  }
-
   if (pd.psi_store) {
     const LineAddr a = line_at<N, AXIS, P>(c, pd.store_lay, line, j);
 #pragma unroll
@@ -765,6 +743,37 @@ __device__ __forceinline__ void compute_line(const Ctx& c, const PassDesc& pd_, 
       v[t] = make_float2(v[t].x * s, v[t].y * s);
     }
   }
+}
+
+template <int N, int AXIS, bool COH = false, int KIND = KIND_GENERIC, int TS = TS_RUNTIME, int P = LinePts<N>::P,
+          bool WAVE = false>
+__device__ __forceinline__ void compute_line(const Ctx& c, const PassDesc& pd_, int line, int j, const LineLds& sh,
+                                             LineIn<N, P>& in) {
+  const float inv_n = 1.0f / (float)N;
+  float2 (&v)[P] = in.v;
+  PassDesc pd = pd_;
+  if constexpr (KIND != KIND_GENERIC) {
+    pd.pre = PRE_PROP;
+    pd.post = POST_PROP;
+    pd.mid = KIND == KIND_FWD_MID ? MID_T_FWD : MID_T_ADJ;
+    pd.conj = KIND == KIND_REV_MID;
+    pd.src_lay = LAY_T;
+    pd.dst_lay = LAY_T;
+  }
+
+  switch (pd.pre) {
+    case PRE_PROP: prop_line<N, false, P, WAVE>(v, sh, j, in, pd.conj != 0); break;
+    case PRE_FFT: fft_line<N, false, P>(v, sh, j, in.tw); break;
+    case PRE_IFFT_N:
+      fft_line<N, true, P>(v, sh, j, in.tw);
+#pragma unroll
+      for (int t = 0; t < P; ++t) v[t] = make_float2(v[t].x * inv_n, v[t].y * inv_n);
+      break;
+    case PRE_IFFT_U: fft_line<N, true, P>(v, sh, j, in.tw); break;
+    default: break;
+  }
+
+  mid_line<N, AXIS, TS, P>(c, pd, line, j, in);
 
   switch (pd.post) {
     case POST_PROP: prop_line<N, false, P, WAVE>(v, sh, j, in, pd.conj != 0); break;

@@ -1,0 +1,66 @@
+// Dataflow schedule: the forward and recompute kernels, and the host side.
+#include <cstdlib>
+#include <mutex>
+
+#include "msl_flow_launch.hpp"
+
+namespace msl {
+namespace {
+
+__global__ void __launch_bounds__(256) k_flow_init(float4* x, int64_t n4) {
+  const float q = __uint_as_float(kUnset);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256)
+    x[i] = make_float4(q, q, q, q);
+}
+
+int log2_of(int n) { return __builtin_ctz((unsigned)n); }
+
+// Pauses (256 cycles each) before the first look at a pass's input: the more a pass exchanges, the
+// longer its stores take to land, and looking too early only slows them.  Cycles per pass by pauses:
+// 64x64 4412 with none, 4574 with one; 128x128 5509, 5429, 5652 (0, 1, 2); 256x256 6675, 6014, 5781,
+// 5943 (0..3); 512x512 11110 with none, 10924 with four.
+int flow_nap(int64_t m) { return m <= 8192 ? 0 : (m <= 32768 ? 1 : (m <= 131072 ? 2 : 4)); }
+
+}  // namespace
+
+// Every workgroup of a launch has to be resident for its passes to end.  Kernels of other kinds end by
+// themselves and only delay that; launches of this schedule on other streams wait like this one, so
+// as many as there are hardware queues (each runs one kernel at a time: GPU_MAX_HW_QUEUES, 4 unless set)
+// must fit on the device at once.
+bool flow_serves(int ny, int nz) {
+  struct Fits {
+    signed char known[11][11];   // 0: not asked yet, 1: fits, -1: does not
+  };
+  static std::mutex mu;
+  static Fits fits[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+  std::lock_guard<std::mutex> lock(mu);
+  signed char& k = fits[dev].known[log2_of(ny)][log2_of(nz)];
+  if (k == 0) {
+    int cus = 0, pf = 0, pr = 0, grid = 0;
+    const char* q = std::getenv("GPU_MAX_HW_QUEUES");
+    const int queues = q && std::atoi(q) > 4 ? std::atoi(q) : 4;
+    const bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                    flow_occupancy<KIND_FWD_MID>(nz, ny, pf, grid) == hipSuccess &&
+                    flow_occupancy_rev(nz, ny, pr, grid) == hipSuccess &&
+                    (int64_t)queues * grid <= (int64_t)cus * (pf < pr ? pf : pr);
+    if (!ok) (void)hipGetLastError();
+    k = ok ? 1 : -1;
+  }
+  return k > 0;
+}
+
+hipError_t launch_flow_init(float2* x, int64_t m, hipStream_t st) {
+  const int64_t n4 = 4 * m / 2, nb = (n4 + 255) / 256;
+  hipLaunchKernelGGL(k_flow_init, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(256), 0, st,
+                     reinterpret_cast<float4*>(x), n4);
+  return hipGetLastError();
+}
+
+hipError_t launch_flow(const Ctx& c, FlowArgs a, int kind, hipStream_t st) {
+  a.nap = flow_nap(c.m);
+  return kind == KIND_FWD_MID ? flow_launch<KIND_FWD_MID>(c, a, st) : launch_flow_rev(c, a, st);
+}
+
+}  // namespace msl

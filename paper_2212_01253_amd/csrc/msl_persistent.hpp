@@ -24,8 +24,8 @@
 // that gave up cannot pass for a valid one.
 //
 // Barrier area (unsigned words at the start of the workspace): [0] error word
-// of the current launch, [1] status word of the current call, [8 ...] one flag
-// per block.
+// of the current launch, [1] status word of the current call, [2], [3] error
+// words of the call's dataflow launches (msl_flow.hpp), [8 ...] one flag per block.
 #pragma once
 
 #include "msl_passes.hpp"
@@ -98,9 +98,9 @@ __global__ void k_reset_barrier(unsigned* bar, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) bar[8 + i] = 0u;
 }
 
-// Clears the status word (start of a call that may run persistent phases).
+// Clears the status word and the dataflow launches' error words (start of a call that runs phases).
 __global__ void k_clear_status(unsigned* bar) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) bar[1] = 0u;
+  if (threadIdx.x < 3 && blockIdx.x == 0) bar[1 + threadIdx.x] = 0u;
 }
 
 // After a persistent launch: if a barrier gave up, raise the status word and
