@@ -663,6 +663,304 @@ __global__ void __launch_bounds__(256) k_conv_halo(HaloArgs a) {
   store(acc1, ty1, tx1);
 }
 
+// ---------------------------------------------------------------------------
+// Stride-1 3x3 convolutions (forward, and the input gradient with the weights
+// transposed and rotated) on register rows.  A wavefront owns 32 output channels x
+// PX blocks of 32 pixels x R rows.  It walks the input rows of its block from the
+// top: the operand of one input row under one column shift (one 16-byte LDS read
+// per lane: 8 channels of a pixel) multiplies up to three rows' accumulators, with
+// the weights of the three kernel rows, so each operand read feeds three MFMAs (the
+// halo kernel above reads three operands for two and is bound by LDS bandwidth).
+// Every accumulator still takes its taps in the order 0 .. 8, channel chunk by
+// channel chunk, so the sums are the halo kernel's bit for bit.
+//
+// Per chunk of 16 input channels the workgroup stages the input rows its pixels
+// cover as two planes of 8 channels, [plane][row][column][8], columns from 8 left of
+// the tile in groups of 8; slot 8 g + (i ^ (g mod 8)) of a row holds column i of
+// group g, so that the staging's writes (4 channels of one column of 4 neighbouring
+// groups x 2 planes per 16 lanes) and the operands' reads (16 neighbouring columns)
+// spread over the banks.  A staging item is 4 channels x 8 columns: four 16-byte
+// reads, transposed in registers, eight 8-byte LDS writes.  The next chunk's reads
+// are issued before the products of this one.  Bound by memory at 32 channels (32 -> 32
+// channels at 32x256x256 186 -> 87 us, 3.1 TB/s; 96 -> 32 400 -> 192 us) and by LDS reads and
+// staging at more (384 -> 128 channels at 32x64x64 360 -> 120 us, 970 TFLOP/s; 256 -> 256 at
+// 32x32x32 162 -> 49 us).
+constexpr int kRowsCh = 16;   // input channels per chunk
+
+template <int MB, int PX, int R, bool XS>
+struct RowsTile {
+  static constexpr int WG = 4 / MB;                  // pixel groups: wavefronts side by side in x (XS) or in y
+  static constexpr int TW = 32 * PX * (XS ? WG : 1), TH = R * (XS ? 1 : WG);   // output tile
+  static constexpr int HH = TH + 2;                  // staged rows
+  static constexpr int NG = TW / 8 + 2;              // staged groups of 8 columns per row
+  static constexpr int PITCH = NG * 8;               // columns per staged row
+  // slots per plane; the planes lie an odd multiple of 64 bytes apart (bank halves of the writes)
+  static constexpr int PLANE = (HH * PITCH + 7) / 8 * 8 + 4;
+  static constexpr int XSLOTS = 2 * PLANE;           // 16-byte slots of the staged input
+  static constexpr int WSLOTS = MB * 32 * 9 * 2;     // 16-byte slots of the weights: [tap][half][row]
+  static constexpr int LDS = (XSLOTS + WSLOTS) * 16;
+  static constexpr int ITEMS = HH * NG * 4, ROUNDS = (ITEMS + 255) / 256;
+};
+
+struct RowsArgs {
+  int M, Mp, C, B, H, W, relu, accum, ybf16, vec, quads;
+  int tiles_x, tiles_y;
+  const uint16_t* wp;   // packed weights [chunk][tap][half][Mp][8] (k_pack_rows)
+  const void* x;        // [C][B][H][W]
+  const float* bias;
+  void* y;              // [M][B][H][W]
+};
+
+// wp[((chunk 9 + t) 2 + half) Mp + m][8] from w16 [Co][9 C]; flip: the input gradient's weights (rows
+// m = input channel, channels = output channels, taps reversed).
+__global__ void __launch_bounds__(256) k_pack_rows(int Co, int C, int flip, int Mp, const uint16_t* __restrict__ w16,
+                                                   uint16_t* __restrict__ wp) {
+  const int M = flip ? C : Co, Cin = flip ? Co : C;
+  const int64_t n = (int64_t)pad16(Cin) * 9 * Mp;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+    const int q = (int)(e & 7);
+    int64_t r = e >> 3;
+    const int m = (int)(r % Mp);
+    r /= Mp;
+    const int half = (int)(r & 1);
+    r >>= 1;
+    const int t = (int)(r % 9), c = (int)(r / 9) * 16 + half * 8 + q;
+    uint16_t v = 0;
+    if (m < M && c < Cin) v = flip ? w16[(int64_t)c * 9 * C + 9 * m + 8 - t] : w16[(int64_t)m * 9 * C + 9 * c + t];
+    wp[e] = v;
+  }
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+template <typename V>
+__device__ __forceinline__ V ld_bytes(const void* base, uint32_t off) {
+  return *reinterpret_cast<const V*>(static_cast<const char*>(base) + off);
+}
+
+// Two float32 values as bfloat16 bits, rounded to nearest even.
+__device__ __forceinline__ uint32_t to_bf16x2(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
+}
+
+// Eight columns x0 .. x0 + 7 of a channel row as bfloat16 pairs, the one at x0 at byte offset off of
+// base: whole and 16-byte aligned (VEC), or at any alignment and those outside [0, W) zero.
+template <bool XBF16, bool VEC>
+__device__ __forceinline__ u32x4 load8(const void* base, uint32_t off, int x0, int W) {
+  typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+  typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(2)));
+  if (VEC || (x0 >= 0 && x0 + 7 < W)) {
+    if constexpr (XBF16) {
+      if constexpr (VEC) return ld_bytes<u32x4>(base, off);
+      else return ld_bytes<u32x4a>(base, off);
+    } else {
+      const f32x4a a = ld_bytes<f32x4a>(base, off), b = ld_bytes<f32x4a>(base, off + 16u);
+      return u32x4{to_bf16x2(a.x, a.y), to_bf16x2(a.z, a.w), to_bf16x2(b.x, b.y), to_bf16x2(b.z, b.w)};
+    }
+  }
+  uint64_t h[2] = {0, 0};
+#pragma unroll 1
+  for (int i = max(0, -x0); i < min(8, W - x0); ++i) {
+    uint64_t v;
+    if constexpr (XBF16) v = ld_bytes<uint16_t>(base, off + 2u * (uint32_t)i);
+    else v = to_bf16(ld_bytes<float>(base, off + 4u * (uint32_t)i));
+    if (i < 4) h[0] |= v << (16 * i);
+    else h[1] |= v << (16 * (i - 4));
+  }
+  return u32x4{(uint32_t)h[0], (uint32_t)(h[0] >> 32), (uint32_t)h[1], (uint32_t)(h[1] >> 32)};
+}
+
+// Workgroups are dealt to the eight XCDs in turn; consecutive tiles, which share halo rows, go to one.
+__device__ __forceinline__ int xcd_contiguous(int b, int n) {
+  const int per = n >> 3;
+  return b < 8 * per ? (b & 7) * per + (b >> 3) : b;
+}
+
+// The value of lane ^ 1 (X = 1) or lane ^ 2 (X = 2).
+template <int X>
+__device__ __forceinline__ uint32_t quad_xor(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, X == 1 ? 0xb1 : 0x4e, 0xf, 0xf, true);
+}
+
+template <int MB, int PX, int R, bool XS, bool XBF16, bool VEC>
+__global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
+  using T = RowsTile<MB, PX, R, XS>;
+  extern __shared__ __attribute__((aligned(16))) u32x4 rows_smem[];
+  u32x4* const xs = rows_smem;               // [2][PLANE]
+  u32x4* const ws = rows_smem + T::XSLOTS;   // [9][2][32 MB]
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int m0 = blockIdx.y * 32 * MB;
+  int t = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int ox0 = (t % a.tiles_x) * T::TW;
+  t /= a.tiles_x;
+  const int oy0 = (t % a.tiles_y) * T::TH;
+  const int b = t / a.tiles_y;
+  // this wavefront's channel block and first pixel in the tile
+  const int cb = wave % MB, wy = XS ? 0 : (wave / MB) * R, wx = XS ? (wave / MB) * 32 * PX : 0;
+  const int64_t plane = (int64_t)a.H * a.W, cstride = (int64_t)a.B * plane;
+  constexpr uint32_t ES = XBF16 ? 2u : 4u;
+
+  // staging items of this thread: channel quad it & 3 of column group g, row hy.  Byte offsets from
+  // channel c0 of the input fit 32 bits (the host sees to it).
+  uint32_t src[T::ROUNDS];
+  int dst[T::ROUNDS], x0[T::ROUNDS];   // first 8-byte LDS slot, the swizzle in its low bits; first column
+  bool ok[T::ROUNDS];
+#pragma unroll
+  for (int q = 0; q < T::ROUNDS; ++q) {
+    const int it = tid + 256 * q, quad = it & 3, rg = it >> 2;
+    const int hy = rg / T::NG, g = rg - hy * T::NG;
+    const int yy = oy0 - 1 + hy, xx = ox0 - 8 + 8 * g;
+    ok[q] = it < T::ITEMS && yy >= 0 && yy < a.H && xx + 7 >= 0 && xx < a.W;
+    src[q] = (uint32_t)((int64_t)(4 * quad) * cstride + (int64_t)b * plane + (int64_t)yy * a.W + xx) * ES;
+    x0[q] = xx;
+    dst[q] = it < T::ITEMS ? 2 * ((quad >> 1) * T::PLANE + hy * T::PITCH + 8 * g) + (quad & 1) : -1;
+  }
+  u32x4 pre[T::ROUNDS][4];
+  constexpr int WR = (T::WSLOTS + 255) / 256;
+  u32x4 wpre[WR];
+  auto fetch = [&](int c0) {
+    const char* const xc = static_cast<const char*>(a.x) + (int64_t)c0 * cstride * ES;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const char* const xk = xc + k * cstride * ES;
+#pragma unroll
+      for (int q = 0; q < T::ROUNDS; ++q) {
+        pre[q][k] = u32x4{0u, 0u, 0u, 0u};
+        if (ok[q] && c0 + 4 * (tid & 3) + k < a.C) pre[q][k] = load8<XBF16, VEC>(xk, src[q], x0[q], a.W);
+      }
+    }
+    const u32x4* const w = reinterpret_cast<const u32x4*>(a.wp) + (int64_t)(c0 >> 4) * 18 * a.Mp;
+#pragma unroll
+    for (int q = 0; q < WR; ++q) {
+      const int e = min(tid + 256 * q, T::WSLOTS - 1), r = e % (32 * MB), th = e / (32 * MB);
+      wpre[q] = w[th * a.Mp + min(m0 + r, a.Mp - 1)];
+    }
+  };
+  auto stage = [&]() {
+#pragma unroll
+    for (int q = 0; q < T::ROUNDS; ++q) {
+      if (dst[q] >= 0) {
+        u32x2* const d = reinterpret_cast<u32x2*>(xs) + dst[q];
+        const int sw = ((x0[q] - ox0 + 8) >> 3) & 7;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {   // columns 2i, 2i + 1
+          u32x2 lo, hi;
+          lo.x = __builtin_amdgcn_perm(pre[q][1][i], pre[q][0][i], 0x05040100u);
+          lo.y = __builtin_amdgcn_perm(pre[q][3][i], pre[q][2][i], 0x05040100u);
+          hi.x = __builtin_amdgcn_perm(pre[q][1][i], pre[q][0][i], 0x07060302u);
+          hi.y = __builtin_amdgcn_perm(pre[q][3][i], pre[q][2][i], 0x07060302u);
+          d[2 * ((2 * i) ^ sw)] = lo;
+          d[2 * ((2 * i + 1) ^ sw)] = hi;
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < WR; ++q) {
+      if ((q + 1) * 256 <= T::WSLOTS || tid + 256 * q < T::WSLOTS) ws[tid + 256 * q] = wpre[q];
+    }
+  };
+  // operand slots: plane lane / 32, column px 32 + lane % 32 + dx (dx = 0 .. 2 for shifts -1 .. 1) of row 0
+  int bs[3][PX];
+#pragma unroll
+  for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+    for (int px = 0; px < PX; ++px) {
+      const int col = 7 + dx + wx + 32 * px + (lane & 31), g = col >> 3;
+      bs[dx][px] = (lane >> 5) * T::PLANE + wy * T::PITCH + 8 * g + ((col & 7) ^ (g & 7));
+    }
+  const int wslot = (lane >> 5) * 32 * MB + cb * 32 + (lane & 31);
+  f32x16 acc[R][PX];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int px = 0; px < PX; ++px) acc[r][px] = f32x16{};
+  fetch(0);
+  for (int c0 = 0; c0 < a.C; c0 += kRowsCh) {
+    stage();
+    __syncthreads();
+    if (c0 + kRowsCh < a.C) fetch(c0 + kRowsCh);
+    bf16x8 av[9];
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) av[tap] = __builtin_bit_cast(bf16x8, ws[tap * 2 * 32 * MB + wslot]);
+#pragma unroll
+    for (int hr = 0; hr < R + 2; ++hr) {   // staged row wy + hr: kernel row ky of output row hr - ky
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+        for (int px = 0; px < PX; ++px) {
+          const bf16x8 bv = __builtin_bit_cast(bf16x8, xs[bs[dx][px] + hr * T::PITCH]);
+#pragma unroll
+          for (int ky = 2; ky >= 0; --ky) {
+            const int r = hr - ky;
+            if (r >= 0 && r < R) acc[r][px] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[3 * ky + dx], bv, acc[r][px], 0, 0, 0);
+          }
+        }
+    }
+    __syncthreads();
+  }
+  // accumulator element 4i + j of lane l: channel 8i + 4 (l / 32) + j, pixel l mod 32
+  const int mc = m0 + cb * 32, ml = 4 * (lane >> 5);
+  float bias[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int m = mc + ml + 8 * (e >> 2) + (e & 3);
+    bias[e] = a.bias && m < a.M ? a.bias[m] : 0.0f;
+  }
+  const bool act = a.relu != 0, add = a.bias != nullptr;
+  auto out = [&](float v, int e) {
+    if (add) v += bias[e];
+    return act ? fmaxf(v, 0.0f) : v;
+  };
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int oy = oy0 + wy + r;
+    if (oy >= a.H) continue;
+#pragma unroll
+    for (int px = 0; px < PX; ++px) {
+      const f32x16& v = acc[r][px];
+      const int ox = ox0 + wx + 32 * px + (lane & 31);
+      if (ox >= a.W) continue;
+      const uint32_t pix = (uint32_t)((int64_t)b * plane + (int64_t)oy * a.W + ox);
+      if (a.ybf16 && a.quads) {
+        // four channels x four pixels of a lane quad, transposed: each lane stores four pixels of one
+        // channel (8 bytes; a channel's 32 pixels by eight lanes)
+        const uint32_t o = 2u * ((uint32_t)(ml + (lane & 3)) * (uint32_t)cstride + (pix & ~3u));
+        const uint32_t sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t p = to_bf16x2(out(v[4 * i], 4 * i), out(v[4 * i + 1], 4 * i + 1));
+          uint32_t q = to_bf16x2(out(v[4 * i + 2], 4 * i + 2), out(v[4 * i + 3], 4 * i + 3));
+          p = __builtin_amdgcn_perm(quad_xor<1>(p), p, sel);   // channel 4i + (lane & 1), pixels of the lane pair
+          q = __builtin_amdgcn_perm(quad_xor<1>(q), q, sel);   // channel 4i + 2 + (lane & 1)
+          const uint32_t x = quad_xor<2>((lane & 2) ? p : q);
+          const u32x2 w = (lane & 2) ? u32x2{x, q} : u32x2{p, x};
+          if (mc + 8 * i + ml + (lane & 3) < a.M)
+            *reinterpret_cast<u32x2*>(static_cast<char*>(a.y) + (int64_t)(mc + 8 * i) * cstride * 2 + o) = w;
+        }
+      } else if (a.ybf16) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int m = mc + 8 * (e >> 2) + (e & 3);
+          if (m + ml < a.M)
+            (static_cast<uint16_t*>(a.y) + (int64_t)m * cstride)[(uint32_t)ml * (uint32_t)cstride + pix] = to_bf16(out(v[e], e));
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int m = mc + 8 * (e >> 2) + (e & 3);
+          if (m + ml < a.M) {
+            float* const d = static_cast<float*>(a.y) + (int64_t)m * cstride + ((uint32_t)ml * (uint32_t)cstride + pix);
+            const float w = out(v[e], e);
+            *d = a.accum ? *d + w : w;
+          }
+        }
+      }
+    }
+  }
+}
+
 // Weight gradient on halo tiles: dw[o][9c + t] = sum over output pixels p of dy[o][p] times the
 // input value of channel c under tap t of p (rounded to bfloat16 as in the forward).  A workgroup of
 // three wavefronts owns 32 input channels x 32 output channels and a range of spatial tiles (its
@@ -1207,6 +1505,50 @@ msl_status need(bool ok, const char* what) { return ok ? MSL_OK : fail(MSL_ERR_A
 
 msl_status launched(const char* what) { return hip_check(hipGetLastError(), what); }
 
+template <int MB, int PX, int R, bool XS>
+msl_status launch_rows_t(RowsArgs a, bool xbf16, hipStream_t st) {
+  using T = RowsTile<MB, PX, R, XS>;
+  a.tiles_x = (a.W + T::TW - 1) / T::TW;
+  a.tiles_y = (a.H + T::TH - 1) / T::TH;
+  const int64_t nx = (int64_t)a.tiles_x * a.tiles_y * a.B, ny = (a.M + 32 * MB - 1) / (32 * MB);
+  MSL_TRY(need(nx < (1ll << 31) && ny <= 65535, "conv: sizes too large"));
+  const dim3 grid((unsigned)nx, (unsigned)ny);
+  switch ((xbf16 ? 2 : 0) + (a.vec ? 1 : 0)) {
+    case 3: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, true, true>), grid, dim3(256), T::LDS, st, a); break;
+    case 2: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, true, false>), grid, dim3(256), T::LDS, st, a); break;
+    case 1: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, false, true>), grid, dim3(256), T::LDS, st, a); break;
+    default: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, false, false>), grid, dim3(256), T::LDS, st, a); break;
+  }
+  return launched("conv kernel");
+}
+
+// Stride-1 convolution of M output channels on register rows; flip: the input gradient's weights.
+msl_status launch_conv_rows(RowsArgs a, int Co, int C, bool flip, const uint16_t* w16, uint16_t* wscratch, bool xbf16,
+                            hipStream_t st) {
+  a.Mp = pad16(a.M);
+  a.wp = wscratch;
+  a.vec = (a.W % 8 == 0 && aligned(a.x, 16)) ? 1 : 0;
+  a.quads = (a.W % 4 == 0 && aligned(a.y, 8)) ? 1 : 0;
+  const int64_t npack = (int64_t)a.Mp * 9 * pad16(a.C);
+  hipLaunchKernelGGL(k_pack_rows, dim3(blocks_for(npack)), dim3(256), 0, st, Co, C, flip ? 1 : 0, a.Mp, w16, wscratch);
+  // One or two 32-channel blocks per workgroup (four measured slower where the planes of float32
+  // gradients are large: 192 channels of 32x128x128, 305 us against 186).  Per workgroup of large work:
+  // 64 x 4 pixels of 64 channels (64x64 channels at 32x128x128 55 us against 60 as 32 x 8) and, in rows too
+  // short for that, 32 x 8 (256 channels at 32x32x32 49 us against 86); 128 x 4 pixels of 32 channels where
+  // many input channels make the products outweigh the output (96 channels at 32x256x256 192 us against
+  // 210).  Small work goes in small pieces, two rows a wavefront: below two workgroups per compute unit
+  // the large ones leave the chip idle (256 channels at 2x32x32 24 us against 31).
+  const int64_t blocks = (a.M + 63) / 64;
+  auto groups = [&](int tw, int th) { return (int64_t)((a.W + tw - 1) / tw) * ((a.H + th - 1) / th) * a.B * blocks; };
+  if (a.M <= 32) {
+    if (a.C >= 64 && a.W >= 96 && groups(128, 4) >= 512) return launch_rows_t<1, 1, 4, true>(a, xbf16, st);
+    return launch_rows_t<1, 1, 2, false>(a, xbf16, st);
+  }
+  if (a.W >= 48 && groups(64, 4) >= 512) return launch_rows_t<2, 2, 2, false>(a, xbf16, st);
+  if (a.W < 48 && groups(32, 8) >= 512) return launch_rows_t<2, 1, 4, false>(a, xbf16, st);
+  return launch_rows_t<2, 1, 2, false>(a, xbf16, st);
+}
+
 // Halo-tile shape of a convolution with M output rows and Ho x Wo outputs per image: rows per
 // workgroup 32, 64 or 128 (one block up to 128 rows), pixels 8192 / MT as a TH x TW block, TW the
 // largest power of two <= min(Wo, 64).  Packs the weights into wscratch first (k_pack_weights,
@@ -1309,6 +1651,15 @@ msl_status msl_nn_conv3x3(int32_t Co, int32_t C, int32_t B, int32_t H, int32_t W
   MSL_TRY(check_ptr(y, y_bf16 ? 2 : 4, "y"));
   MSL_TRY(check_ptr(wscratch, 16, "wscratch"));
   MSL_TRY(need((int64_t)C * 9 < (1 << 30) && (int64_t)B * H * W < (1ll << 40), "conv: sizes too large"));
+  // k_conv_rows addresses 16 channels with 32 bits; its 32-pixel blocks waste half in rows of 16 and less
+  if (stride == 1 && W > 16 && (int64_t)B * H * W < (1ll << 26)) {
+    RowsArgs r{};
+    r.M = Co; r.C = C; r.B = B; r.H = H; r.W = W;
+    r.relu = relu ? 1 : 0;
+    r.ybf16 = y_bf16 ? 1 : 0;
+    r.x = x; r.bias = bias; r.y = y;
+    return launch_conv_rows(r, Co, C, false, w16, wscratch, x_bf16 != 0, static_cast<hipStream_t>(hip_stream));
+  }
   HaloArgs a{};
   a.M = Co; a.C = C; a.B = B; a.H = H; a.W = W; a.s = stride; a.Ho = H / stride; a.Wo = W / stride;
   a.relu = relu ? 1 : 0;
@@ -1330,6 +1681,13 @@ msl_status msl_nn_conv3x3_adjoint(int32_t Co, int32_t C, int32_t B, int32_t H, i
     // sub-pixel form, a 2x2 convolution over dy with 4 C rows (see k_conv_halo)
     MSL_TRY(check_ptr(wscratch, 16, "wscratch"));
     MSL_TRY(need((int64_t)C * 9 < (1 << 30) && (int64_t)B * H * W < (1ll << 40), "conv adjoint: sizes too large"));
+    if (stride == 1 && W > 16 && (int64_t)B * H * W < (1ll << 26)) {
+      RowsArgs r{};
+      r.M = C; r.C = Co; r.B = B; r.H = H; r.W = W;
+      r.accum = accumulate ? 1 : 0;
+      r.x = dy16; r.y = dx;
+      return launch_conv_rows(r, Co, C, true, w16, wscratch, true, static_cast<hipStream_t>(hip_stream));
+    }
     HaloArgs h{};
     h.M = stride == 1 ? C : 4 * C;
     h.C = Co; h.B = B; h.s = 1;

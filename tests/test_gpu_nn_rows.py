@@ -1,0 +1,76 @@
+"""Stride-1 3x3 convolutions (forward and input gradient) at the edges of their tiles.
+
+The reference is the sum over the nine taps in float64 of the same bfloat16 operands.  Each
+output is a float32 sum of 9 C products (exact in float32) and a bias, so it is within
+(9 C + 2) 2^-24 times the sum of the products' magnitudes, and a bfloat16 output within 2^-8 of its
+magnitude (the unit roundoff) more.  Shapes cover rows shorter than a 32-pixel block and one over it,
+columns that end inside a group of eight, one row, channel counts around the chunk of 16 and the
+blocks of 32 and 64 and every tile shape of the dispatch (the large ones take 512 workgroups).
+"""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def T():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2212_01253_amd import nn
+    return nn
+
+
+def conv64(x, w):
+    """x [C][B][H][W], w [O][C][3][3] float64 -> [O][B][H][W], padding 1."""
+    C, B, H, W = x.shape
+    xp = torch.nn.functional.pad(x, (1, 1, 1, 1))
+    y = torch.zeros((w.shape[0], B * H * W), dtype=torch.float64, device=x.device)
+    for i in range(3):
+        for j in range(3):
+            y += w[:, :, i, j].contiguous() @ xp[:, :, i:i + H, j:j + W].reshape(C, -1)
+    return y.reshape(-1, B, H, W)
+
+
+def shifted(t, by):
+    """A copy of t whose storage starts `by` elements into an aligned buffer."""
+    buf = torch.zeros(t.numel() + by, dtype=t.dtype, device=t.device)
+    v = buf[by:].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("O,C,B,H,W", [
+    (1, 1, 1, 1, 17), (32, 16, 2, 9, 18), (33, 17, 1, 8, 31), (31, 15, 2, 10, 32), (64, 33, 1, 5, 33), (65, 2, 3, 7, 34),
+    (5, 48, 1, 12, 48), (70, 20, 1, 6, 95), (96, 64, 1, 4, 130), (16, 130, 1, 3, 64), (128, 31, 1, 17, 24),
+    (40, 3, 32, 64, 64), (34, 5, 64, 61, 20), (9, 65, 32, 61, 98)])
+@pytest.mark.parametrize("xbf16,ybf16,shift", [(True, True, 0), (False, True, 0), (True, False, 1), (False, True, 1)])
+def test_rows_convolution(T, O, C, B, H, W, xbf16, ybf16, shift):
+    gen = torch.Generator(device="cuda").manual_seed(O * 1000 + C)
+    rn = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+    x, w, bias = rn(C, B, H, W), (rn(O, C, 3, 3) / (3 * C ** 0.5)).to(torch.bfloat16), rn(O)
+    xb = x.to(torch.bfloat16)
+    arg = shifted(xb.view(torch.int16) if xbf16 else x, shift)
+    y = shifted(torch.zeros((O, B, H, W), dtype=torch.int16 if ybf16 else torch.float32, device="cuda"), shift)
+    w16 = w.view(torch.int16).reshape(-1)
+    T.conv3x3(O, C, B, H, W, 1, w16, arg, y, bias=bias, relu=True)
+    ref = conv64(xb.double(), w.double()) + bias.double().view(-1, 1, 1, 1)
+    mag = conv64(xb.double().abs(), w.double().abs()) + bias.double().abs().view(-1, 1, 1, 1)
+    tol = (9 * C + 2) * 2.0 ** -24 * mag + (2.0 ** -8 * ref.abs() if ybf16 else 0.0)
+    got = (y.contiguous().view(torch.bfloat16) if ybf16 else y).double()
+    assert bool(((got - torch.relu(ref)).abs() <= tol).all())
+    # the input gradient, alone and added onto another
+    dy = rn(O, B, H, W).to(torch.bfloat16)
+    dy16 = shifted(dy.view(torch.int16), shift)
+    wt = w.double().flip(2, 3).transpose(0, 1).contiguous()
+    ref, mag = conv64(dy.double(), wt), conv64(dy.double().abs(), wt.abs())
+    base = rn(C, B, H, W)
+    dx = shifted(base, shift)
+    T.conv3x3_adjoint(O, C, B, H, W, 1, w16, dy16, dx)
+    tol = (9 * O + 2) * 2.0 ** -24 * mag
+    assert bool(((dx.double() - ref).abs() <= tol).all())
+    if shift % 2 == 0:   # (accumulation asks for 8-byte alignment)
+        acc = base.clone()
+        T.conv3x3_adjoint(O, C, B, H, W, 1, w16, dy16, acc, accumulate=True)
+        assert torch.equal(acc, base + dx)
