@@ -1089,6 +1089,199 @@ __global__ void __launch_bounds__(192) k_conv_wgrad_halo(WgradArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Weight gradient of a stride-1 convolution straight from the planes.  With the pixels as the
+// product's depth, both operands lie in memory as the MFMA wants them: a lane's eight depth
+// values are eight neighbouring pixels of one channel, one 16-byte read.  A wavefront owns 32
+// input x 32 output channels and all nine taps (144 accumulators) and walks down the rows of a strip
+// of 32 pixels: per row of the input it forms the three column shifts in registers
+// (v_alignbit with the pixels left and right of the eight) and multiplies each with the output
+// gradients of the three rows that meet it, which it keeps from row to row; nothing passes through
+// LDS, and the reads of a row are in flight while the row before is multiplied.  The four
+// wavefronts of a workgroup take different strips and row ranges (units) of the same channels and
+// add their sums in LDS at the end, so a workgroup writes one part.
+//
+// Bound by the planes' scattered 64-byte pieces (32 to 64 planes per wavefront), not by latency: one
+// wavefront per SIMD with seven rows in flight measured the same (96 -> 32 channels at 32x256x256 372 us)
+// or slower (384 -> 128 at 32x64x64 387 against 263).  Against the halo kernel: 32 -> 32 channels at
+// 32x256x256 240 -> 111 us, 96 -> 32 580 -> 376, 64 -> 64 at 32x128x128 209 -> 69, 384 -> 128 at 32x64x64
+// 470 -> 263, 256 -> 256 at 32x32x32 203 -> 70; against the patch-column product that served widths
+// not a multiple of 8: 150 -> 12 channels at 8x200x66 294 -> 49 us.
+//
+// Parts are [tap][o][c]; k_sum_wgrad adds them.  The rows of a unit cost two more input rows at its
+// ends, so units are tall where there are enough of them.
+constexpr int kWgStrip = 32;
+constexpr int kWgradGroups = 512;   // workgroups wanted: two per compute unit
+
+struct WrowsArgs {
+  int Co, C, B, H, W;
+  int rh, strips, chunks;   // rows per unit, strips per row, units per strip
+  int units, per_part;      // units of all images, units per part (a multiple of four)
+  int cblocks, oblocks;
+  const uint16_t* dy16;     // [Co][B][H][W]
+  const void* x;            // [C][B][H][W]
+  float* partials;          // [parts][9][Co][C]
+};
+
+// Pixel x0 of the row at byte offset off (of pixel 0) as bfloat16 bits, zero outside [0, W).
+template <bool XBF16>
+__device__ __forceinline__ uint32_t load1(const void* base, uint32_t off, int x0, int W) {
+  if (x0 < 0 || x0 >= W) return 0u;
+  if constexpr (XBF16) return ld_bytes<uint16_t>(base, off + 2u * (uint32_t)x0);
+  else return to_bf16(ld_bytes<float>(base, off + 4u * (uint32_t)x0));
+}
+
+template <bool XBF16, bool VEC>
+__global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float wr_smem[];   // [2][144][64]
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
+  const int id = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int nco = a.cblocks * a.oblocks, part = id / nco, co = id - part * nco;
+  const int c = (co % a.cblocks) * 32 + (lane & 31), o = (co / a.cblocks) * 32 + (lane & 31);
+  const int64_t plane = (int64_t)a.H * a.W, cstride = (int64_t)a.B * plane;
+  constexpr uint32_t ES = XBF16 ? 2u : 4u;
+  const bool c_ok = c < a.C, o_ok = o < a.Co;
+  // this lane's channel planes (a channel that is not there reads the last one and is zeroed)
+  const char* const xc = static_cast<const char*>(a.x) + (int64_t)min(c, a.C - 1) * cstride * ES;
+  const char* const dc = reinterpret_cast<const char*>(a.dy16) + (int64_t)min(o, a.Co - 1) * cstride * 2;
+  f32x16 acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) acc[t] = f32x16{};
+  const int u1 = min(a.units, (part + 1) * a.per_part);
+  for (int u = part * a.per_part + wave; u < u1; u += 4) {
+    int t = u;
+    const int sx = t % a.strips;
+    t /= a.strips;
+    const int y0 = (t % a.chunks) * a.rh, b = t / a.chunks, y1 = min(a.H, y0 + a.rh);
+    // the lane's sixteen pixels px .. px + 15, eight per depth step; the pixel left of the strip (lower half
+    // of the lanes) and right of it (upper half) come in `edge`, where the shifted operands want them
+    const int px = sx * kWgStrip + 16 * half;
+    const uint32_t img = (uint32_t)((int64_t)b * plane);
+    struct XRow {
+      u32x4 v[2];
+      uint32_t edge;
+    };
+    XRow xr[2];
+    u32x4 dr[4][2];
+    auto load_x = [&](int y, XRow& q) {
+      const bool in = c_ok && y >= 0 && y < a.H;
+      const uint32_t row = (img + (uint32_t)(y * a.W)) * ES;
+      q.edge = 0u;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int p = px + 8 * k;
+        q.v[k] = u32x4{0u, 0u, 0u, 0u};
+        if (in && p < a.W) q.v[k] = load8<XBF16, VEC>(xc, row + (uint32_t)p * ES, p, a.W);
+      }
+      if (in) q.edge = load1<XBF16>(xc, row, half ? px + 16 : px - 1, a.W) << (half ? 0 : 16);
+    };
+    auto load_d = [&](int y, u32x4 (&q)[2]) {
+      const bool in = o_ok && y >= y0 && y < y1;
+      const uint32_t row = (img + (uint32_t)(y * a.W)) * 2u;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int p = px + 8 * k;
+        q[k] = u32x4{0u, 0u, 0u, 0u};
+        if (in && p < a.W) q[k] = load8<true, VEC>(dc, row + (uint32_t)p * 2u, p, a.W);
+      }
+    };
+    // row y of the input meets gradient rows y + 1, y, y - 1 (taps ky = 0, 1, 2)
+    auto products = [&](const XRow& q, const u32x4 (&up)[2], const u32x4 (&mid)[2], const u32x4 (&down)[2]) {
+      // lower half of the lanes: left neighbour the edge, right one the upper half's first pixels; upper
+      // half: left the lower half's last pixels, right the edge
+      const uint32_t left = __builtin_amdgcn_permlane32_swap(q.edge, q.v[1].w, false, false)[0];
+      const uint32_t right = __builtin_amdgcn_permlane32_swap(q.v[0].x, q.edge, false, false)[1];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const u32x4 v = q.v[k];
+        const uint32_t l = k ? q.v[0].w : left, r = k ? right : q.v[1].x;
+        const uint32_t m0 = __builtin_amdgcn_alignbit(v.y, v.x, 16), m1 = __builtin_amdgcn_alignbit(v.z, v.y, 16),
+                       m2 = __builtin_amdgcn_alignbit(v.w, v.z, 16);
+        const u32x4 lo = {__builtin_amdgcn_alignbit(v.x, l, 16), m0, m1, m2};
+        const u32x4 hi = {m0, m1, m2, __builtin_amdgcn_alignbit(r, v.w, 16)};
+        const bf16x8 xs[3] = {__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, hi)};
+        const bf16x8 d[3] = {__builtin_bit_cast(bf16x8, up[k]), __builtin_bit_cast(bf16x8, mid[k]),
+                             __builtin_bit_cast(bf16x8, down[k])};
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+          for (int kx = 0; kx < 3; ++kx)
+            acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[ky], xs[kx], acc[3 * ky + kx], 0, 0, 0);
+      }
+    };
+    // rows y = y0 - 1 .. y1 of the input; slot of gradient row y0 + q: (q + 2) & 3
+    load_d(y0 - 2, dr[0]);
+    load_d(y0 - 1, dr[1]);
+    load_d(y0, dr[2]);
+    load_x(y0 - 1, xr[0]);
+    for (int y = y0 - 1; y <= y1; y += 4) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {   // row y + s: gradient rows in slots s + 2 (up), s + 1, s
+        if (y + s <= y1) {
+          load_x(y + s + 1, xr[(s + 1) & 1]);
+          load_d(y + s + 2, dr[(s + 3) & 3]);
+          products(xr[s & 1], dr[(s + 2) & 3], dr[(s + 1) & 3], dr[s & 3]);
+        }
+      }
+    }
+  }
+  // the four wavefronts' sums: 2 and 3 onto 0 and 1, then 1 onto 0
+#pragma unroll
+  for (int step = 2; step >= 1; step >>= 1) {
+    if (wave >= step && wave < 2 * step) {
+      float* const d = wr_smem + (wave - step) * 9216 + lane;
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) d[(16 * t + e) * 64] = acc[t][e];
+    }
+    __syncthreads();
+    if (wave < step) {
+      const float* const d = wr_smem + wave * 9216 + lane;
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] += d[(16 * t + e) * 64];
+    }
+    __syncthreads();
+  }
+  if (wave != 0 || !c_ok) return;
+  // accumulator element 4i + j of lane l: output channel 8i + 4 (l / 32) + j of the block, input channel l mod 32
+  float* const P = a.partials + (int64_t)part * 9 * a.Co * a.C;
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int oo = (co / a.cblocks) * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+      if (oo < a.Co) P[((int64_t)t * a.Co + oo) * a.C + c] = acc[t][e];
+    }
+}
+
+// dw[(o C + c) 9 + t] = sum over the parts of P[part][t][o][c], in the order of k_sum_parts.
+__global__ void __launch_bounds__(256) k_sum_wgrad(int n, int parts, const float* __restrict__ P, float* __restrict__ dw) {
+  __shared__ float part_sum[16][17];
+  const int ei = threadIdx.x & 15, sl = threadIdx.x >> 4;
+  const int64_t mn = (int64_t)9 * n, e = (int64_t)blockIdx.x * 16 + ei;
+  float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
+  if (e < mn) {
+    int s = sl;
+    for (; s + 48 < parts; s += 64) {
+      a0 += P[(int64_t)s * mn + e];
+      a1 += P[(int64_t)(s + 16) * mn + e];
+      a2 += P[(int64_t)(s + 32) * mn + e];
+      a3 += P[(int64_t)(s + 48) * mn + e];
+    }
+    for (; s < parts; s += 16) a0 += P[(int64_t)s * mn + e];
+  }
+  part_sum[sl][ei] = (a0 + a1) + (a2 + a3);
+  __syncthreads();
+  if (sl == 0 && e < mn) {
+    float acc = 0.0f;
+    for (int q = 0; q < 16; ++q) acc += part_sum[q][ei];
+    dw[(e % n) * 9 + e / n] = acc;
+  }
+}
+
 // C[i] = sum over the parts s of P[s][i].  A workgroup takes 16 consecutive elements; its 16 thread
 // slices each sum the parts s = slice, slice + 16, ... of every element (four independent loads in
 // flight per thread), then slice sums are added in slice order, so the result does not depend on the
@@ -1722,6 +1915,38 @@ msl_status msl_nn_conv3x3_weight_grad(int32_t Co, int32_t C, int32_t B, int32_t 
   MSL_TRY(check_ptr(dw, 4, "dw"));
   MSL_TRY(check_ptr(partials, 4, "partials"));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  if (stride == 1 && (int64_t)B * H * W < (1ll << 29)) {   // (a plane's byte offsets fit 32 bits)
+    WrowsArgs w{};
+    w.Co = Co; w.C = C; w.B = B; w.H = H; w.W = W;
+    w.strips = (W + kWgStrip - 1) / kWgStrip;
+    w.cblocks = (C + 31) / 32;
+    w.oblocks = (Co + 31) / 32;
+    const int64_t nco = (int64_t)w.cblocks * w.oblocks;
+    const int want = (int)std::max<int64_t>(1, (kWgradGroups + nco - 1) / nco);   // parts that fill the GPU
+    w.rh = 32;
+    while (w.rh > 4 && (int64_t)B * w.strips * ((H + w.rh - 1) / w.rh) < 4 * want) w.rh /= 2;
+    w.chunks = (H + w.rh - 1) / w.rh;
+    const int64_t units = (int64_t)B * w.strips * w.chunks;
+    MSL_TRY(need(units < (1ll << 30) && (int64_t)C * Co < (1 << 27), "conv weight gradient: sizes too large"));
+    w.units = (int)units;
+    int parts = (int)std::min<int64_t>({(int64_t)splits, (int64_t)want, (units + 3) / 4});
+    w.per_part = (int)((units + 4 * (int64_t)parts - 1) / (4 * (int64_t)parts)) * 4;
+    parts = (int)((units + w.per_part - 1) / w.per_part);
+    MSL_TRY(need(nco * parts < (1ll << 31), "conv weight gradient: sizes too large"));
+    w.dy16 = dy16; w.x = x; w.partials = partials;
+    const bool vec = W % 8 == 0 && aligned(x, 16) && aligned(dy16, 16);
+    const dim3 grid((unsigned)(nco * parts));
+    const int lds = 2 * 9216 * (int)sizeof(float);
+    switch ((x_bf16 ? 2 : 0) + (vec ? 1 : 0)) {
+      case 3: hipLaunchKernelGGL((k_conv_wgrad_rows<true, true>), grid, dim3(256), lds, st, w); break;
+      case 2: hipLaunchKernelGGL((k_conv_wgrad_rows<true, false>), grid, dim3(256), lds, st, w); break;
+      case 1: hipLaunchKernelGGL((k_conv_wgrad_rows<false, true>), grid, dim3(256), lds, st, w); break;
+      default: hipLaunchKernelGGL((k_conv_wgrad_rows<false, false>), grid, dim3(256), lds, st, w); break;
+    }
+    const int64_t mn = (int64_t)Co * C * 9;
+    hipLaunchKernelGGL(k_sum_wgrad, dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, Co * C, parts, partials, dw);
+    return launched("conv weight gradient kernels");
+  }
   if ((W / stride) % 8 == 0) {
     // halo tiles (k_conv_wgrad_halo): 128 / s pixels per tile, as TH x TW, TW <= 64
     WgradArgs w{};

@@ -1,11 +1,13 @@
-"""Stride-1 3x3 convolutions (forward and input gradient) at the edges of their tiles.
+"""Stride-1 3x3 convolutions (forward, input and weight gradient) at the edges of their tiles.
 
 The reference is the sum over the nine taps in float64 of the same bfloat16 operands.  Each
 output is a float32 sum of 9 C products (exact in float32) and a bias, so it is within
 (9 C + 2) 2^-24 times the sum of the products' magnitudes, and a bfloat16 output within 2^-8 of its
 magnitude (the unit roundoff) more.  Shapes cover rows shorter than a 32-pixel block and one over it,
 columns that end inside a group of eight, one row, channel counts around the chunk of 16 and the
-blocks of 32 and 64 and every tile shape of the dispatch (the large ones take 512 workgroups).
+blocks of 32 and 64 and every tile shape of the dispatch (the large ones take 512 workgroups).  A weight
+gradient is a float32 sum over the pixels, within their count (and the parts') times 2^-24 of the sum
+of the magnitudes.
 """
 import pytest
 
@@ -74,3 +76,26 @@ def test_rows_convolution(T, O, C, B, H, W, xbf16, ybf16, shift):
         acc = base.clone()
         T.conv3x3_adjoint(O, C, B, H, W, 1, w16, dy16, acc, accumulate=True)
         assert torch.equal(acc, base + dx)
+
+
+@pytest.mark.parametrize("O,C,B,H,W,splits", [
+    (1, 1, 1, 1, 1, 1), (2, 3, 1, 3, 2, 4), (33, 31, 2, 5, 33, 3), (32, 32, 1, 4, 16, 1), (31, 65, 3, 37, 31, 64),
+    (64, 16, 1, 33, 64, 7), (5, 40, 2, 66, 40, 2), (70, 2, 1, 9, 95, 2048), (3, 7, 2, 130, 8, 16)])
+@pytest.mark.parametrize("xbf16,shift", [(True, 0), (False, 0), (True, 1), (False, 1)])
+def test_rows_weight_gradient(T, O, C, B, H, W, splits, xbf16, shift):
+    gen = torch.Generator(device="cuda").manual_seed(O * 1000 + C)
+    x = torch.randn((C, B, H, W), device="cuda", generator=gen)
+    dy = torch.randn((O, B, H, W), device="cuda", generator=gen).to(torch.bfloat16)
+    xb = x.to(torch.bfloat16)
+    arg = shifted(xb.view(torch.int16) if xbf16 else x, shift)
+    dw = torch.full((O, C, 3, 3), float("nan"), device="cuda")
+    parts = torch.full((splits * O * C * 9,), float("nan"), device="cuda")
+    T.conv3x3_weight_grad(O, C, B, H, W, 1, shifted(dy.view(torch.int16), shift), arg, dw, splits, parts)
+
+    def ref(a, b):
+        ap, n = torch.nn.functional.pad(a, (1, 1, 1, 1)), B * H * W
+        taps = [ap[:, :, i:i + H, j:j + W].reshape(C, n).t().contiguous() for i in range(3) for j in range(3)]
+        return torch.stack([b.reshape(O, n) @ t for t in taps], dim=2).reshape(O, C, 3, 3)
+
+    r, mag = ref(xb.double(), dy.double()), ref(xb.double().abs(), dy.double().abs())
+    assert bool(((dw.double() - r).abs() <= (B * H * W + splits) * 2.0 ** -24 * mag).all())
