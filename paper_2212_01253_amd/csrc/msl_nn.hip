@@ -110,22 +110,17 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
-// 3x3 convolutions as implicit products: the same tiles, LDS layout and MFMA
-// sequence as k_gemm_bf16, with the patch operand formed while it is loaded
-// (no patch matrix in memory).  k runs over (channel, tap), tap = 3 (dy + 1) +
-// (dx + 1), in the patch matrix's row order, so the forward product is the
-// explicit one bit for bit.
+// The input gradient of a stride-2 convolution into an array without 8-byte alignment, as an implicit
+// product: the tiles, LDS layout and MFMA sequence of k_gemm_bf16, with the patch operand formed while
+// it is loaded.  k runs over (output channel, tap), tap = 3 (dy + 1) + (dx + 1).
 
 struct ConvArgs {
-  int Co, C, B, H, W, s, Ho, Wo, relu;
-  int K;      // GEMM depth: C * 9 (forward) or Co * 9 (input gradient)
-  int64_t N;  // GEMM columns: B * Ho * Wo (forward) or B * H * W (input gradient)
+  int Co, C, B, H, W, s, Ho, Wo;
+  int K;      // depth: Co * 9
+  int64_t N;  // columns: B * H * W
   const uint16_t* w16;  // [Co][C * 9]
-  const float* x;       // forward input [C][B][H][W]
-  const uint16_t* x16;  // weight gradient: the input as bfloat16 bits instead of x (or nullptr)
-  const uint16_t* dy16; // input gradient: output gradient [Co][B][Ho][Wo], bfloat16
-  const float* bias;
-  float* y;             // forward output [Co][B][Ho][Wo] or input gradient [C][B][H][W]
+  const uint16_t* dy16; // output gradient [Co][B][Ho][Wo], bfloat16
+  float* y;             // input gradient [C][B][H][W]
 };
 
 // Stores v[0..3] and v[4..7] as two 8-byte LDS writes.
@@ -149,93 +144,6 @@ __device__ __forceinline__ void mfma_tile(const uint16_t (&As)[TM][KP], const ui
     const bf16x4 b1 = *reinterpret_cast<const bf16x4*>(&Bs[wn + 32 + (lane & 31)][kq]);
     acc0 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b0, acc0, 0, 0, 0);
     acc1 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b1, acc1, 0, 0, 0);
-  }
-}
-
-// y = act(conv(x) + bias): M = Co, N = B Ho Wo, K = C 9.  Thread t loads
-// weight row m0 + t/4, k 8 (t mod 4) .. +8, and the 16 patch values of
-// pixel n0 + t mod 128 at k 16 (t / 128) .. +16.
-__global__ void __launch_bounds__(256) k_conv_fwd(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[TM][KP];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[TN][KP];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int m0 = blockIdx.y * TM;
-  const int64_t n0 = (int64_t)blockIdx.x * TN;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
-  f32x16 acc0 = {}, acc1 = {};
-  const int nl = tid % TN, kh = tid / TN;
-  const int64_t n = n0 + nl;
-  const bool n_ok = n < a.N;
-  int b = 0, i = 0, j = 0;
-  if (n_ok) {
-    j = (int)(n % a.Wo);
-    const int64_t t = n / a.Wo;
-    i = (int)(t % a.Ho);
-    b = (int)(t / a.Ho);
-  }
-  const int y0 = a.s * i - 1, x0 = a.s * j - 1;   // window corner (dy = dx = -1)
-  const int64_t cstride = (int64_t)a.B * a.H * a.W;
-  const float* xb = a.x + (int64_t)b * a.H * a.W;
-  const bool w_vec = (a.K & 7) == 0 && (reinterpret_cast<uintptr_t>(a.w16) & 15) == 0;
-  for (int k0 = 0; k0 < a.K; k0 += TK) {
-    {
-      const int m = tid >> 2, kq = (tid & 3) * 8;
-      const int gm = m0 + m, gk = k0 + kq;
-      uint16_t v[8];
-      if (w_vec && gm < a.Co && gk + 8 <= a.K) {
-        const uint4 u = *reinterpret_cast<const uint4*>(a.w16 + (int64_t)gm * a.K + gk);
-        v[0] = (uint16_t)u.x; v[1] = (uint16_t)(u.x >> 16); v[2] = (uint16_t)u.y; v[3] = (uint16_t)(u.y >> 16);
-        v[4] = (uint16_t)u.z; v[5] = (uint16_t)(u.z >> 16); v[6] = (uint16_t)u.w; v[7] = (uint16_t)(u.w >> 16);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = (gm < a.Co && gk + q < a.K) ? a.w16[(int64_t)gm * a.K + gk + q] : (uint16_t)0;
-      }
-      lds_store8(&As[m][kq], v);
-    }
-    {
-      const int kb = k0 + kh * 16;
-      int c = kb / 9, tap = kb - 9 * c;
-      uint16_t v[16];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        float val = 0.0f;
-        const int yy = y0 + tap / 3, xx = x0 + tap % 3;
-        if (n_ok && kb + q < a.K && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W)
-          val = xb[(int64_t)c * cstride + (int64_t)yy * a.W + xx];
-        v[q] = to_bf16(val);
-        if (++tap == 9) {
-          tap = 0;
-          ++c;
-        }
-      }
-      uint16_t lo[8], hi[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        lo[q] = v[q];
-        hi[q] = v[q + 8];
-      }
-      lds_store8(&Bs[nl][kh * 16], lo);
-      lds_store8(&Bs[nl][kh * 16 + 8], hi);
-    }
-    __syncthreads();
-    mfma_tile(As, Bs, wm, wn, lane, acc0, acc1);
-    __syncthreads();
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int64_t nn = n0 + wn + 32 * h + (lane & 31);
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int m = m0 + wm + 8 * i4 + 4 * (lane >> 5) + jj;
-        if (m < a.Co && nn < a.N) {
-          float v = h ? acc1[4 * i4 + jj] : acc0[4 * i4 + jj];
-          if (a.bias) v += a.bias[m];
-          if (a.relu) v = fmaxf(v, 0.0f);
-          a.y[(int64_t)m * a.N + nn] = v;
-        }
-      }
   }
 }
 
@@ -323,90 +231,9 @@ __global__ void __launch_bounds__(256) k_conv_bwd_data(ConvArgs a) {
   }
 }
 
-// Weight gradient, split along the pixels like msl_nn_gemm_bf16_splitk:
-// part z accumulates dW[o][9c + t] over pixels [z kchunk, (z + 1) kchunk) into
-// partials + z Co 9C.  M = Co, N = 9C, K = B Ho Wo.  Thread t loads dy row
-// m0 + t/4, pixels 8 (t mod 4) .. +8, and the patch values of pixel t mod 32
-// for the 16 (channel, tap) columns n0 + 16 (t / 32) .. +16.
-__global__ void __launch_bounds__(256) k_conv_bwd_weight(ConvArgs a, int kchunk, float* __restrict__ partials) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[TM][KP];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[TN][KP];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
-  f32x16 acc0 = {}, acc1 = {};
-  const int64_t npix = (int64_t)a.B * a.Ho * a.Wo;
-  const int64_t kbeg = (int64_t)blockIdx.z * kchunk;
-  const int64_t kend = kbeg + kchunk < npix ? kbeg + kchunk : npix;
-  const int NC = a.C * 9;
-  const int64_t cstride = (int64_t)a.B * a.H * a.W;
-  const bool dy_vec = (npix & 7) == 0 && (reinterpret_cast<uintptr_t>(a.dy16) & 15) == 0;
-  const int kk = tid & 31, nq = (tid >> 5) * 16;
-  for (int64_t k0 = kbeg; k0 < kend; k0 += TK) {
-    {
-      const int m = tid >> 2, kq = (tid & 3) * 8;
-      const int gm = m0 + m;
-      const int64_t gk = k0 + kq;
-      uint16_t v[8];
-      if (dy_vec && gm < a.Co && gk + 8 <= kend) {
-        const uint4 u = *reinterpret_cast<const uint4*>(a.dy16 + (int64_t)gm * npix + gk);
-        v[0] = (uint16_t)u.x; v[1] = (uint16_t)(u.x >> 16); v[2] = (uint16_t)u.y; v[3] = (uint16_t)(u.y >> 16);
-        v[4] = (uint16_t)u.z; v[5] = (uint16_t)(u.z >> 16); v[6] = (uint16_t)u.w; v[7] = (uint16_t)(u.w >> 16);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = (gm < a.Co && gk + q < kend) ? a.dy16[(int64_t)gm * npix + gk + q] : (uint16_t)0;
-      }
-      lds_store8(&As[m][kq], v);
-    }
-    {
-      const int64_t p = k0 + kk;
-      const bool p_ok = p < kend;
-      int b = 0, i = 0, j = 0;
-      if (p_ok) {
-        j = (int)(p % a.Wo);
-        const int64_t t = p / a.Wo;
-        i = (int)(t % a.Ho);
-        b = (int)(t / a.Ho);
-      }
-      const int y0 = a.s * i - 1, x0 = a.s * j - 1;
-      const int64_t ib = (int64_t)b * a.H * a.W;
-      const int nb = n0 + nq;
-      int c = nb / 9, tap = nb - 9 * c;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        uint16_t val = 0;
-        const int yy = y0 + tap / 3, xx = x0 + tap % 3;
-        if (p_ok && nb + q < NC && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W) {
-          const int64_t e = ib + (int64_t)c * cstride + (int64_t)yy * a.W + xx;
-          val = a.x16 ? a.x16[e] : to_bf16(a.x[e]);
-        }
-        Bs[nq + q][kk] = val;
-        if (++tap == 9) {
-          tap = 0;
-          ++c;
-        }
-      }
-    }
-    __syncthreads();
-    mfma_tile(As, Bs, wm, wn, lane, acc0, acc1);
-    __syncthreads();
-  }
-  float* const P = partials + (int64_t)blockIdx.z * a.Co * NC;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int n = n0 + wn + 32 * h + (lane & 31);
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int m = m0 + wm + 8 * i4 + 4 * (lane >> 5) + jj;
-        if (m < a.Co && n < NC) P[(int64_t)m * NC + n] = h ? acc1[4 * i4 + jj] : acc0[4 * i4 + jj];
-      }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// 3x3 convolutions on halo tiles.  A workgroup owns MT output channels (rows)
+// 3x3 convolutions on halo tiles, for output rows of at most 16 pixels and for images of many pixels
+// (the register-row kernels below serve the others).  A workgroup owns MT output channels (rows)
 // x NT = 8192 / MT pixels of one image, a TH x TW block of output positions.
 // For every chunk of 16 input channels it stages once, in LDS and as
 // bfloat16, the input block the 3x3 windows of its pixels cover (the halo:
@@ -687,36 +514,51 @@ __global__ void __launch_bounds__(256) k_conv_halo(HaloArgs a) {
 // 32x32x32 162 -> 49 us).
 constexpr int kRowsCh = 16;   // input channels per chunk
 
-template <int MB, int PX, int R, bool XS>
+// Stride 2 (ROWS_S2): the columns of a staged row lie apart by parity, [even][odd], so that an operand's
+// pixels, two columns apart, are neighbours; an operand read then feeds one or two MFMAs (the input
+// row's even or odd place decides which kernel rows it meets).  The input gradient of a stride-2
+// convolution (ROWS_SUB) is the 2x2 convolution over dy with 4 C rows that k_conv_halo describes.
+enum RowsMode : int { ROWS_S1 = 0, ROWS_S2 = 1, ROWS_SUB = 2 };
+
+template <int MB, int PX, int R, bool XS, int MODE>
 struct RowsTile {
   static constexpr int WG = 4 / MB;                  // pixel groups: wavefronts side by side in x (XS) or in y
   static constexpr int TW = 32 * PX * (XS ? WG : 1), TH = R * (XS ? 1 : WG);   // output tile
-  static constexpr int HH = TH + 2;                  // staged rows
-  static constexpr int NG = TW / 8 + 2;              // staged groups of 8 columns per row
+  static constexpr int S = MODE == ROWS_S2 ? 2 : 1;
+  static constexpr int NK = MODE == ROWS_SUB ? 2 : 3, NTAP = NK * NK;   // kernel rows and columns, taps
+  static constexpr int LEFT = MODE == ROWS_SUB ? 0 : 8;   // staged columns left of the tile
+  static constexpr int HR = S * (R - 1) + NK;        // input rows of a wavefront
+  static constexpr int HH = S * (TH - 1) + NK;       // staged rows
+  static constexpr int NG = (S * TW + LEFT) / 8 + (MODE == ROWS_S2 ? 0 : 1);   // staged groups of 8 columns per row
   static constexpr int PITCH = NG * 8;               // columns per staged row
   // slots per plane; the planes lie an odd multiple of 64 bytes apart (bank halves of the writes)
   static constexpr int PLANE = (HH * PITCH + 7) / 8 * 8 + 4;
   static constexpr int XSLOTS = 2 * PLANE;           // 16-byte slots of the staged input
-  static constexpr int WSLOTS = MB * 32 * 9 * 2;     // 16-byte slots of the weights: [tap][half][row]
+  static constexpr int WSLOTS = MB * 32 * NTAP * 2;  // 16-byte slots of the weights: [tap][half][row]
   static constexpr int LDS = (XSLOTS + WSLOTS) * 16;
   static constexpr int ITEMS = HH * NG * 4, ROUNDS = (ITEMS + 255) / 256;
+  // slot of staged column `col` in its row
+  __host__ __device__ static constexpr int slot(int col) {
+    if (MODE == ROWS_S2) return (col & 1) * NG * 4 + ((col >> 1) & ~3) + (((col >> 1) & 3) ^ ((col >> 3) & 3));
+    return (col & ~7) + ((col & 7) ^ ((col >> 3) & 7));
+  }
 };
 
 struct RowsArgs {
-  int M, Mp, C, B, H, W, relu, accum, ybf16, vec, quads;
+  int M, Mp, C, B, H, W, Ho, Wo, relu, accum, ybf16, vec, quads;
   int tiles_x, tiles_y;
   const uint16_t* wp;   // packed weights [chunk][tap][half][Mp][8] (k_pack_rows)
   const void* x;        // [C][B][H][W]
   const float* bias;
-  void* y;              // [M][B][H][W]
+  void* y;              // [M][B][Ho][Wo]; ROWS_SUB: [M / 4][B][2 Ho][2 Wo]
 };
 
-// wp[((chunk 9 + t) 2 + half) Mp + m][8] from w16 [Co][9 C]; flip: the input gradient's weights (rows
-// m = input channel, channels = output channels, taps reversed).
-__global__ void __launch_bounds__(256) k_pack_rows(int Co, int C, int flip, int Mp, const uint16_t* __restrict__ w16,
+// wp[((chunk ntap + t) 2 + half) Mp + m][8] from w16 [Co][9 C], the modes of k_pack_weights (0 forward, 1
+// stride-1 input gradient, 2 its sub-pixel form).
+__global__ void __launch_bounds__(256) k_pack_rows(int Co, int C, int mode, int Mp, const uint16_t* __restrict__ w16,
                                                    uint16_t* __restrict__ wp) {
-  const int M = flip ? C : Co, Cin = flip ? Co : C;
-  const int64_t n = (int64_t)pad16(Cin) * 9 * Mp;
+  const int M = mode == 0 ? Co : (mode == 1 ? C : 4 * C), Cin = mode == 0 ? C : Co, ntap = mode == 2 ? 4 : 9;
+  const int64_t n = (int64_t)pad16(Cin) * ntap * Mp;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
     const int q = (int)(e & 7);
     int64_t r = e >> 3;
@@ -724,9 +566,18 @@ __global__ void __launch_bounds__(256) k_pack_rows(int Co, int C, int flip, int 
     r /= Mp;
     const int half = (int)(r & 1);
     r >>= 1;
-    const int t = (int)(r % 9), c = (int)(r / 9) * 16 + half * 8 + q;
+    const int t = (int)(r % ntap), c = (int)(r / ntap) * 16 + half * 8 + q;
     uint16_t v = 0;
-    if (m < M && c < Cin) v = flip ? w16[(int64_t)c * 9 * C + 9 * m + 8 - t] : w16[(int64_t)m * 9 * C + 9 * c + t];
+    if (m < M && c < Cin) {
+      if (mode == 0) {
+        v = w16[(int64_t)m * 9 * C + 9 * c + t];
+      } else if (mode == 1) {
+        v = w16[(int64_t)c * 9 * C + 9 * m + 8 - t];
+      } else {
+        const int ky = sub_tap((m >> 1) & 1, t >> 1), kx = sub_tap(m & 1, t & 1);
+        if (ky >= 0 && kx >= 0) v = w16[(int64_t)c * 9 * C + 9 * (m >> 2) + 3 * ky + kx];
+      }
+    }
     wp[e] = v;
   }
 }
@@ -745,31 +596,48 @@ __device__ __forceinline__ uint32_t to_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
 }
 
-// Eight columns x0 .. x0 + 7 of a channel row as bfloat16 pairs, the one at x0 at byte offset off of
-// base: whole and 16-byte aligned (VEC), or at any alignment and those outside [0, W) zero.
-template <bool XBF16, bool VEC>
+// How a row of pixels may be read: in aligned groups of eight that lie whole in it or whole outside
+// (ROW_VEC), at any alignment in rows of at least eight pixels (ROW_ANY), pixel by pixel (ROW_SHORT).
+enum RowRead : int { ROW_VEC = 0, ROW_ANY = 1, ROW_SHORT = 2 };
+
+// Eight columns x0 .. x0 + 7 of a channel row as bfloat16 pairs, the one at x0 >= 0 inside the row and at
+// byte offset off of base; columns from W on are zero (ROW_ANY reads the row's last eight pixels then and
+// shifts them down).
+template <bool XBF16, int RD>
 __device__ __forceinline__ u32x4 load8(const void* base, uint32_t off, int x0, int W) {
   typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
   typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(2)));
-  if (VEC || (x0 >= 0 && x0 + 7 < W)) {
-    if constexpr (XBF16) {
-      if constexpr (VEC) return ld_bytes<u32x4>(base, off);
-      else return ld_bytes<u32x4a>(base, off);
-    } else {
-      const f32x4a a = ld_bytes<f32x4a>(base, off), b = ld_bytes<f32x4a>(base, off + 16u);
-      return u32x4{to_bf16x2(a.x, a.y), to_bf16x2(a.z, a.w), to_bf16x2(b.x, b.y), to_bf16x2(b.z, b.w)};
-    }
-  }
-  uint64_t h[2] = {0, 0};
+  constexpr uint32_t ES = XBF16 ? 2u : 4u;
+  if constexpr (RD == ROW_SHORT) {
+    uint64_t h[2] = {0, 0};
 #pragma unroll 1
-  for (int i = max(0, -x0); i < min(8, W - x0); ++i) {
-    uint64_t v;
-    if constexpr (XBF16) v = ld_bytes<uint16_t>(base, off + 2u * (uint32_t)i);
-    else v = to_bf16(ld_bytes<float>(base, off + 4u * (uint32_t)i));
-    if (i < 4) h[0] |= v << (16 * i);
-    else h[1] |= v << (16 * (i - 4));
+    for (int i = 0; i < min(8, W - x0); ++i) {
+      uint64_t v;
+      if constexpr (XBF16) v = ld_bytes<uint16_t>(base, off + 2u * (uint32_t)i);
+      else v = to_bf16(ld_bytes<float>(base, off + 4u * (uint32_t)i));
+      if (i < 4) h[0] |= v << (16 * i);
+      else h[1] |= v << (16 * (i - 4));
+    }
+    return u32x4{(uint32_t)h[0], (uint32_t)(h[0] >> 32), (uint32_t)h[1], (uint32_t)(h[1] >> 32)};
   }
-  return u32x4{(uint32_t)h[0], (uint32_t)(h[0] >> 32), (uint32_t)h[1], (uint32_t)(h[1] >> 32)};
+  const int d = RD == ROW_VEC ? 0 : max(0, x0 + 8 - W);   // columns beyond the row
+  const uint32_t o = off - (uint32_t)d * ES;
+  u32x4 u;
+  if constexpr (XBF16) {
+    if constexpr (RD == ROW_VEC) u = ld_bytes<u32x4>(base, o);
+    else u = ld_bytes<u32x4a>(base, o);
+  } else {
+    const f32x4a a = ld_bytes<f32x4a>(base, o), b = ld_bytes<f32x4a>(base, o + 16u);
+    u = u32x4{to_bf16x2(a.x, a.y), to_bf16x2(a.z, a.w), to_bf16x2(b.x, b.y), to_bf16x2(b.z, b.w)};
+  }
+  if (RD == ROW_ANY && d > 0) {
+    const uint64_t l = (uint64_t)u.x | ((uint64_t)u.y << 32), h = (uint64_t)u.z | ((uint64_t)u.w << 32);
+    const uint64_t p = (d & 4) ? h : l, q = (d & 4) ? 0 : h;
+    const int s = 16 * (d & 3);
+    const uint64_t r = (p >> s) | ((q << 1) << (63 - s)), t = q >> s;
+    u = u32x4{(uint32_t)r, (uint32_t)(r >> 32), (uint32_t)t, (uint32_t)(t >> 32)};
+  }
+  return u;
 }
 
 // Workgroups are dealt to the eight XCDs in turn; consecutive tiles, which share halo rows, go to one.
@@ -784,9 +652,10 @@ __device__ __forceinline__ uint32_t quad_xor(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, X == 1 ? 0xb1 : 0x4e, 0xf, 0xf, true);
 }
 
-template <int MB, int PX, int R, bool XS, bool XBF16, bool VEC>
+template <int MB, int PX, int R, bool XS, int MODE, bool XBF16, bool VEC>
 __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
-  using T = RowsTile<MB, PX, R, XS>;
+  using T = RowsTile<MB, PX, R, XS, MODE>;
+  constexpr int NTAP = T::NTAP, NK = T::NK;
   extern __shared__ __attribute__((aligned(16))) u32x4 rows_smem[];
   u32x4* const xs = rows_smem;               // [2][PLANE]
   u32x4* const ws = rows_smem + T::XSLOTS;   // [9][2][32 MB]
@@ -811,11 +680,11 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
   for (int q = 0; q < T::ROUNDS; ++q) {
     const int it = tid + 256 * q, quad = it & 3, rg = it >> 2;
     const int hy = rg / T::NG, g = rg - hy * T::NG;
-    const int yy = oy0 - 1 + hy, xx = ox0 - 8 + 8 * g;
+    const int yy = T::S * oy0 - (MODE == ROWS_SUB ? 0 : 1) + hy, xx = T::S * ox0 - T::LEFT + 8 * g;
     ok[q] = it < T::ITEMS && yy >= 0 && yy < a.H && xx + 7 >= 0 && xx < a.W;
     src[q] = (uint32_t)((int64_t)(4 * quad) * cstride + (int64_t)b * plane + (int64_t)yy * a.W + xx) * ES;
     x0[q] = xx;
-    dst[q] = it < T::ITEMS ? 2 * ((quad >> 1) * T::PLANE + hy * T::PITCH + 8 * g) + (quad & 1) : -1;
+    dst[q] = it < T::ITEMS ? 2 * ((quad >> 1) * T::PLANE + hy * T::PITCH + (MODE == ROWS_S2 ? 4 : 8) * g) + (quad & 1) : -1;
   }
   u32x4 pre[T::ROUNDS][4];
   constexpr int WR = (T::WSLOTS + 255) / 256;
@@ -828,10 +697,10 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
 #pragma unroll
       for (int q = 0; q < T::ROUNDS; ++q) {
         pre[q][k] = u32x4{0u, 0u, 0u, 0u};
-        if (ok[q] && c0 + 4 * (tid & 3) + k < a.C) pre[q][k] = load8<XBF16, VEC>(xk, src[q], x0[q], a.W);
+        if (ok[q] && c0 + 4 * (tid & 3) + k < a.C) pre[q][k] = load8<XBF16, VEC ? ROW_VEC : ROW_ANY>(xk, src[q], x0[q], a.W);
       }
     }
-    const u32x4* const w = reinterpret_cast<const u32x4*>(a.wp) + (int64_t)(c0 >> 4) * 18 * a.Mp;
+    const u32x4* const w = reinterpret_cast<const u32x4*>(a.wp) + (int64_t)(c0 >> 4) * 2 * NTAP * a.Mp;
 #pragma unroll
     for (int q = 0; q < WR; ++q) {
       const int e = min(tid + 256 * q, T::WSLOTS - 1), r = e % (32 * MB), th = e / (32 * MB);
@@ -843,7 +712,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
     for (int q = 0; q < T::ROUNDS; ++q) {
       if (dst[q] >= 0) {
         u32x2* const d = reinterpret_cast<u32x2*>(xs) + dst[q];
-        const int sw = ((x0[q] - ox0 + 8) >> 3) & 7;
+        const int g = (x0[q] - T::S * ox0 + T::LEFT) >> 3, sw = MODE == ROWS_S2 ? g & 3 : g & 7;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {   // columns 2i, 2i + 1
           u32x2 lo, hi;
@@ -851,8 +720,13 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
           lo.y = __builtin_amdgcn_perm(pre[q][3][i], pre[q][2][i], 0x05040100u);
           hi.x = __builtin_amdgcn_perm(pre[q][1][i], pre[q][0][i], 0x07060302u);
           hi.y = __builtin_amdgcn_perm(pre[q][3][i], pre[q][2][i], 0x07060302u);
-          d[2 * ((2 * i) ^ sw)] = lo;
-          d[2 * ((2 * i + 1) ^ sw)] = hi;
+          if constexpr (MODE == ROWS_S2) {
+            d[2 * (i ^ sw)] = lo;
+            d[2 * (T::NG * 4 + (i ^ sw))] = hi;
+          } else {
+            d[2 * ((2 * i) ^ sw)] = lo;
+            d[2 * ((2 * i + 1) ^ sw)] = hi;
+          }
         }
       }
     }
@@ -861,14 +735,14 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
       if ((q + 1) * 256 <= T::WSLOTS || tid + 256 * q < T::WSLOTS) ws[tid + 256 * q] = wpre[q];
     }
   };
-  // operand slots: plane lane / 32, column px 32 + lane % 32 + dx (dx = 0 .. 2 for shifts -1 .. 1) of row 0
-  int bs[3][PX];
+  // operand slots: plane lane / 32, the columns of pixels px 32 + lane % 32 under kernel column dx, row 0
+  int bs[NK][PX];
 #pragma unroll
-  for (int dx = 0; dx < 3; ++dx)
+  for (int dx = 0; dx < NK; ++dx)
 #pragma unroll
     for (int px = 0; px < PX; ++px) {
-      const int col = 7 + dx + wx + 32 * px + (lane & 31), g = col >> 3;
-      bs[dx][px] = (lane >> 5) * T::PLANE + wy * T::PITCH + 8 * g + ((col & 7) ^ (g & 7));
+      const int col = T::S * (wx + 32 * px + (lane & 31)) + T::LEFT + dx - (MODE == ROWS_SUB ? 0 : 1);
+      bs[dx][px] = (lane >> 5) * T::PLANE + T::S * wy * T::PITCH + T::slot(col);
     }
   const int wslot = (lane >> 5) * 32 * MB + cb * 32 + (lane & 31);
   f32x16 acc[R][PX];
@@ -881,20 +755,21 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
     stage();
     __syncthreads();
     if (c0 + kRowsCh < a.C) fetch(c0 + kRowsCh);
-    bf16x8 av[9];
+    bf16x8 av[NTAP];
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) av[tap] = __builtin_bit_cast(bf16x8, ws[tap * 2 * 32 * MB + wslot]);
+    for (int tap = 0; tap < NTAP; ++tap) av[tap] = __builtin_bit_cast(bf16x8, ws[tap * 2 * 32 * MB + wslot]);
 #pragma unroll
-    for (int hr = 0; hr < R + 2; ++hr) {   // staged row wy + hr: kernel row ky of output row hr - ky
+    for (int hr = 0; hr < T::HR; ++hr) {   // input row hr of the wavefront: kernel row ky of output row (hr - ky) / S
 #pragma unroll
-      for (int dx = 0; dx < 3; ++dx)
+      for (int dx = 0; dx < NK; ++dx)
 #pragma unroll
         for (int px = 0; px < PX; ++px) {
           const bf16x8 bv = __builtin_bit_cast(bf16x8, xs[bs[dx][px] + hr * T::PITCH]);
 #pragma unroll
-          for (int ky = 2; ky >= 0; --ky) {
-            const int r = hr - ky;
-            if (r >= 0 && r < R) acc[r][px] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[3 * ky + dx], bv, acc[r][px], 0, 0, 0);
+          for (int ky = NK - 1; ky >= 0; --ky) {
+            const int r = (hr - ky) / T::S;
+            if (hr >= ky && (hr - ky) % T::S == 0 && r < R)
+              acc[r][px] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[NK * ky + dx], bv, acc[r][px], 0, 0, 0);
           }
         }
     }
@@ -908,6 +783,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
     const int m = mc + ml + 8 * (e >> 2) + (e & 3);
     bias[e] = a.bias && m < a.M ? a.bias[m] : 0.0f;
   }
+  const int64_t ocs = (int64_t)a.B * a.Ho * a.Wo;   // pixels of an output channel
   const bool act = a.relu != 0, add = a.bias != nullptr;
   auto out = [&](float v, int e) {
     if (add) v += bias[e];
@@ -916,17 +792,36 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int oy = oy0 + wy + r;
-    if (oy >= a.H) continue;
+    if (oy >= a.Ho) continue;
 #pragma unroll
     for (int px = 0; px < PX; ++px) {
       const f32x16& v = acc[r][px];
       const int ox = ox0 + wx + 32 * px + (lane & 31);
-      if (ox >= a.W) continue;
-      const uint32_t pix = (uint32_t)((int64_t)b * plane + (int64_t)oy * a.W + ox);
+      if (ox >= a.Wo) continue;
+      if constexpr (MODE == ROWS_SUB) {
+        // rows 4c + j of the product: channel c, the 2 x 2 block's position j
+        const int W2 = 2 * a.Wo;
+        const uint32_t o = (uint32_t)(((int64_t)b * 2 * a.Ho + 2 * oy) * W2 + 2 * ox);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (mc + 8 * i + ml >= a.M) continue;
+          float* const d = static_cast<float*>(a.y) + (int64_t)((mc + 8 * i + ml) >> 2) * 4 * ocs + o;
+          float2 u0 = make_float2(v[4 * i], v[4 * i + 1]), u1 = make_float2(v[4 * i + 2], v[4 * i + 3]);
+          if (a.accum) {
+            const float2 p0 = *reinterpret_cast<const float2*>(d), p1 = *reinterpret_cast<const float2*>(d + W2);
+            u0 = make_float2(p0.x + u0.x, p0.y + u0.y);
+            u1 = make_float2(p1.x + u1.x, p1.y + u1.y);
+          }
+          *reinterpret_cast<float2*>(d) = u0;
+          *reinterpret_cast<float2*>(d + W2) = u1;
+        }
+        continue;
+      }
+      const uint32_t pix = (uint32_t)(((int64_t)b * a.Ho + oy) * a.Wo + ox);
       if (a.ybf16 && a.quads) {
         // four channels x four pixels of a lane quad, transposed: each lane stores four pixels of one
         // channel (8 bytes; a channel's 32 pixels by eight lanes)
-        const uint32_t o = 2u * ((uint32_t)(ml + (lane & 3)) * (uint32_t)cstride + (pix & ~3u));
+        const uint32_t o = 2u * ((uint32_t)(ml + (lane & 3)) * (uint32_t)ocs + (pix & ~3u));
         const uint32_t sel = (lane & 1) ? 0x03020706u : 0x05040100u;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -937,21 +832,21 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
           const uint32_t x = quad_xor<2>((lane & 2) ? p : q);
           const u32x2 w = (lane & 2) ? u32x2{x, q} : u32x2{p, x};
           if (mc + 8 * i + ml + (lane & 3) < a.M)
-            *reinterpret_cast<u32x2*>(static_cast<char*>(a.y) + (int64_t)(mc + 8 * i) * cstride * 2 + o) = w;
+            *reinterpret_cast<u32x2*>(static_cast<char*>(a.y) + (int64_t)(mc + 8 * i) * ocs * 2 + o) = w;
         }
       } else if (a.ybf16) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int m = mc + 8 * (e >> 2) + (e & 3);
           if (m + ml < a.M)
-            (static_cast<uint16_t*>(a.y) + (int64_t)m * cstride)[(uint32_t)ml * (uint32_t)cstride + pix] = to_bf16(out(v[e], e));
+            (static_cast<uint16_t*>(a.y) + (int64_t)m * ocs)[(uint32_t)ml * (uint32_t)ocs + pix] = to_bf16(out(v[e], e));
         }
       } else {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int m = mc + 8 * (e >> 2) + (e & 3);
           if (m + ml < a.M) {
-            float* const d = static_cast<float*>(a.y) + (int64_t)m * cstride + ((uint32_t)ml * (uint32_t)cstride + pix);
+            float* const d = static_cast<float*>(a.y) + (int64_t)m * ocs + ((uint32_t)ml * (uint32_t)ocs + pix);
             const float w = out(v[e], e);
             *d = a.accum ? *d + w : w;
           }
@@ -961,136 +856,8 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
   }
 }
 
-// Weight gradient on halo tiles: dw[o][9c + t] = sum over output pixels p of dy[o][p] times the
-// input value of channel c under tap t of p (rounded to bfloat16 as in the forward).  A workgroup of
-// three wavefronts owns 32 input channels x 32 output channels and a range of spatial tiles (its
-// part of the pixel sum); wavefront r computes the three taps of kernel row r.  Per tile it stages
-// the input block of its 32 channels (stage_block, positions channel-contiguous) and the output
-// gradient of its 32 output channels at the tile's pixels ([o][pixel]); k runs over the pixels, 16
-// per 32x32x16 MFMA: A = the channels' values under the tap at 16 pixels (8 per lane, gathered from
-// the staged positions), B = dy at those pixels (8 consecutive per lane, one 16-byte LDS read).
-constexpr int WCK = 32;        // input channels per workgroup
-constexpr int WCKP = WCK + 4;  // staged position stride (bfloat16): 72 bytes
-constexpr int WOC = 32;        // output channels per workgroup tile (a workgroup takes one or two)
-
-struct WgradArgs {
-  int Co, C, B, H, W, s, Ho, Wo;
-  int TW, TH, KT, tiles_x, tiles_y, ntiles, per_part;
-  int vec;
-  const uint16_t* dy16;  // [Co][B][Ho][Wo]
-  const void* x;         // [C][B][H][W], float32 or (XBF16) bfloat16 bits
-  float* partials;       // [parts][Co][9C]
-};
-
-// bfloat16 slots of the staged input block, rounded up to 16 bytes (the dy tile after it is read
-// with 16-byte accesses)
-__host__ __device__ inline int wgrad_xs_slots(int TW, int TH, int s) {
-  const int HW = (TW - 1) * s + 3, HH = (TH - 1) * s + 3;
-  return (HH * HW * WCKP + 7) / 8 * 8;
-}
-
-int wgrad_lds_bytes(int TW, int TH, int s, int ot) {
-  return (wgrad_xs_slots(TW, TH, s) + ot * WOC * (TW * TH + 8)) * (int)sizeof(uint16_t);
-}
-
-template <int OT, bool XBF16>
-__global__ void __launch_bounds__(192) k_conv_wgrad_halo(WgradArgs a) {
-  constexpr int NOC = 32 * OT;                      // output channels of this workgroup
-  extern __shared__ __attribute__((aligned(16))) uint16_t wg_smem[];
-  const int HW = (a.TW - 1) * a.s + 3, HH = (a.TH - 1) * a.s + 3;
-  const int DKP = a.KT + 8;                         // row stride of the staged dy tile
-  uint16_t* const xs = wg_smem;                     // [HH * HW][WCKP]
-  uint16_t* const dys = wg_smem + wgrad_xs_slots(a.TW, a.TH, a.s);   // [NOC][DKP]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int c0 = blockIdx.x * WCK, o0 = blockIdx.y * NOC, part = blockIdx.z;
-  const int kq = 8 * (lane >> 5);
-  const int64_t plane = (int64_t)a.H * a.W, cstride = (int64_t)a.B * plane;
-  const int64_t npix = (int64_t)a.B * a.Ho * a.Wo;
-  const bool vec = a.vec != 0;
-  const bool dvec = (a.Wo & 7) == 0 && (reinterpret_cast<uintptr_t>(a.dy16) & 15) == 0;
-  f32x16 acc[3][OT];                                // [tap column dx][output-channel tile]
-#pragma unroll
-  for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-    for (int ot = 0; ot < OT; ++ot) acc[dx][ot] = f32x16{};
-  const int t0 = part * a.per_part, t1 = min(a.ntiles, t0 + a.per_part);
-  for (int tile = t0; tile < t1; ++tile) {
-    int t = tile;
-    const int ox0 = (t % a.tiles_x) * a.TW;
-    t /= a.tiles_x;
-    const int oy0 = (t % a.tiles_y) * a.TH;
-    const int b = t / a.tiles_y;
-    const int iy0 = oy0 * a.s - 1, ix0 = ox0 * a.s - 1;
-    stage_block<WCK, WCKP, XBF16>(xs, a.x, a.C, c0, cstride, (int64_t)b * plane, a.H, a.W, iy0, ix0, HH, HW, vec);
-    // dy tile: item = (output channel, 8-pixel group of a tile row)
-    const int ng = a.KT / 8;
-    for (int it = tid; it < NOC * ng; it += blockDim.x) {
-      const int oc = it / ng, g = it - oc * ng;
-      const int n = 8 * g, ty = n / a.TW, tx = n - ty * a.TW;
-      const int o = o0 + oc, oy = oy0 + ty, ox = ox0 + tx;
-      uint4 u = make_uint4(0u, 0u, 0u, 0u);
-      if (o < a.Co && oy < a.Ho) {
-        const uint16_t* src = a.dy16 + (int64_t)o * npix + ((int64_t)b * a.Ho + oy) * a.Wo;
-        if (dvec && ox + 7 < a.Wo) {
-          u = *reinterpret_cast<const uint4*>(src + ox);
-        } else {
-          uint16_t v[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) v[q] = ox + q < a.Wo ? src[ox + q] : (uint16_t)0;
-          u.x = (uint32_t)v[0] | ((uint32_t)v[1] << 16);
-          u.y = (uint32_t)v[2] | ((uint32_t)v[3] << 16);
-          u.z = (uint32_t)v[4] | ((uint32_t)v[5] << 16);
-          u.w = (uint32_t)v[6] | ((uint32_t)v[7] << 16);
-        }
-      }
-      *reinterpret_cast<uint4*>(&dys[oc * DKP + n]) = u;
-    }
-    __syncthreads();
-    for (int k0 = 0; k0 < a.KT; k0 += 16) {
-      const int n = k0 + kq;                         // this lane's 8 pixels: n .. n+7, one tile row
-      const int ty = n / a.TW, tx = n - ty * a.TW;
-      bf16x8 bv[OT];
-#pragma unroll
-      for (int ot = 0; ot < OT; ++ot)
-        bv[ot] = *reinterpret_cast<const bf16x8*>(&dys[(32 * ot + (lane & 31)) * DKP + n]);
-      const int base = ((ty * a.s + wave) * HW + tx * a.s) * WCKP + (lane & 31);
-      const int step = a.s * WCKP;
-#pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        bf16x8 av;
-        const uint16_t* src = xs + base + dx * WCKP;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) av[i] = __builtin_bit_cast(__bf16, src[i * step]);
-#pragma unroll
-        for (int ot = 0; ot < OT; ++ot)
-          acc[dx][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv[ot], acc[dx][ot], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-  // accumulator element 4i + j of lane l: channel row 8i + 4 (l / 32) + j, output channel l mod 32
-  const int NC = 9 * a.C;
-#pragma unroll
-  for (int ot = 0; ot < OT; ++ot) {
-    const int o = o0 + 32 * ot + (lane & 31);
-    if (o >= a.Co) continue;
-    float* const P = a.partials + ((int64_t)part * a.Co + o) * NC;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = c0 + 8 * i + 4 * (lane >> 5) + j;
-        if (c < a.C) {
-          P[9 * c + 3 * wave + 0] = acc[0][ot][4 * i + j];
-          P[9 * c + 3 * wave + 1] = acc[1][ot][4 * i + j];
-          P[9 * c + 3 * wave + 2] = acc[2][ot][4 * i + j];
-        }
-      }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Weight gradient of a stride-1 convolution straight from the planes.  With the pixels as the
+// Weight gradient of a convolution straight from the planes.  With the pixels as the
 // product's depth, both operands lie in memory as the MFMA wants them: a lane's eight depth
 // values are eight neighbouring pixels of one channel, one 16-byte read.  A wavefront owns 32
 // input x 32 output channels and all nine taps (144 accumulators) and walks down the rows of a strip
@@ -1104,9 +871,14 @@ __global__ void __launch_bounds__(192) k_conv_wgrad_halo(WgradArgs a) {
 // Bound by the planes' scattered 64-byte pieces (32 to 64 planes per wavefront), not by latency: one
 // wavefront per SIMD with seven rows in flight measured the same (96 -> 32 channels at 32x256x256 372 us)
 // or slower (384 -> 128 at 32x64x64 387 against 263).  Against the halo kernel: 32 -> 32 channels at
-// 32x256x256 240 -> 111 us, 96 -> 32 580 -> 376, 64 -> 64 at 32x128x128 209 -> 69, 384 -> 128 at 32x64x64
-// 470 -> 263, 256 -> 256 at 32x32x32 203 -> 70; against the patch-column product that served widths
-// not a multiple of 8: 150 -> 12 channels at 8x200x66 294 -> 49 us.
+// 32x256x256 240 -> 121 us, 96 -> 32 580 -> 394, 64 -> 64 at 32x128x128 209 -> 78, 384 -> 128 at 32x64x64
+// 470 -> 281, 256 -> 256 at 32x32x32 203 -> 78; against the patch-column product that served widths
+// not a multiple of 8: 150 -> 12 channels at 8x200x66 294 -> 56 us.
+//
+// Stride 2: a strip is 32 pixels of the gradient over 64 of the input, whose even and odd columns are
+// parted in registers (the middle tap takes the even ones, the right tap the odd ones, the left tap the
+// odd ones shifted by one); an even input row meets one gradient row, an odd one two (32 -> 64 channels
+// at 32x256x256 162 -> 89 us, 128 -> 256 at 32x64x64 159 -> 59).
 //
 // Parts are [tap][o][c]; k_sum_wgrad adds them.  The rows of a unit cost two more input rows at its
 // ends, so units are tall where there are enough of them.
@@ -1114,24 +886,24 @@ constexpr int kWgStrip = 32;
 constexpr int kWgradGroups = 512;   // workgroups wanted: two per compute unit
 
 struct WrowsArgs {
-  int Co, C, B, H, W;
+  int Co, C, B, H, W, Ho, Wo;
   int rh, strips, chunks;   // rows per unit, strips per row, units per strip
   int units, per_part;      // units of all images, units per part (a multiple of four)
   int cblocks, oblocks;
-  const uint16_t* dy16;     // [Co][B][H][W]
+  const uint16_t* dy16;     // [Co][B][Ho][Wo]
   const void* x;            // [C][B][H][W]
   float* partials;          // [parts][9][Co][C]
 };
 
-// Pixel x0 of the row at byte offset off (of pixel 0) as bfloat16 bits, zero outside [0, W).
+// The pixel in column x0 of its row, at byte offset off of base, as bfloat16 bits; zero outside [0, W).
 template <bool XBF16>
 __device__ __forceinline__ uint32_t load1(const void* base, uint32_t off, int x0, int W) {
   if (x0 < 0 || x0 >= W) return 0u;
-  if constexpr (XBF16) return ld_bytes<uint16_t>(base, off + 2u * (uint32_t)x0);
-  else return to_bf16(ld_bytes<float>(base, off + 4u * (uint32_t)x0));
+  if constexpr (XBF16) return ld_bytes<uint16_t>(base, off);
+  else return to_bf16(ld_bytes<float>(base, off));
 }
 
-template <bool XBF16, bool VEC>
+template <int S, bool XBF16, int RD>
 __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
   extern __shared__ __attribute__((aligned(16))) float wr_smem[];   // [2][144][64]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
@@ -1143,7 +915,8 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
   const bool c_ok = c < a.C, o_ok = o < a.Co;
   // this lane's channel planes (a channel that is not there reads the last one and is zeroed)
   const char* const xc = static_cast<const char*>(a.x) + (int64_t)min(c, a.C - 1) * cstride * ES;
-  const char* const dc = reinterpret_cast<const char*>(a.dy16) + (int64_t)min(o, a.Co - 1) * cstride * 2;
+  const int64_t oplane = (int64_t)a.Ho * a.Wo;
+  const char* const dc = reinterpret_cast<const char*>(a.dy16) + (int64_t)min(o, a.Co - 1) * (a.B * oplane) * 2;
   f32x16 acc[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) acc[t] = f32x16{};
@@ -1152,75 +925,134 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
     int t = u;
     const int sx = t % a.strips;
     t /= a.strips;
-    const int y0 = (t % a.chunks) * a.rh, b = t / a.chunks, y1 = min(a.H, y0 + a.rh);
+    const int y0 = (t % a.chunks) * a.rh, b = t / a.chunks, y1 = min(a.Ho, y0 + a.rh);
     // the lane's sixteen pixels px .. px + 15, eight per depth step; the pixel left of the strip (lower half
     // of the lanes) and right of it (upper half) come in `edge`, where the shifted operands want them
     const int px = sx * kWgStrip + 16 * half;
-    const uint32_t img = (uint32_t)((int64_t)b * plane);
+    // eight pixels before the lane's (load8 reads as far back at a row's end), in input row S y0 - 1 and in
+    // gradient row y0: offsets from there within the unit's rows fit 32 bits (the host sees to it)
+    const char* const xu = xc + ((int64_t)b * plane + (int64_t)(S * y0 - 1) * a.W + S * px - 8) * ES;
+    const char* const du = dc + ((int64_t)b * oplane + (int64_t)y0 * a.Wo + px - 8) * 2;
+    const uint32_t eo = (half ? 24u : 7u) * ES;   // the edge pixel (stride 1; stride 2: the lower half's)
     struct XRow {
-      u32x4 v[2];
+      u32x4 v[2 * S];
       uint32_t edge;
     };
     XRow xr[2];
     u32x4 dr[4][2];
     auto load_x = [&](int y, XRow& q) {
       const bool in = c_ok && y >= 0 && y < a.H;
-      const uint32_t row = (img + (uint32_t)(y * a.W)) * ES;
+      const uint32_t row = (uint32_t)(y - (S * y0 - 1)) * (uint32_t)a.W * ES;
       q.edge = 0u;
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int p = px + 8 * k;
+      for (int k = 0; k < 2 * S; ++k) {
+        const int p = S * px + 8 * k;
         q.v[k] = u32x4{0u, 0u, 0u, 0u};
-        if (in && p < a.W) q.v[k] = load8<XBF16, VEC>(xc, row + (uint32_t)p * ES, p, a.W);
+        if (in && p < a.W) q.v[k] = load8<XBF16, RD>(xu, row + 8u * (uint32_t)(k + 1) * ES, p, a.W);
       }
-      if (in) q.edge = load1<XBF16>(xc, row, half ? px + 16 : px - 1, a.W) << (half ? 0 : 16);
+      if (S == 1) {
+        if (in) q.edge = load1<XBF16>(xu, row + eo, half ? px + 16 : px - 1, a.W) << (half ? 0 : 16);
+      } else {
+        if (in && !half) q.edge = load1<XBF16>(xu, row + eo, 2 * px - 1, a.W) << 16;
+      }
     };
     auto load_d = [&](int y, u32x4 (&q)[2]) {
       const bool in = o_ok && y >= y0 && y < y1;
-      const uint32_t row = (img + (uint32_t)(y * a.W)) * 2u;
+      const uint32_t row = (uint32_t)(y - y0) * (uint32_t)a.Wo * 2u;
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int p = px + 8 * k;
         q[k] = u32x4{0u, 0u, 0u, 0u};
-        if (in && p < a.W) q[k] = load8<true, VEC>(dc, row + (uint32_t)p * 2u, p, a.W);
+        if (in && p < a.Wo) q[k] = load8<true, RD>(du, row + 16u * (uint32_t)(k + 1), p, a.Wo);
       }
     };
-    // row y of the input meets gradient rows y + 1, y, y - 1 (taps ky = 0, 1, 2)
-    auto products = [&](const XRow& q, const u32x4 (&up)[2], const u32x4 (&mid)[2], const u32x4 (&down)[2]) {
-      // lower half of the lanes: left neighbour the edge, right one the upper half's first pixels; upper
-      // half: left the lower half's last pixels, right the edge
-      const uint32_t left = __builtin_amdgcn_permlane32_swap(q.edge, q.v[1].w, false, false)[0];
-      const uint32_t right = __builtin_amdgcn_permlane32_swap(q.v[0].x, q.edge, false, false)[1];
+    if constexpr (S == 1) {
+      // row y of the input meets gradient rows y + 1, y, y - 1 (taps ky = 0, 1, 2)
+      auto products = [&](const XRow& q, const u32x4 (&up)[2], const u32x4 (&mid)[2], const u32x4 (&down)[2]) {
+        // lower half of the lanes: left neighbour the edge, right one the upper half's first pixels; upper
+        // half: left the lower half's last pixels, right the edge
+        const uint32_t left = __builtin_amdgcn_permlane32_swap(q.edge, q.v[1].w, false, false)[0];
+        const uint32_t right = __builtin_amdgcn_permlane32_swap(q.v[0].x, q.edge, false, false)[1];
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const u32x4 v = q.v[k];
-        const uint32_t l = k ? q.v[0].w : left, r = k ? right : q.v[1].x;
-        const uint32_t m0 = __builtin_amdgcn_alignbit(v.y, v.x, 16), m1 = __builtin_amdgcn_alignbit(v.z, v.y, 16),
-                       m2 = __builtin_amdgcn_alignbit(v.w, v.z, 16);
-        const u32x4 lo = {__builtin_amdgcn_alignbit(v.x, l, 16), m0, m1, m2};
-        const u32x4 hi = {m0, m1, m2, __builtin_amdgcn_alignbit(r, v.w, 16)};
-        const bf16x8 xs[3] = {__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, hi)};
-        const bf16x8 d[3] = {__builtin_bit_cast(bf16x8, up[k]), __builtin_bit_cast(bf16x8, mid[k]),
-                             __builtin_bit_cast(bf16x8, down[k])};
+        for (int k = 0; k < 2; ++k) {
+          const u32x4 v = q.v[k];
+          const uint32_t l = k ? q.v[0].w : left, r = k ? right : q.v[1].x;
+          const uint32_t m0 = __builtin_amdgcn_alignbit(v.y, v.x, 16), m1 = __builtin_amdgcn_alignbit(v.z, v.y, 16),
+                         m2 = __builtin_amdgcn_alignbit(v.w, v.z, 16);
+          const u32x4 lo = {__builtin_amdgcn_alignbit(v.x, l, 16), m0, m1, m2};
+          const u32x4 hi = {m0, m1, m2, __builtin_amdgcn_alignbit(r, v.w, 16)};
+          const bf16x8 xs[3] = {__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, hi)};
+          const bf16x8 d[3] = {__builtin_bit_cast(bf16x8, up[k]), __builtin_bit_cast(bf16x8, mid[k]),
+                               __builtin_bit_cast(bf16x8, down[k])};
 #pragma unroll
-        for (int ky = 0; ky < 3; ++ky)
+          for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
-          for (int kx = 0; kx < 3; ++kx)
-            acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[ky], xs[kx], acc[3 * ky + kx], 0, 0, 0);
+            for (int kx = 0; kx < 3; ++kx)
+              acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[ky], xs[kx], acc[3 * ky + kx], 0, 0, 0);
+        }
+      };
+      // rows y = y0 - 1 .. y1 of the input; slot of gradient row y0 + q: (q + 2) & 3
+      load_d(y0 - 2, dr[0]);
+      load_d(y0 - 1, dr[1]);
+      load_d(y0, dr[2]);
+      load_x(y0 - 1, xr[0]);
+      for (int y = y0 - 1; y <= y1; y += 4) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {   // row y + s: gradient rows in slots s + 2 (up), s + 1, s
+          if (y + s <= y1) {
+            load_x(y + s + 1, xr[(s + 1) & 1]);
+            load_d(y + s + 2, dr[(s + 3) & 3]);
+            products(xr[s & 1], dr[(s + 2) & 3], dr[(s + 1) & 3], dr[s & 3]);
+          }
+        }
       }
-    };
-    // rows y = y0 - 1 .. y1 of the input; slot of gradient row y0 + q: (q + 2) & 3
-    load_d(y0 - 2, dr[0]);
-    load_d(y0 - 1, dr[1]);
-    load_d(y0, dr[2]);
-    load_x(y0 - 1, xr[0]);
-    for (int y = y0 - 1; y <= y1; y += 4) {
+    } else {
+      // input row 2 y (odd 0) or 2 y + 1 (odd 1) with gradient row d under kernel row 1 or 2, and the odd
+      // row with gradient row e under kernel row 0
+      auto products = [&](const XRow& q, int odd, const u32x4 (&d)[2], const u32x4 (&e)[2]) {
+        u32x4 ev[2], od[2];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {   // row y + s: gradient rows in slots s + 2 (up), s + 1, s
-        if (y + s <= y1) {
-          load_x(y + s + 1, xr[(s + 1) & 1]);
-          load_d(y + s + 2, dr[(s + 3) & 3]);
-          products(xr[s & 1], dr[(s + 2) & 3], dr[(s + 1) & 3], dr[s & 3]);
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const u32x4 v = q.v[2 * k + i];
+            ev[k][2 * i] = __builtin_amdgcn_perm(v.y, v.x, 0x05040100u);
+            ev[k][2 * i + 1] = __builtin_amdgcn_perm(v.w, v.z, 0x05040100u);
+            od[k][2 * i] = __builtin_amdgcn_perm(v.y, v.x, 0x07060302u);
+            od[k][2 * i + 1] = __builtin_amdgcn_perm(v.w, v.z, 0x07060302u);
+          }
+        const uint32_t left = __builtin_amdgcn_permlane32_swap(q.edge, od[1].w, false, false)[0];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const u32x4 v = od[k];
+          const u32x4 lo = {__builtin_amdgcn_alignbit(v.x, k ? od[0].w : left, 16), __builtin_amdgcn_alignbit(v.y, v.x, 16),
+                            __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16)};
+          const bf16x8 xs[3] = {__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, ev[k]),
+                                __builtin_bit_cast(bf16x8, v)};
+          const bf16x8 g = __builtin_bit_cast(bf16x8, d[k]);
+#pragma unroll
+          for (int kx = 0; kx < 3; ++kx) {
+            const int t = odd ? 6 + kx : 3 + kx;
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, xs[kx], acc[t], 0, 0, 0);
+            if (odd) acc[kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, e[k]), xs[kx], acc[kx], 0, 0, 0);
+          }
+        }
+      };
+      // gradient row y0 - 1 + q in slot q & 3; odd input rows in xr[1], even ones in xr[0]
+      load_d(y0 - 1, dr[0]);   // (zero: the row above the unit)
+      load_d(y0, dr[1]);
+      load_x(2 * y0 - 1, xr[1]);
+      load_x(2 * y0, xr[0]);
+      for (int y = y0 - 1; y < y1; y += 4) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {   // gradient row y + s in slot s
+          if (y + s < y1) {
+            load_d(y + s + 2, dr[(s + 2) & 3]);
+            products(xr[1], 1, dr[s], dr[(s + 1) & 3]);      // input row 2 (y + s) + 1
+            load_x(2 * (y + s) + 3, xr[1]);
+            if (y + s + 1 < y1) products(xr[0], 0, dr[(s + 1) & 3], dr[s]);   // input row 2 (y + s) + 2
+            load_x(2 * (y + s) + 4, xr[0]);
+          }
         }
       }
     }
@@ -1698,32 +1530,38 @@ msl_status need(bool ok, const char* what) { return ok ? MSL_OK : fail(MSL_ERR_A
 
 msl_status launched(const char* what) { return hip_check(hipGetLastError(), what); }
 
-template <int MB, int PX, int R, bool XS>
+template <int MB, int PX, int R, bool XS, int MODE>
 msl_status launch_rows_t(RowsArgs a, bool xbf16, hipStream_t st) {
-  using T = RowsTile<MB, PX, R, XS>;
-  a.tiles_x = (a.W + T::TW - 1) / T::TW;
-  a.tiles_y = (a.H + T::TH - 1) / T::TH;
+  using T = RowsTile<MB, PX, R, XS, MODE>;
+  static_assert(T::LDS <= 64 * 1024, "LDS of a workgroup");
+  a.tiles_x = (a.Wo + T::TW - 1) / T::TW;
+  a.tiles_y = (a.Ho + T::TH - 1) / T::TH;
   const int64_t nx = (int64_t)a.tiles_x * a.tiles_y * a.B, ny = (a.M + 32 * MB - 1) / (32 * MB);
   MSL_TRY(need(nx < (1ll << 31) && ny <= 65535, "conv: sizes too large"));
   const dim3 grid((unsigned)nx, (unsigned)ny);
-  switch ((xbf16 ? 2 : 0) + (a.vec ? 1 : 0)) {
-    case 3: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, true, true>), grid, dim3(256), T::LDS, st, a); break;
-    case 2: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, true, false>), grid, dim3(256), T::LDS, st, a); break;
-    case 1: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, false, true>), grid, dim3(256), T::LDS, st, a); break;
-    default: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, false, false>), grid, dim3(256), T::LDS, st, a); break;
+  if constexpr (MODE == ROWS_SUB) {   // (its input is a bfloat16 gradient)
+    if (a.vec) hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, MODE, true, true>), grid, dim3(256), T::LDS, st, a);
+    else hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, MODE, true, false>), grid, dim3(256), T::LDS, st, a);
+  } else {
+    switch ((xbf16 ? 2 : 0) + (a.vec ? 1 : 0)) {
+      case 3: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, MODE, true, true>), grid, dim3(256), T::LDS, st, a); break;
+      case 2: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, MODE, true, false>), grid, dim3(256), T::LDS, st, a); break;
+      case 1: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, MODE, false, true>), grid, dim3(256), T::LDS, st, a); break;
+      default: hipLaunchKernelGGL((k_conv_rows<MB, PX, R, XS, MODE, false, false>), grid, dim3(256), T::LDS, st, a); break;
+    }
   }
   return launched("conv kernel");
 }
 
-// Stride-1 convolution of M output channels on register rows; flip: the input gradient's weights.
-msl_status launch_conv_rows(RowsArgs a, int Co, int C, bool flip, const uint16_t* w16, uint16_t* wscratch, bool xbf16,
+// Convolution of M output rows on register rows; pack: the weights' mode (k_pack_rows).
+msl_status launch_conv_rows(RowsArgs a, int Co, int C, int stride, int pack, const uint16_t* w16, uint16_t* wscratch, bool xbf16,
                             hipStream_t st) {
   a.Mp = pad16(a.M);
   a.wp = wscratch;
   a.vec = (a.W % 8 == 0 && aligned(a.x, 16)) ? 1 : 0;
-  a.quads = (a.W % 4 == 0 && aligned(a.y, 8)) ? 1 : 0;
-  const int64_t npack = (int64_t)a.Mp * 9 * pad16(a.C);
-  hipLaunchKernelGGL(k_pack_rows, dim3(blocks_for(npack)), dim3(256), 0, st, Co, C, flip ? 1 : 0, a.Mp, w16, wscratch);
+  a.quads = (a.Wo % 4 == 0 && aligned(a.y, 8)) ? 1 : 0;
+  const int64_t npack = (int64_t)a.Mp * (pack == 2 ? 4 : 9) * pad16(a.C);
+  hipLaunchKernelGGL(k_pack_rows, dim3(blocks_for(npack)), dim3(256), 0, st, Co, C, pack, a.Mp, w16, wscratch);
   // One or two 32-channel blocks per workgroup (four measured slower where the planes of float32
   // gradients are large: 192 channels of 32x128x128, 305 us against 186).  Per workgroup of large work:
   // 64 x 4 pixels of 64 channels (64x64 channels at 32x128x128 55 us against 60 as 32 x 8) and, in rows too
@@ -1732,14 +1570,23 @@ msl_status launch_conv_rows(RowsArgs a, int Co, int C, bool flip, const uint16_t
   // 210).  Small work goes in small pieces, two rows a wavefront: below two workgroups per compute unit
   // the large ones leave the chip idle (256 channels at 2x32x32 24 us against 31).
   const int64_t blocks = (a.M + 63) / 64;
-  auto groups = [&](int tw, int th) { return (int64_t)((a.W + tw - 1) / tw) * ((a.H + th - 1) / th) * a.B * blocks; };
-  if (a.M <= 32) {
-    if (a.C >= 64 && a.W >= 96 && groups(128, 4) >= 512) return launch_rows_t<1, 1, 4, true>(a, xbf16, st);
-    return launch_rows_t<1, 1, 2, false>(a, xbf16, st);
+  auto groups = [&](int tw, int th) { return (int64_t)((a.Wo + tw - 1) / tw) * ((a.Ho + th - 1) / th) * a.B * blocks; };
+  if (pack == 2) {
+    if (a.W >= 48 && groups(64, 4) >= 512) return launch_rows_t<2, 2, 2, false, ROWS_SUB>(a, xbf16, st);
+    return launch_rows_t<2, 1, 2, false, ROWS_SUB>(a, xbf16, st);
   }
-  if (a.W >= 48 && groups(64, 4) >= 512) return launch_rows_t<2, 2, 2, false>(a, xbf16, st);
-  if (a.W < 48 && groups(32, 8) >= 512) return launch_rows_t<2, 1, 4, false>(a, xbf16, st);
-  return launch_rows_t<2, 1, 2, false>(a, xbf16, st);
+  if (stride == 2) {
+    if (a.M <= 32) return launch_rows_t<1, 1, 2, false, ROWS_S2>(a, xbf16, st);
+    if (a.Wo >= 48 && groups(64, 4) >= 512) return launch_rows_t<2, 2, 2, false, ROWS_S2>(a, xbf16, st);
+    return launch_rows_t<2, 1, 2, false, ROWS_S2>(a, xbf16, st);
+  }
+  if (a.M <= 32) {
+    if (a.C >= 64 && a.W >= 96 && groups(128, 4) >= 512) return launch_rows_t<1, 1, 4, true, ROWS_S1>(a, xbf16, st);
+    return launch_rows_t<1, 1, 2, false, ROWS_S1>(a, xbf16, st);
+  }
+  if (a.W >= 48 && groups(64, 4) >= 512) return launch_rows_t<2, 2, 2, false, ROWS_S1>(a, xbf16, st);
+  if (a.W < 48 && groups(32, 8) >= 512) return launch_rows_t<2, 1, 4, false, ROWS_S1>(a, xbf16, st);
+  return launch_rows_t<2, 1, 2, false, ROWS_S1>(a, xbf16, st);
 }
 
 // Halo-tile shape of a convolution with M output rows and Ho x Wo outputs per image: rows per
@@ -1845,13 +1692,13 @@ msl_status msl_nn_conv3x3(int32_t Co, int32_t C, int32_t B, int32_t H, int32_t W
   MSL_TRY(check_ptr(wscratch, 16, "wscratch"));
   MSL_TRY(need((int64_t)C * 9 < (1 << 30) && (int64_t)B * H * W < (1ll << 40), "conv: sizes too large"));
   // k_conv_rows addresses 16 channels with 32 bits; its 32-pixel blocks waste half in rows of 16 and less
-  if (stride == 1 && W > 16 && (int64_t)B * H * W < (1ll << 26)) {
+  if (W / stride > 16 && (int64_t)B * H * W < (1ll << 26)) {
     RowsArgs r{};
-    r.M = Co; r.C = C; r.B = B; r.H = H; r.W = W;
+    r.M = Co; r.C = C; r.B = B; r.H = H; r.W = W; r.Ho = H / stride; r.Wo = W / stride;
     r.relu = relu ? 1 : 0;
     r.ybf16 = y_bf16 ? 1 : 0;
     r.x = x; r.bias = bias; r.y = y;
-    return launch_conv_rows(r, Co, C, false, w16, wscratch, x_bf16 != 0, static_cast<hipStream_t>(hip_stream));
+    return launch_conv_rows(r, Co, C, stride, 0, w16, wscratch, x_bf16 != 0, static_cast<hipStream_t>(hip_stream));
   }
   HaloArgs a{};
   a.M = Co; a.C = C; a.B = B; a.H = H; a.W = W; a.s = stride; a.Ho = H / stride; a.Wo = W / stride;
@@ -1874,12 +1721,13 @@ msl_status msl_nn_conv3x3_adjoint(int32_t Co, int32_t C, int32_t B, int32_t H, i
     // sub-pixel form, a 2x2 convolution over dy with 4 C rows (see k_conv_halo)
     MSL_TRY(check_ptr(wscratch, 16, "wscratch"));
     MSL_TRY(need((int64_t)C * 9 < (1 << 30) && (int64_t)B * H * W < (1ll << 40), "conv adjoint: sizes too large"));
-    if (stride == 1 && W > 16 && (int64_t)B * H * W < (1ll << 26)) {
+    if (W / stride > 16 && (int64_t)B * H * W < (1ll << 26)) {
       RowsArgs r{};
-      r.M = C; r.C = Co; r.B = B; r.H = H; r.W = W;
+      r.M = stride == 1 ? C : 4 * C; r.C = Co; r.B = B;
+      r.H = r.Ho = H / stride; r.W = r.Wo = W / stride;   // both grids are dy's
       r.accum = accumulate ? 1 : 0;
       r.x = dy16; r.y = dx;
-      return launch_conv_rows(r, Co, C, true, w16, wscratch, true, static_cast<hipStream_t>(hip_stream));
+      return launch_conv_rows(r, Co, C, 1, stride == 1 ? 1 : 2, w16, wscratch, true, static_cast<hipStream_t>(hip_stream));
     }
     HaloArgs h{};
     h.M = stride == 1 ? C : 4 * C;
@@ -1915,94 +1763,40 @@ msl_status msl_nn_conv3x3_weight_grad(int32_t Co, int32_t C, int32_t B, int32_t 
   MSL_TRY(check_ptr(dw, 4, "dw"));
   MSL_TRY(check_ptr(partials, 4, "partials"));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (stride == 1 && (int64_t)B * H * W < (1ll << 29)) {   // (a plane's byte offsets fit 32 bits)
-    WrowsArgs w{};
-    w.Co = Co; w.C = C; w.B = B; w.H = H; w.W = W;
-    w.strips = (W + kWgStrip - 1) / kWgStrip;
-    w.cblocks = (C + 31) / 32;
-    w.oblocks = (Co + 31) / 32;
-    const int64_t nco = (int64_t)w.cblocks * w.oblocks;
-    const int want = (int)std::max<int64_t>(1, (kWgradGroups + nco - 1) / nco);   // parts that fill the GPU
-    w.rh = 32;
-    while (w.rh > 4 && (int64_t)B * w.strips * ((H + w.rh - 1) / w.rh) < 4 * want) w.rh /= 2;
-    w.chunks = (H + w.rh - 1) / w.rh;
-    const int64_t units = (int64_t)B * w.strips * w.chunks;
-    MSL_TRY(need(units < (1ll << 30) && (int64_t)C * Co < (1 << 27), "conv weight gradient: sizes too large"));
-    w.units = (int)units;
-    int parts = (int)std::min<int64_t>({(int64_t)splits, (int64_t)want, (units + 3) / 4});
-    w.per_part = (int)((units + 4 * (int64_t)parts - 1) / (4 * (int64_t)parts)) * 4;
-    parts = (int)((units + w.per_part - 1) / w.per_part);
-    MSL_TRY(need(nco * parts < (1ll << 31), "conv weight gradient: sizes too large"));
-    w.dy16 = dy16; w.x = x; w.partials = partials;
-    const bool vec = W % 8 == 0 && aligned(x, 16) && aligned(dy16, 16);
-    const dim3 grid((unsigned)(nco * parts));
-    const int lds = 2 * 9216 * (int)sizeof(float);
-    switch ((x_bf16 ? 2 : 0) + (vec ? 1 : 0)) {
-      case 3: hipLaunchKernelGGL((k_conv_wgrad_rows<true, true>), grid, dim3(256), lds, st, w); break;
-      case 2: hipLaunchKernelGGL((k_conv_wgrad_rows<true, false>), grid, dim3(256), lds, st, w); break;
-      case 1: hipLaunchKernelGGL((k_conv_wgrad_rows<false, true>), grid, dim3(256), lds, st, w); break;
-      default: hipLaunchKernelGGL((k_conv_wgrad_rows<false, false>), grid, dim3(256), lds, st, w); break;
-    }
-    const int64_t mn = (int64_t)Co * C * 9;
-    hipLaunchKernelGGL(k_sum_wgrad, dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, Co * C, parts, partials, dw);
-    return launched("conv weight gradient kernels");
-  }
-  if ((W / stride) % 8 == 0) {
-    // halo tiles (k_conv_wgrad_halo): 128 / s pixels per tile, as TH x TW, TW <= 64
-    WgradArgs w{};
-    w.Co = Co; w.C = C; w.B = B; w.H = H; w.W = W; w.s = stride; w.Ho = H / stride; w.Wo = W / stride;
-    int TW = 8;
-    while (2 * TW <= std::min(w.Wo, 64)) TW *= 2;
-    w.TW = TW;
-    w.KT = 128 / stride;   // smaller tiles: less LDS per workgroup, more of them per CU
-    w.TH = w.KT / TW;
-    w.tiles_x = (w.Wo + TW - 1) / TW;
-    w.tiles_y = (w.Ho + w.TH - 1) / w.TH;
-    const int64_t ntiles = (int64_t)w.tiles_x * w.tiles_y * B;
-    MSL_TRY(need(ntiles < (1ll << 31) && (int64_t)C * 9 < (1 << 30), "conv weight gradient: sizes too large"));
-    w.ntiles = (int)ntiles;
-    // two output-channel tiles per workgroup when there are 64 or more output channels: each staged
-    // input block then feeds twice the products
-    const int ot = Co >= 2 * WOC ? 2 : 1;
-    const int cb = (C + WCK - 1) / WCK, ob = (Co + ot * WOC - 1) / (ot * WOC);
-    // parts: at most `splits`, enough workgroups to fill the GPU (about 2048), at least one tile each
-    int parts = std::min<int64_t>(splits, ntiles);
-    parts = std::max(1, std::min(parts, (2048 + cb * ob - 1) / (cb * ob)));
-    w.per_part = (int)((ntiles + parts - 1) / parts);
-    parts = (int)((ntiles + w.per_part - 1) / w.per_part);
-    w.vec = (W % 4 == 0 && aligned(x, x_bf16 ? 8 : 16)) ? 1 : 0;
-    w.dy16 = dy16; w.x = x; w.partials = partials;
-    const int lds = wgrad_lds_bytes(w.TW, w.TH, stride, ot);
-    MSL_TRY(need(lds <= 64 * 1024 && cb <= 65535 && ob <= 65535, "conv weight gradient: sizes too large"));
-    const dim3 grid(cb, ob, parts);
-    if (ot == 2 && x_bf16) hipLaunchKernelGGL((k_conv_wgrad_halo<2, true>), grid, dim3(192), lds, st, w);
-    else if (ot == 2) hipLaunchKernelGGL((k_conv_wgrad_halo<2, false>), grid, dim3(192), lds, st, w);
-    else if (x_bf16) hipLaunchKernelGGL((k_conv_wgrad_halo<1, true>), grid, dim3(192), lds, st, w);
-    else hipLaunchKernelGGL((k_conv_wgrad_halo<1, false>), grid, dim3(192), lds, st, w);
-    const int64_t mn = (int64_t)Co * 9 * C;
-    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, mn, parts, partials, Co,
-                       9 * C, 9 * C, dw);
-    return launched("conv weight gradient kernels");
-  }
-  ConvArgs a{};
-  a.Co = Co; a.C = C; a.B = B; a.H = H; a.W = W; a.s = stride; a.Ho = H / stride; a.Wo = W / stride;
-  a.dy16 = dy16;
-  if (x_bf16) a.x16 = static_cast<const uint16_t*>(x);
-  else a.x = static_cast<const float*>(x);
-  const int64_t npix = (int64_t)B * a.Ho * a.Wo;
-  MSL_TRY(need(npix < (1ll << 40) && (int64_t)C * 9 < (1 << 30), "conv weight gradient: sizes too large"));
-  // pixel range per part: a multiple of the K tile (the split of msl_nn_gemm_bf16_splitk)
-  int64_t kchunk = (npix + splits - 1) / splits;
-  kchunk = (kchunk + TK - 1) / TK * TK;
-  MSL_TRY(need(kchunk < (1ll << 31), "conv weight gradient: too few parts"));
-  const int parts = (int)((npix + kchunk - 1) / kchunk);
-  const int NC = C * 9;
-  const dim3 grid((unsigned)((NC + TN - 1) / TN), (unsigned)((Co + TM - 1) / TM), (unsigned)parts);
-  MSL_TRY(need(grid.y <= 65535 && grid.z <= 65535, "conv weight gradient: too many channels or parts"));
-  hipLaunchKernelGGL(k_conv_bwd_weight, grid, dim3(256), 0, st, a, (int)kchunk, partials);
-  const int64_t mn = (int64_t)Co * NC;
-  hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, mn, parts, partials, Co, NC,
-                     NC, dw);
+  WrowsArgs w{};
+  w.Co = Co; w.C = C; w.B = B; w.H = H; w.W = W; w.Ho = H / stride; w.Wo = W / stride;
+  w.strips = (w.Wo + kWgStrip - 1) / kWgStrip;
+  w.cblocks = (C + 31) / 32;
+  w.oblocks = (Co + 31) / 32;
+  const int64_t nco = (int64_t)w.cblocks * w.oblocks;
+  const int want = (int)std::max<int64_t>(1, (kWgradGroups + nco - 1) / nco);   // parts that fill the GPU
+  w.rh = 32;
+  while (w.rh > 4 && (int64_t)B * w.strips * ((w.Ho + w.rh - 1) / w.rh) < 4 * want) w.rh /= 2;
+  while (w.rh > 1 && (int64_t)(stride * (w.rh + 1) + 1) * W >= (1ll << 30)) w.rh /= 2;   // 32-bit offsets in a unit
+  w.chunks = (w.Ho + w.rh - 1) / w.rh;
+  const int64_t units = (int64_t)B * w.strips * w.chunks;
+  MSL_TRY(need(units < (1ll << 30) && (int64_t)(2 * stride + 1) * W < (1ll << 30) && (int64_t)C * Co < (1 << 27), "conv weight gradient: sizes too large"));
+  w.units = (int)units;
+  int parts = (int)std::min<int64_t>({(int64_t)splits, (int64_t)want, (units + 3) / 4});
+  w.per_part = (int)((units + 4 * (int64_t)parts - 1) / (4 * (int64_t)parts)) * 4;
+  parts = (int)((units + w.per_part - 1) / w.per_part);
+  MSL_TRY(need(nco * parts < (1ll << 31), "conv weight gradient: sizes too large"));
+  w.dy16 = dy16; w.x = x; w.partials = partials;
+  const bool vec = w.Wo % 8 == 0 && aligned(x, 16) && aligned(dy16, 16);
+  const dim3 grid((unsigned)(nco * parts));
+  const int lds = 2 * 9216 * (int)sizeof(float);
+  auto launch = [&](auto rd) {
+    constexpr int RD = decltype(rd)::value;
+    if (stride == 1 && x_bf16) hipLaunchKernelGGL((k_conv_wgrad_rows<1, true, RD>), grid, dim3(256), lds, st, w);
+    else if (stride == 1) hipLaunchKernelGGL((k_conv_wgrad_rows<1, false, RD>), grid, dim3(256), lds, st, w);
+    else if (x_bf16) hipLaunchKernelGGL((k_conv_wgrad_rows<2, true, RD>), grid, dim3(256), lds, st, w);
+    else hipLaunchKernelGGL((k_conv_wgrad_rows<2, false, RD>), grid, dim3(256), lds, st, w);
+  };
+  if (vec) launch(std::integral_constant<int, ROW_VEC>{});
+  else if (w.Wo >= 8) launch(std::integral_constant<int, ROW_ANY>{});
+  else launch(std::integral_constant<int, ROW_SHORT>{});
+  const int64_t mn = (int64_t)Co * C * 9;
+  hipLaunchKernelGGL(k_sum_wgrad, dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, Co * C, parts, partials, dw);
   return launched("conv weight gradient kernels");
 }
 
