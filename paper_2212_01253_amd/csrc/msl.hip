@@ -122,13 +122,6 @@ __device__ inline void cycle_store(double x, float* out, int64_t stride) {
   }
 }
 
-// Element i of an n-element line table [DITHER][n] float2.
-__device__ inline void cycle_store2(double re, double im, float2* tab, int n, int i) {
-  float* const b = reinterpret_cast<float*>(tab) + 2 * (int64_t)i;
-  cycle_store(re, b, 2 * (int64_t)n);
-  cycle_store(im, b + 1, 2 * (int64_t)n);
-}
-
 __device__ inline void split_store(double re, double im, float2* hi, float2* lo, int64_t i) {
   const float hr = (float)re, hm = (float)im;
   hi[i] = make_float2(hr, hm);
@@ -142,25 +135,55 @@ __device__ inline double kfreq(int m, int n, double d) {
   return 2.0 * M_PI * (double)f / ((double)n * d);
 }
 
-// Twiddles W_n^e = exp(-2 pi i e / n), e < n, as a [DITHER][n] cycle table.
-__global__ void k_twiddles(int n, float2* tab) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  double s, c;
-  sincospi(-2.0 * (double)e / (double)n, &s, &c);
-  cycle_store2(c, s, tab, n, e);
-}
+// What a call writes before its passes: line tables and the tilted probe, every one of them a job of one
+// launch (a launch each, of a few hundred threads, cost a 64x64x128 forward 31 us of 304, and a batch of
+// 48 instances 1.2 ms of 22.6).
+enum JobKind : int {
+  JOB_TWIDDLES = 0,  // W_n^e = exp(-2 pi i e / n), e < n, as a [DITHER][n] cycle table
+  JOB_HPAR = 1,      // paraxial one-axis propagator factor exp(+i dx kq^2 / 2k) / n (pitch d) as a cycle table
+  JOB_PROBE = 2      // tilted plane wave exp(+i q j) on row j of an n x nz grid
+};
+struct Job {
+  float2* out;
+  double d, dx, k;   // JOB_HPAR; JOB_PROBE: q in d
+  int kind, n, nz;
+};
+constexpr int kMaxJobs = 64;
+struct JobList {
+  Job j[kMaxJobs];
+  unsigned* bar;     // status and error words to clear, or nullptr
+  int n;
+};
+static_assert(sizeof(JobList) <= 4096, "kernel arguments are limited to 4 KB");
 
-// Paraxial one-axis propagator factor exp(+i dx kq^2 / 2k) / n, as a
-// [DITHER][n] cycle table.
-__global__ void k_hpar(int n, double d, double dx, double k, float2* tab) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= n) return;
-  const double q = kfreq(m, n, d);
-  const double ph = dx * q * q / (2.0 * k);
+// One job per blockIdx.y.  A table entry's two components go to neighbouring threads: the modulator's 64
+// dependent steps are what a table's time is.
+__global__ void __launch_bounds__(256) k_jobs(JobList l) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && l.bar && threadIdx.x < 3) l.bar[1 + threadIdx.x] = 0u;
+  const Job& q = l.j[blockIdx.y];
+  if (q.kind == JOB_PROBE) {
+    const int64_t m = (int64_t)q.n * q.nz;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m; i += (int64_t)gridDim.x * 256) {
+      const int j = (int)(i / q.nz);
+      double s, c;
+      sincos(fmod(q.d * (double)j, 2.0 * M_PI), &s, &c);
+      q.out[i] = make_float2((float)c, (float)s);
+    }
+    return;
+  }
+  const int i = blockIdx.x * 256 + threadIdx.x, e = i >> 1;
+  if (e >= q.n) return;
   double s, c;
-  sincos(ph, &s, &c);
-  cycle_store2(c / n, s / n, tab, n, m);
+  if (q.kind == JOB_TWIDDLES) {
+    sincospi(-2.0 * (double)e / (double)q.n, &s, &c);
+  } else {
+    const double kq = kfreq(e, q.n, q.d);
+    const double ph = q.dx * kq * kq / (2.0 * q.k);
+    sincos(ph, &s, &c);
+    c /= q.n;
+    s /= q.n;
+  }
+  cycle_store((i & 1) ? s : c, reinterpret_cast<float*>(q.out) + i, 2 * (int64_t)q.n);
 }
 
 // Exact angular-spectrum propagator H[my][mz] / ny.
@@ -182,16 +205,6 @@ __global__ void k_hexact(int ny, int nz, double dy, double dz, double dx, double
     im = amp * s;
   }
   split_store(re / ny, im / ny, hi, lo, i);
-}
-
-// Tilted plane wave exp(+i k sin(alpha) j dy).
-__global__ void k_probe(int ny, int nz, double q, float2* out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)ny * nz) return;
-  const int j = (int)(i / nz);
-  double s, c;
-  sincos(fmod(q * (double)j, 2.0 * M_PI), &s, &c);
-  out[i] = make_float2((float)c, (float)s);
 }
 
 // Tile (a, b) (rows 2a, 2a+1, columns 2b, 2b+1) handled at work index t of a
@@ -531,24 +544,53 @@ Call make_call(const msl_geometry& g, const Layout& lay, void* ws, hipStream_t s
 
 Call make_call(const msl_geometry& g, int k, void* ws, hipStream_t st) { return make_call(g, layout(g, k), ws, st); }
 
-msl_status build_tables(const Call& k, bool need_prop) {
+// The jobs of a list, in launches of up to kMaxJobs.
+struct Jobs {
+  std::vector<Job> q;
+  int64_t most = 0;   // threads of the largest job
+  void add(const Job& j) {
+    q.push_back(j);
+    const int64_t t = j.kind == JOB_PROBE ? (int64_t)j.n * j.nz : 2 * (int64_t)j.n;
+    if (t > most) most = t;
+  }
+  void tables(const msl_geometry& g, float2* twz, float2* twy, float2* hz, float2* hy) {
+    const double kk = 2.0 * M_PI / g.wavelength_nm;
+    add({twz, 0.0, 0.0, 0.0, JOB_TWIDDLES, g.nz, 0});
+    add({twy, 0.0, 0.0, 0.0, JOB_TWIDDLES, g.ny, 0});
+    if (hz) add({hz, g.dz_nm, g.dx_nm, kk, JOB_HPAR, g.nz, 0});
+    if (hy) add({hy, g.dy_nm, g.dx_nm, kk, JOB_HPAR, g.ny, 0});
+  }
+  void probe(const msl_geometry& g, float2* out) {
+    const double q_ = 2.0 * M_PI / g.wavelength_nm * std::sin(g.alpha_i_rad) * g.dy_nm;
+    add({out, q_, 0.0, 0.0, JOB_PROBE, g.ny, g.nz});
+  }
+  msl_status run(unsigned* bar, hipStream_t st) const {
+    const unsigned gx = (unsigned)std::min<int64_t>((most + 255) / 256, 256);   // (tables need at most 8)
+    for (size_t i = 0; i < q.size(); i += kMaxJobs) {
+      JobList l{};
+      l.n = (int)std::min<size_t>(kMaxJobs, q.size() - i);
+      for (int j = 0; j < l.n; ++j) l.j[j] = q[i + j];
+      l.bar = i == 0 ? bar : nullptr;
+      hipLaunchKernelGGL(k_jobs, dim3(gx, l.n), dim3(256), 0, st, l);
+    }
+    return hip_check(hipGetLastError(), "table kernels");
+  }
+};
+
+// Start of a call that runs passes: its tables, the probe (into probe_out, if given) and its workspace
+// status word (status: a workspace has one), msl_workspace_status, restarted at 0.
+msl_status start_call(const Call& k, bool need_prop, float2* probe_out, bool status) {
   const msl_geometry& g = k.g;
   auto P = [&](size_t off) { return reinterpret_cast<float2*>(k.ws + off); };
-  const int tb = 256;
-  hipLaunchKernelGGL(k_twiddles, dim3((g.nz + tb - 1) / tb), dim3(tb), 0, k.st, g.nz, P(k.L.twz));
-  hipLaunchKernelGGL(k_twiddles, dim3((g.ny + tb - 1) / tb), dim3(tb), 0, k.st, g.ny, P(k.L.twy));
-  if (need_prop) {
-    const double kk = 2.0 * M_PI / g.wavelength_nm;
-    if (g.propagator == MSL_PROP_PARAXIAL) {
-      hipLaunchKernelGGL(k_hpar, dim3((g.nz + tb - 1) / tb), dim3(tb), 0, k.st, g.nz, g.dz_nm, g.dx_nm, kk,
-                         P(k.L.hz));
-      hipLaunchKernelGGL(k_hpar, dim3((g.ny + tb - 1) / tb), dim3(tb), 0, k.st, g.ny, g.dy_nm, g.dx_nm, kk,
-                         P(k.L.hy));
-    } else {
-      const int64_t m = (int64_t)g.ny * g.nz;
-      hipLaunchKernelGGL(k_hexact, dim3((unsigned)((m + tb - 1) / tb)), dim3(tb), 0, k.st, g.ny, g.nz, g.dy_nm,
-                         g.dz_nm, g.dx_nm, kk, P(k.L.H_hi), P(k.L.H_lo));
-    }
+  const bool par = need_prop && g.propagator == MSL_PROP_PARAXIAL;
+  Jobs jobs;
+  jobs.tables(g, P(k.L.twz), P(k.L.twy), par ? P(k.L.hz) : nullptr, par ? P(k.L.hy) : nullptr);
+  if (probe_out) jobs.probe(g, probe_out);
+  MSL_TRY(jobs.run(status ? reinterpret_cast<unsigned*>(k.ws + k.L.bar) : nullptr, k.st));
+  if (need_prop && !par) {
+    const int64_t m = (int64_t)g.ny * g.nz;
+    hipLaunchKernelGGL(k_hexact, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, k.st, g.ny, g.nz, g.dy_nm, g.dz_nm,
+                       g.dx_nm, 2.0 * M_PI / g.wavelength_nm, P(k.L.H_hi), P(k.L.H_lo));
   }
   return hip_check(hipGetLastError(), "table kernels");
 }
@@ -699,12 +741,6 @@ msl_status run_phases(const Call& k, const PhaseSpec& a, const PhaseSpec* b) {
 
 msl_status run_phase(const Call& k, const PhaseSpec& ph) { return run_phases(k, ph, nullptr); }
 
-// Start of a call that runs phases: its workspace status word (msl_workspace_status) restarts at 0.
-msl_status clear_status(const Call& k) {
-  hipLaunchKernelGGL(msl::k_clear_status, dim3(1), dim3(64), 0, k.st, reinterpret_cast<unsigned*>(k.ws + k.L.bar));
-  return hip_check(hipGetLastError(), "status kernel");
-}
-
 msl_status copy_field(const Call& k, void* dst, const void* src) {
   return hip_check(hipMemcpyAsync(dst, src, (size_t)k.c.m * 8, hipMemcpyDeviceToDevice, k.st), "hipMemcpyAsync");
 }
@@ -758,9 +794,12 @@ struct BatchRec {
   // the kernel forms those pointers from the workspace base it receives as an argument, so the
   // compiler addresses them as global memory (pointers read from the records are generic)
   uint64_t off_twz, off_twy, off_hz, off_hy, off_pack, off_field;
+  const float2* in_rm;   // probe
+  float2* out_rm;        // exit wave
+  int ns;
 };
 
-constexpr int kRecChunk = 16;  // records per descriptor-store launch (kernel arguments < 4 KB)
+constexpr int kRecChunk = 12;  // records per descriptor-store launch (kernel arguments < 4 KB)
 
 struct RecChunk {
   BatchRec r[kRecChunk];
@@ -800,39 +839,81 @@ __global__ void __launch_bounds__(256) k_pass_batch(const BatchRec* __restrict__
                                                                    msl::line_buffers<N, P>(lds, g, G));
 }
 
+// Passes of a batch that are no middle pass, over instances recs[0 .. gridDim.x / groups_per_inst): the
+// first of the slice loop, the last (of instances of one slice count) and the far field's two.
+enum BatchEdge : int { EDGE_FIRST = 0, EDGE_LAST = 1, EDGE_FF0 = 2, EDGE_FF1 = 3 };
+
 template <int N, int P, int AXIS>
-hipError_t launch_pass_batch_tp(const BatchRec* recs, char* wsb, int n_inst, int nlines, const PassDesc& tmpl,
+__global__ void __launch_bounds__(256) k_pass_batch_edge(const BatchRec* __restrict__ recs, char* __restrict__ wsb,
+                                                         int groups_per_inst, int edge) {
+  extern __shared__ float2 lds[];  // line_pass_lds_bytes(N, G)
+  constexpr int L = N / P;
+  const int G = blockDim.x / L;
+  const int g = threadIdx.x % G, j = threadIdx.x / G;
+  const int gb = msl::xcd_group(blockIdx.x, gridDim.x);
+  const BatchRec& r = recs[gb / groups_per_inst];
+  Ctx c = r.c;
+  if (edge >= EDGE_FF0 && !c.intensity) return;
+  c.twz = reinterpret_cast<const float2*>(wsb + r.off_twz);
+  c.twy = reinterpret_cast<const float2*>(wsb + r.off_twy);
+  c.hz = reinterpret_cast<const float2*>(wsb + r.off_hz);
+  c.hy = reinterpret_cast<const float2*>(wsb + r.off_hy);
+  c.dbT = reinterpret_cast<const float2*>(wsb + r.off_pack);
+  PhaseSpec ph{};
+  ph.kind = edge >= EDGE_FF0 ? msl::PH_FF : msl::PH_FWD_FULL;
+  ph.ns = ph.s1 = r.ns;
+  ph.m = c.m;
+  ph.field = reinterpret_cast<float2*>(wsb + r.off_field);
+  ph.in_rm = edge >= EDGE_FF0 ? r.out_rm : r.in_rm;
+  ph.out_rm = edge >= EDGE_FF0 ? nullptr : r.out_rm;
+  const PassDesc pd = msl::phase_pass(ph, edge == EDGE_LAST ? r.ns : (edge == EDGE_FF1 ? 1 : 0));
+  msl::run_line<N, AXIS, false, msl::KIND_GENERIC, msl::TS_RUNTIME, P>(c, pd, (gb % groups_per_inst) * G + g, j,
+                                                                     msl::line_buffers<N, P>(lds, g, G));
+}
+
+// Middle pass tmpl, or (edge >= 0) pass `edge`, of n_inst instances.
+template <int N, int P, int AXIS>
+hipError_t launch_pass_batch_tp(const BatchRec* recs, char* wsb, int n_inst, int nlines, const PassDesc& tmpl, int edge,
                                 hipStream_t st) {
   constexpr int L = N / P;
   const int G = lines_per_group(N, nlines, (int64_t)nlines * n_inst);
   const int gpi = nlines / G;
-  hipLaunchKernelGGL((k_pass_batch<N, P, AXIS>), dim3(n_inst * gpi), dim3(L * G), (unsigned)line_pass_lds_bytes(N, G),
-                     st, recs, wsb, gpi, tmpl);
+  const dim3 grid(n_inst * gpi), block(L * G);
+  const unsigned lds = (unsigned)line_pass_lds_bytes(N, G);
+  if (edge >= 0) hipLaunchKernelGGL((k_pass_batch_edge<N, P, AXIS>), grid, block, lds, st, recs, wsb, gpi, edge);
+  else hipLaunchKernelGGL((k_pass_batch<N, P, AXIS>), grid, block, lds, st, recs, wsb, gpi, tmpl);
   return hipGetLastError();
 }
 
 template <int N, int AXIS>
-hipError_t launch_pass_batch_t(const BatchRec* recs, char* wsb, int n_inst, int nlines, const PassDesc& tmpl,
+hipError_t launch_pass_batch_t(const BatchRec* recs, char* wsb, int n_inst, int nlines, const PassDesc& tmpl, int edge,
                                hipStream_t st) {
   if constexpr (N >= 64) {
-    if (points_per_lane(N) == 8) return launch_pass_batch_tp<N, 8, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
+    if (points_per_lane(N) == 8) return launch_pass_batch_tp<N, 8, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
   }
-  return launch_pass_batch_tp<N, 4, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
+  return launch_pass_batch_tp<N, 4, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
 }
 
 template <int AXIS>
 hipError_t launch_pass_batch_axis(int n, const BatchRec* recs, char* wsb, int n_inst, int nlines, const PassDesc& tmpl,
-                                  hipStream_t st) {
+                                  int edge, hipStream_t st) {
   switch (n) {
-    case 16: return launch_pass_batch_t<16, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
-    case 32: return launch_pass_batch_t<32, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
-    case 64: return launch_pass_batch_t<64, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
-    case 128: return launch_pass_batch_t<128, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
-    case 256: return launch_pass_batch_t<256, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
-    case 512: return launch_pass_batch_t<512, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
-    case 1024: return launch_pass_batch_t<1024, AXIS>(recs, wsb, n_inst, nlines, tmpl, st);
+    case 16: return launch_pass_batch_t<16, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
+    case 32: return launch_pass_batch_t<32, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
+    case 64: return launch_pass_batch_t<64, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
+    case 128: return launch_pass_batch_t<128, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
+    case 256: return launch_pass_batch_t<256, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
+    case 512: return launch_pass_batch_t<512, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
+    case 1024: return launch_pass_batch_t<1024, AXIS>(recs, wsb, n_inst, nlines, tmpl, edge, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+// A pass along `axis` of instances recs[0 .. n_inst) of an ny x nz grid.
+hipError_t launch_pass_batch(const BatchRec* recs, char* wsb, int n_inst, int ny, int nz, int axis, const PassDesc& tmpl,
+                             int edge, hipStream_t st) {
+  return axis == msl::ROW ? launch_pass_batch_axis<msl::ROW>(nz, recs, wsb, n_inst, ny, tmpl, edge, st)
+                          : launch_pass_batch_axis<msl::COL>(ny, recs, wsb, n_inst, nz, tmpl, edge, st);
 }
 
 // Workspace of a batch: the records, then per instance its tables (twiddles,
@@ -1173,16 +1254,9 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
   k.flow_rot = rot;
   k.c.delta = delta;
   k.c.beta = beta;
-  MSL_TRY(clear_status(k));
-  MSL_TRY(build_tables(k, true));
   float2* f = reinterpret_cast<float2*>(field_out);
-  const float2* in = reinterpret_cast<const float2*>(probe);
-  if (!probe) {
-    const double q = 2.0 * M_PI / g->wavelength_nm * std::sin(g->alpha_i_rad) * g->dy_nm;
-    hipLaunchKernelGGL(k_probe, dim3((unsigned)((k.c.m + 255) / 256)), dim3(256), 0, k.st, g->ny, g->nz, q, f);
-    MSL_TRY(hip_check(hipGetLastError(), "probe kernel"));
-    in = f;
-  }
+  const float2* in = probe ? reinterpret_cast<const float2*>(probe) : f;
+  MSL_TRY(start_call(k, true, probe ? nullptr : f, true));
   // the first pass reads the probe (row-major), the passes work on the tiled
   // working field, the last one writes the exit wave row-major
   PhaseSpec ph = blank_phase(k, msl::PH_FWD_FULL);
@@ -1222,15 +1296,9 @@ msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const 
   Call k = make_call(*g, lay, base, static_cast<hipStream_t>(hip_stream));
   k.c.delta = delta;
   k.c.beta = beta;
-  MSL_TRY(build_tables(k, true));
   float2* f = reinterpret_cast<float2*>(field_out);
-  const float2* in = reinterpret_cast<const float2*>(probe);
-  if (!probe) {
-    const double q = 2.0 * M_PI / g->wavelength_nm * std::sin(g->alpha_i_rad) * g->dy_nm;
-    hipLaunchKernelGGL(k_probe, dim3((unsigned)((k.c.m + 255) / 256)), dim3(256), 0, k.st, g->ny, g->nz, q, f);
-    MSL_TRY(hip_check(hipGetLastError(), "probe kernel"));
-    in = nullptr;
-  }
+  const float2* in = reinterpret_cast<const float2*>(probe);   // (the tilted probe is written in place)
+  MSL_TRY(start_call(k, true, probe ? nullptr : f, false));
   // No slice pack and no tiled working field (neither would fit a fixed
   // scratch): the passes work on the exit-wave array itself, row-major, and
   // the column passes evaluate the transmission of their slices from the
@@ -1257,8 +1325,7 @@ msl_status msl_far_field(const msl_geometry* g, const msl_c64* field, float* int
   MSL_TRY(check_ws(*g, 0, workspace, ws_bytes));
   Call k = make_call(*g, 0, workspace, static_cast<hipStream_t>(hip_stream));
   k.c.intensity = intensity;
-  MSL_TRY(clear_status(k));
-  MSL_TRY(build_tables(k, false));
+  MSL_TRY(start_call(k, false, nullptr, true));
   PhaseSpec ph = blank_phase(k, msl::PH_FF);
   ph.in_rm = reinterpret_cast<const float2*>(field);
   ph.field = reinterpret_cast<float2*>(k.ws + k.L.tmp);
@@ -1292,8 +1359,7 @@ msl_status msl_far_field_adjoint(const msl_geometry* g, const msl_c64* field, co
   MSL_TRY(check_ws(*g, 0, workspace, ws_bytes));
   Call k = make_call(*g, 0, workspace, static_cast<hipStream_t>(hip_stream));
   k.c.grad_intensity = grad_intensity;
-  MSL_TRY(clear_status(k));
-  MSL_TRY(build_tables(k, false));
+  MSL_TRY(start_call(k, false, nullptr, true));
   PhaseSpec ph = blank_phase(k, msl::PH_FFADJ);
   ph.in_rm = reinterpret_cast<const float2*>(field);
   ph.field = reinterpret_cast<float2*>(k.ws + k.L.tmp);
@@ -1325,8 +1391,7 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
   k.c.beta = beta;
   k.c.gdelta = grad_delta;
   k.c.gbeta = grad_beta;
-  MSL_TRY(clear_status(k));
-  MSL_TRY(build_tables(k, true));
+  MSL_TRY(start_call(k, true, nullptr, true));
   if (flags & MSL_REUSE_SLICE_PACK) {
     if (g->propagator == MSL_PROP_PARAXIAL) k.c.dbT = reinterpret_cast<const float2*>(k.ws + k.L.dbT);
   } else {
@@ -1458,6 +1523,7 @@ msl_status msl_forward_batch(const msl_instance* inst, int32_t n, void* workspac
   // per instance: tables, probe, pool pack, record
   std::vector<BatchRec> recs(n);
   std::vector<PhaseSpec> phs(n);
+  Jobs jobs;
   for (int r = 0; r < n; ++r) {
     const int i = order[r];
     const msl_instance& x = inst[i];
@@ -1485,21 +1551,10 @@ msl_status msl_forward_batch(const msl_instance* inst, int32_t n, void* workspac
     c.slice_index = x.slice_index;
     c.n_pool = x.n_pool;
     c.intensity = x.intensity_out;
-    const int tb = 256;
-    const double kk = 2.0 * M_PI / g.wavelength_nm;
-    hipLaunchKernelGGL(k_twiddles, dim3((g.nz + tb - 1) / tb), dim3(tb), 0, st, g.nz, P(b.twz));
-    hipLaunchKernelGGL(k_twiddles, dim3((g.ny + tb - 1) / tb), dim3(tb), 0, st, g.ny, P(b.twy));
-    hipLaunchKernelGGL(k_hpar, dim3((g.nz + tb - 1) / tb), dim3(tb), 0, st, g.nz, g.dz_nm, g.dx_nm, kk, P(b.hz));
-    hipLaunchKernelGGL(k_hpar, dim3((g.ny + tb - 1) / tb), dim3(tb), 0, st, g.ny, g.dy_nm, g.dx_nm, kk, P(b.hy));
-    MSL_TRY(hip_check(hipGetLastError(), "table kernels"));
+    jobs.tables(g, P(b.twz), P(b.twy), P(b.hz), P(b.hy));
     float2* f = reinterpret_cast<float2*>(x.field_out);
-    const float2* in = reinterpret_cast<const float2*>(x.probe);
-    if (!x.probe) {
-      const double q = kk * std::sin(g.alpha_i_rad) * g.dy_nm;
-      hipLaunchKernelGGL(k_probe, dim3((unsigned)((c.m + 255) / 256)), dim3(256), 0, st, g.ny, g.nz, q, f);
-      MSL_TRY(hip_check(hipGetLastError(), "probe kernel"));
-      in = f;
-    }
+    const float2* in = x.probe ? reinterpret_cast<const float2*>(x.probe) : f;
+    if (!x.probe) jobs.probe(g, f);
     float2* pack = P(b.pack);
     MSL_TRY(hip_check(launch_pack(x.pool_delta, x.pool_beta, pack, g.ny, g.nz, 0, x.n_pool, 0, 1, 0, c, st),
                       "pack kernel"));
@@ -1512,6 +1567,9 @@ msl_status msl_forward_batch(const msl_instance* inst, int32_t n, void* workspac
     recs[r].off_hy = b.hy;
     recs[r].off_pack = b.pack;
     recs[r].off_field = b.tmp;
+    recs[r].in_rm = in;
+    recs[r].out_rm = f;
+    recs[r].ns = g.n_slices;
     PhaseSpec& ph = phs[r];
     ph = PhaseSpec{};
     ph.kind = msl::PH_FWD_FULL;
@@ -1523,6 +1581,7 @@ msl_status msl_forward_batch(const msl_instance* inst, int32_t n, void* workspac
     ph.in_rm = in;
     ph.out_rm = f;
   }
+  MSL_TRY(jobs.run(nullptr, st));
   for (int r0 = 0; r0 < n; r0 += kRecChunk) {
     RecChunk ch{};
     ch.n = std::min(kRecChunk, n - r0);
@@ -1553,38 +1612,32 @@ msl_status msl_forward_batch(const msl_instance* inst, int32_t n, void* workspac
     const hipStream_t gs = (gi == 0 || nextra == 0) ? st : h->bs[(gi - 1) % nextra];
     const int ny = inst[order[g0]].g.ny, nz = inst[order[g0]].g.nz;
     const int max_ns = inst[order[g0]].g.n_slices;
-    for (int r = g0; r < g1; ++r) MSL_TRY(hip_check(launch_pass(recs[r].c, msl::phase_pass(phs[r], 0), gs), "pass kernel"));
+    auto pass = [&](int r, int count, int axis, const PassDesc& tmpl, int edge) {
+      return hip_check(launch_pass_batch(drecs + r, ws, count, ny, nz, axis, tmpl, edge, gs), "batched pass kernel");
+    };
+    MSL_TRY(pass(g0, g1 - g0, msl::ROW, PassDesc{}, EDGE_FIRST));
     int active = g1 - g0;  // instances with n_slices > p, a prefix of the group
     for (int p = 1; p <= max_ns; ++p) {
+      const int was = active;
       while (active > 0 && inst[order[g0 + active - 1]].g.n_slices <= p) --active;
       if (active > 0) {
         const PassDesc tmpl = msl::phase_pass(phs[g0], p);
-        const hipError_t e = tmpl.axis == msl::ROW
-                                 ? launch_pass_batch_axis<msl::ROW>(nz, drecs + g0, ws, active, ny, tmpl, gs)
-                                 : launch_pass_batch_axis<msl::COL>(ny, drecs + g0, ws, active, nz, tmpl, gs);
-        MSL_TRY(hip_check(e, "batched pass kernel"));
+        MSL_TRY(pass(g0, active, tmpl.axis, tmpl, -1));
       }
       // instances whose slice loop ended at p: their last propagation
-      for (int r = g0 + active; r < g1 && inst[order[r]].g.n_slices >= p; ++r)
-        if (inst[order[r]].g.n_slices == p)
-          MSL_TRY(hip_check(launch_pass(recs[r].c, msl::phase_pass(phs[r], p), gs), "pass kernel"));
+      if (was > active) MSL_TRY(pass(g0 + active, was - active, (p & 1) ? msl::COL : msl::ROW, PassDesc{}, EDGE_LAST));
+    }
+    // far fields (of the exit waves; the working fields are free again)
+    bool ff = false;
+    for (int r = g0; r < g1; ++r) ff = ff || recs[r].c.intensity;
+    if (ff) {
+      MSL_TRY(pass(g0, g1 - g0, msl::ROW, PassDesc{}, EDGE_FF0));
+      MSL_TRY(pass(g0, g1 - g0, msl::COL, PassDesc{}, EDGE_FF1));
     }
   }
   for (int i = 0; i < nextra; ++i) {
     MSL_TRY(hip_check(hipEventRecord(h->bjoin[i], h->bs[i]), "hipEventRecord"));
     MSL_TRY(hip_check(hipStreamWaitEvent(st, h->bjoin[i], 0), "hipStreamWaitEvent"));
-  }
-  // far fields
-  for (int r = 0; r < n; ++r) {
-    if (!recs[r].c.intensity) continue;
-    PhaseSpec ff{};
-    ff.kind = msl::PH_FF;
-    ff.m = recs[r].c.m;
-    ff.ns = phs[r].ns;
-    ff.in_rm = phs[r].out_rm;   // the exit wave (row-major); the working field is free again
-    ff.field = phs[r].field;
-    for (int p = 0; p < msl::phase_npasses(ff); ++p)
-      MSL_TRY(hip_check(launch_pass(recs[r].c, msl::phase_pass(ff, p), st), "far-field kernel"));
   }
   return MSL_OK;
 }

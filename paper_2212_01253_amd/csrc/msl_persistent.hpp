@@ -98,11 +98,6 @@ __global__ void k_reset_barrier(unsigned* bar, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) bar[8 + i] = 0u;
 }
 
-// Clears the status word and the dataflow launches' error words (start of a call that runs phases).
-__global__ void k_clear_status(unsigned* bar) {
-  if (threadIdx.x < 3 && blockIdx.x == 0) bar[1 + threadIdx.x] = 0u;
-}
-
 // After a persistent launch: if a barrier gave up, raise the status word and
 // fill the up to four working fields of m elements with NaN.
 __global__ void k_fold_barrier_error(unsigned* bar, float2* f0, float2* f1, float2* f2, float2* f3, int64_t m) {
