@@ -147,7 +147,10 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
  * returns MSL_ERR_UNSUPPORTED before anything is enqueued.  All calls on one
  * GPU share its array, which keeps the last call's tables: calls that overlap
  * on one GPU (other streams, other host threads) race and must be ordered by
- * the caller.  The schedule setting is ignored (always one launch per pass). */
+ * the caller.  MSL_SCHED_AUTO runs the middle passes of a paraxial call as one
+ * dataflow launch where its exchange fields (4 ny nz complex64) fit the array
+ * beside the tables, any other setting one launch per pass; a wait that ends
+ * at the spin limit leaves NaN in field_out. */
 #define MSL_NOALLOC_SCRATCH_BYTES ((size_t)(4 * 64 * 1024 * 8 + 2 * 512 * 512 * 8))
 msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const float* beta,
                                const msl_c64* probe, msl_c64* field_out,

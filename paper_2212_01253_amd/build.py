@@ -9,7 +9,8 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRCS = [os.path.join(HERE, "csrc", f) for f in ("msl.hip", "msl_flow.hip", "msl_flow_rev.hip", "msl_recon.hip", "msl_nn.hip")]
+SRCS = [os.path.join(HERE, "csrc", f) for f in ("msl.hip", "msl_flow.hip", "msl_flow_fwd.hip", "msl_flow_rev.hip", "msl_flow_stack.hip",
+                                                 "msl_flow_xfwd.hip", "msl_flow_xrev.hip", "msl_recon.hip", "msl_nn.hip")]
 OUT = os.path.join(HERE, "libmsl.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -79,7 +79,7 @@ Layout layout(const msl_geometry& g, int k) {
     L.seg = take((size_t)(k > 1 ? k - 1 : 0) * m * 8 * 2);  // two tiled segment buffers
     L.gT = take(odd * m * 8);  // odd slices' gradients, same layout as dbT
   }
-  if (!exact && g.ny <= 512 && g.nz <= 512)
+  if (g.ny <= 512 && g.nz <= 512)
     for (int q = 0; q < (k >= 1 ? 2 : 1); ++q) L.xf[q] = take(4 * m * 8);
   L.total = o;
   return L;
@@ -663,20 +663,26 @@ bool whole_device(hipStream_t st) {
   return n >= cus;
 }
 
-// Whether the middle passes of the call's phases go to the dataflow schedule: the default schedule at
-// the default launch shape (a set one asks for the per-pass kernels it describes), a paraxial call
-// with a slice pack, a grid it serves, and a stream that may use every compute unit.
-bool use_flow(const Call& k) {
-  if (!k.flow_rot || g_schedule != MSL_SCHED_AUTO || !k.c.dbT || k.g.propagator != MSL_PROP_PARAXIAL) return false;
+// The dataflow kind (msl::FlowKind) that takes the middle passes of phase a, or -1: the default schedule at
+// the default launch shape (a set one asks for the per-pass kernels it describes), exchange fields in the
+// call's scratch, a grid it serves, and a stream that may use every compute unit.
+int flow_kind(const Call& k, const PhaseSpec& a) {
+  if (!k.flow_rot || g_schedule != MSL_SCHED_AUTO) return -1;
+  int kind = -1;
+  if (a.kind == msl::PH_FWD_FULL || a.kind == msl::PH_FWD_RECOMP)
+    kind = a.exact ? msl::FLOW_XFWD : (k.c.dbT ? msl::FLOW_FWD : (a.rowmajor ? msl::FLOW_STACK : -1));
+  else if (a.kind == msl::PH_REV)
+    kind = a.exact ? msl::FLOW_XREV : (k.c.dbT ? msl::FLOW_REV : -1);
+  if (kind < 0 || (a.rowmajor != 0) != (kind == msl::FLOW_STACK)) return -1;
   for (const int n : {k.c.ny, k.c.nz}) {
     const int e = __builtin_ctz((unsigned)n);
-    if (n > 512 || g_lines_per_group[e] > 0 || g_points_per_lane[e] > 0) return false;
+    if (n > 512 || g_lines_per_group[e] > 0 || g_points_per_lane[e] > 0) return -1;
   }
-  return msl::flow_serves(k.c.ny, k.c.nz) && whole_device(k.st);
+  return msl::flow_serves(kind, k.c.ny, k.c.nz) && whole_device(k.st) ? kind : -1;
 }
 
 // Passes p0 .. p0 + n - 1 of phase a, all of its middle kind, as one dataflow launch.
-msl_status run_flow(const Call& k, const PhaseSpec& a, int p0, int n) {
+msl_status run_flow(const Call& k, const PhaseSpec& a, int kind, int p0, int n) {
   const int set = a.kind == msl::PH_FWD_RECOMP ? 1 : 0;   // the recompute runs beside the reverse sweep
   unsigned* bar = reinterpret_cast<unsigned*>(k.ws + k.L.bar);
   msl::FlowArgs f{};
@@ -694,8 +700,7 @@ msl_status run_flow(const Call& k, const PhaseSpec& a, int p0, int n) {
   }
   f.rot = rot;
   rot = (rot + n - 1) & 3;
-  return hip_check(msl::launch_flow(k.c, f, a.kind == msl::PH_REV ? msl::KIND_REV_MID : msl::KIND_FWD_MID, k.st),
-                   "dataflow kernel");
+  return hip_check(msl::launch_flow(kind, k.c, f, k.st), "dataflow kernel");
 }
 
 // Runs phase a, and phase b beside it when given (independent fields of a
@@ -706,26 +711,26 @@ msl_status run_phases(const Call& k, const PhaseSpec& a, const PhaseSpec* b) {
   const int np = npa > npb ? npa : npb;
   if (np == 0) return MSL_OK;
   unsigned* bar = reinterpret_cast<unsigned*>(k.ws + k.L.bar);
-  if (use_persistent(k, np)) {
+  if (!a.rowmajor && use_persistent(k, np)) {
     hipError_t e = msl::launch_persistent(k.c, a, npa, npb > 0 ? b : nullptr, npb, bar, g_spin_limit, k.st);
     if (e == hipSuccess) return MSL_OK;
     if (g_schedule == MSL_SCHED_PERSISTENT) return hip_check(e, "persistent pass kernel");
     (void)hipGetLastError();  // AUTO: the per-pass schedule below does the same work
   }
-  int f0 = 0, f1 = 0;   // passes [f0, f1): one dataflow launch
-  if (use_flow(k)) {
-    const int kind = a.kind == msl::PH_REV ? msl::KIND_REV_MID : msl::KIND_FWD_MID;
-    while (f0 < npa && msl::pass_kind(msl::phase_pass(a, f0)) != kind) ++f0;
+  int f0 = npa, f1 = npa;   // passes [f0, f1): one dataflow launch
+  const int kind = flow_kind(k, a);
+  if (kind >= 0) {
+    auto takes = [&](int p) { return msl::flow_takes(kind, msl::phase_pass(a, p)); };
+    f0 = 0;
+    while (f0 < npa && !takes(f0)) ++f0;
     if (f0 < npa && msl::phase_pass(a, f0).axis != msl::COL) ++f0;  // a dataflow launch begins with a column pass
     f1 = f0;
-    while (f1 < npa && msl::pass_kind(msl::phase_pass(a, f1)) == kind) ++f1;
+    while (f1 < npa && takes(f1)) ++f1;
     if (f1 - f0 < msl::kFlowMinPasses) f0 = f1 = npa;
-  } else {
-    f0 = f1 = npa;
   }
   for (int p = 0; p < npa; ++p) {
     if (p == f0) {
-      MSL_TRY(run_flow(k, a, f0, f1 - f0));
+      MSL_TRY(run_flow(k, a, kind, f0, f1 - f0));
       p = f1 - 1;
       continue;
     }
@@ -1083,6 +1088,11 @@ Layout noalloc_layout(const msl_geometry& g) {
   L.H_hi = take(exact ? m * 8 : 0);
   L.H_lo = take(exact ? m * 8 : 0);
   L.total = o;
+  // the dataflow schedule's error words and exchange fields, where they fit (xf[0] stays 0 where not)
+  if (!exact && o + kAlign + up(4 * m * 8) <= kNoAllocBytes) {
+    L.bar = take(kAlign);
+    L.xf[0] = take(4 * m * 8);
+  }
   return L;
 }
 
@@ -1298,12 +1308,14 @@ msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const 
   k.c.beta = beta;
   float2* f = reinterpret_cast<float2*>(field_out);
   const float2* in = reinterpret_cast<const float2*>(probe);   // (the tilted probe is written in place)
-  MSL_TRY(start_call(k, true, probe ? nullptr : f, false));
+  int rot[2] = {-1, -1};
+  if (lay.xf[0]) k.flow_rot = rot;
+  MSL_TRY(start_call(k, true, probe ? nullptr : f, lay.xf[0] != 0));
   // No slice pack and no tiled working field (neither would fit a fixed
   // scratch): the passes work on the exit-wave array itself, row-major, and
   // the column passes evaluate the transmission of their slices from the
-  // caller's stack, with the same arithmetic as the pack.  Always one launch
-  // per pass.
+  // caller's stack, with the same arithmetic as the pack.  One launch per pass,
+  // or the dataflow schedule where its exchange fields fit the scratch too.
   PhaseSpec ph = blank_phase(k, msl::PH_FWD_FULL);
   ph.s0 = 0;
   ph.s1 = g->n_slices;
@@ -1312,9 +1324,7 @@ msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const 
   ph.rowmajor = 1;
   ph.ckpt = reinterpret_cast<float2*>(ckpt);
   ph.ckpt_every = ckpt ? ckpt_every : 0;
-  const int np = msl::phase_npasses(ph);
-  for (int p = 0; p < np; ++p) MSL_TRY(hip_check(launch_pass(k.c, msl::phase_pass(ph, p), k.st), "pass kernel"));
-  return MSL_OK;
+  return run_phase(k, ph);
 }
 
 msl_status msl_far_field(const msl_geometry* g, const msl_c64* field, float* intensity, void* workspace,

@@ -1,8 +1,8 @@
-// Dataflow schedule: the forward and recompute kernels, and the host side.
+// Dataflow schedule: the host side.
 #include <cstdlib>
 #include <mutex>
 
-#include "msl_flow_launch.hpp"
+#include "msl_flow_host.hpp"
 
 namespace msl {
 namespace {
@@ -27,24 +27,32 @@ int flow_nap(int64_t m) { return m <= 8192 ? 0 : (m <= 32768 ? 1 : (m <= 131072 
 // themselves and only delay that; launches of this schedule on other streams wait like this one, so
 // as many as there are hardware queues (each runs one kernel at a time: GPU_MAX_HW_QUEUES, 4 unless set)
 // must fit on the device at once.
-bool flow_serves(int ny, int nz) {
+bool flow_serves(int kind, int ny, int nz) {
   struct Fits {
-    signed char known[11][11];   // 0: not asked yet, 1: fits, -1: does not
+    signed char known[FLOW_KINDS][11][11];   // 0: not asked yet, 1: fits, -1: does not
   };
   static std::mutex mu;
   static Fits fits[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
   std::lock_guard<std::mutex> lock(mu);
-  signed char& k = fits[dev].known[log2_of(ny)][log2_of(nz)];
+  signed char& k = fits[dev].known[kind][log2_of(ny)][log2_of(nz)];
   if (k == 0) {
-    int cus = 0, pf = 0, pr = 0, grid = 0;
+    int cus = 0, per_cu = 0, grid = 0;
     const char* q = std::getenv("GPU_MAX_HW_QUEUES");
     const int queues = q && std::atoi(q) > 4 ? std::atoi(q) : 4;
-    const bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                    flow_occupancy<KIND_FWD_MID>(nz, ny, pf, grid) == hipSuccess &&
-                    flow_occupancy_rev(nz, ny, pr, grid) == hipSuccess &&
-                    (int64_t)queues * grid <= (int64_t)cus * (pf < pr ? pf : pr);
+    hipError_t e = hipErrorNotSupported;
+    switch (kind) {
+      case FLOW_FWD: e = flow_occupancy<FLOW_FWD>(nz, ny, per_cu, grid); break;
+      case FLOW_REV: e = flow_occupancy<FLOW_REV>(nz, ny, per_cu, grid); break;
+      case FLOW_STACK: e = flow_occupancy<FLOW_STACK>(nz, ny, per_cu, grid); break;
+      case FLOW_XFWD: e = flow_occupancy<FLOW_XFWD>(nz, ny, per_cu, grid); break;
+      case FLOW_XREV: e = flow_occupancy<FLOW_XREV>(nz, ny, per_cu, grid); break;
+      default: break;
+    }
+    const bool ok = e == hipSuccess &&
+                    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                    (int64_t)queues * grid <= (int64_t)cus * per_cu;
     if (!ok) (void)hipGetLastError();
     k = ok ? 1 : -1;
   }
@@ -58,9 +66,16 @@ hipError_t launch_flow_init(float2* x, int64_t m, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_flow(const Ctx& c, FlowArgs a, int kind, hipStream_t st) {
+hipError_t launch_flow(int kind, const Ctx& c, FlowArgs a, hipStream_t st) {
   a.nap = flow_nap(c.m);
-  return kind == KIND_FWD_MID ? flow_launch<KIND_FWD_MID>(c, a, st) : launch_flow_rev(c, a, st);
+  switch (kind) {
+    case FLOW_FWD: return flow_launch<FLOW_FWD>(c, a, st);
+    case FLOW_REV: return flow_launch<FLOW_REV>(c, a, st);
+    case FLOW_STACK: return flow_launch<FLOW_STACK>(c, a, st);
+    case FLOW_XFWD: return flow_launch<FLOW_XFWD>(c, a, st);
+    case FLOW_XREV: return flow_launch<FLOW_XREV>(c, a, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace msl

@@ -1,4 +1,4 @@
-// Dataflow schedule: the middle passes of a paraxial phase in one launch,
+// Dataflow schedule: the middle passes of a phase in one launch,
 // handed from pass to pass through memory without a barrier.
 //
 // A wavefront (workgroup) keeps its line for the whole launch.  Every pass
@@ -16,6 +16,10 @@
 // 512x512 6.3 and 4.8; gradient of 256x256x1024 10.7 and 7.5 ms, of
 // 512x512x2048 33.7 and 30.9 ms (there the reverse sweep and the recompute
 // beside it, 9.6 us a slice, gain nothing over their per-pass launches).
+// The exact propagator (a row and a column pass per slice; a column lane keeps its elements of the 2-D
+// factor in registers for the whole launch), per slice: 64x64 7.1 and 3.2 us, 256x256 8.6 and 4.2,
+// 512x512 12.8 and 7.6, its adjoint 15.9 and 4.7, 16.6 and 6.9, 20.1 and 14.1.  The forward that evaluates
+// T from the stacks: 64x64 4.4 and 2.3, 256x256 5.5 and 3.0.
 // Lines of 1024 points take two wavefronts and stay with the per-pass launches.
 //
 // Four exchange fields rotate: pass i reads X[i % 4], writes X[(i + 1) % 4] and
@@ -46,10 +50,6 @@
 
 namespace msl {
 
-constexpr uint32_t kUnset = 0xffb5a3c7u;  // real part of an element not yet stored (a quiet NaN)
-
-// Descriptor of pass p of the phase, a middle pass of the kind: slice, cycle
-// position and the fields that only this pass reads or writes.
 // Keeps a kernel argument in scalar registers for the whole launch (left alone, the compiler
 // reads it again from memory in every pass, on the path between two passes).
 template <typename V>
@@ -61,39 +61,45 @@ __device__ __forceinline__ void pin(V& v) {
 // of both axes' passes in registers, and 512-point lines (8 points per lane) spill.
 __device__ __forceinline__ void fresh(int& v) { asm volatile("" : "+v"(v)); }
 
-template <int KIND>
+constexpr bool flow_exact(int k) { return k == FLOW_XFWD || k == FLOW_XREV; }
+constexpr bool flow_rev(int k) { return k == FLOW_REV || k == FLOW_XREV; }
+constexpr bool flow_pack(int k) { return k == FLOW_FWD || k == FLOW_REV; }
+
+// Slice of pass p of the phase.
+template <int K>
 __device__ __forceinline__ int flow_slice(const PhaseSpec& ph, int p) {
-  return KIND == KIND_FWD_MID ? ph.s0 + p : ph.s1 - 1 - (p - (ph.leading ? 1 : 0));
+  const int q = flow_rev(K) ? p - (ph.leading ? 1 : 0) : p, s = flow_exact(K) ? q >> 1 : q;
+  return flow_rev(K) ? ph.s1 - 1 - s : ph.s0 + s;
 }
 
-template <int KIND>
+// Descriptor of pass p of the phase: slice, cycle position and the fields that only this pass reads or
+// writes (the exact propagator's column passes have none).
+template <int K, int AXIS>
 __device__ __forceinline__ PassDesc flow_desc(const PhaseSpec& ph, int p) {
   PassDesc d{};
-  d.pre = PRE_PROP;
-  d.post = POST_PROP;
-  d.src_lay = d.dst_lay = LAY_T;
-  const int s = flow_slice<KIND>(ph, p);
+  const int s = flow_slice<K>(ph, p);
   d.slice = s;
-  d.axis = s & 1;
-  d.tab = (s >> 1) & (DITHER - 1);   // tab_of, paraxial
-  if constexpr (KIND == KIND_FWD_MID) {
+  d.axis = AXIS;
+  d.tab = (flow_exact(K) ? s : s >> 1) & (DITHER - 1);   // tab_of
+  if (flow_exact(K) && AXIS == COL) return d;
+  const int lay = !flow_exact(K) && (s & 1) ? LAY_C : LAY_T;   // seg_lay
+  if constexpr (!flow_rev(K)) {
     d.mid = MID_T_FWD;
     if (ph.kind == PH_FWD_RECOMP) {
-      d.psi_store = ph.seg + (int64_t)(p - 1) * ph.m;
-      d.store_lay = (s & 1) ? LAY_C : LAY_T;
+      d.psi_store = ph.seg + (int64_t)(s - ph.s0 - 1) * ph.m;
+      d.store_lay = lay;
     } else {
       d.psi_store = ckpt_slot(ph, s);
       d.store_lay = LAY_R;
     }
   } else {
     d.mid = MID_T_ADJ;
-    d.conj = 1;
     if (s == ph.s0) {
       d.psi_load = ph.ckpt_c;
       d.load_lay = LAY_R;
     } else {
       d.psi_load = ph.seg + (int64_t)(s - ph.s0 - 1) * ph.m;
-      d.load_lay = ph.seg_row_major ? LAY_R : ((s & 1) ? LAY_C : LAY_T);
+      d.load_lay = ph.seg_row_major ? LAY_R : lay;
     }
   }
   return d;
@@ -128,7 +134,7 @@ __device__ __forceinline__ V ld_off(const void* base, uint32_t off) {
   return *reinterpret_cast<const V*>(static_cast<const char*>(base) + off);
 }
 
-template <int N, int AXIS, int P>
+template <int N, int AXIS, int P, int K>
 __device__ __forceinline__ void flow_offs(const Ctx& c, int line, int j, FlowOffs<N, P>& o) {
   using T = LineTw<N, P>;
   constexpr int L = N / P;
@@ -143,13 +149,14 @@ __device__ __forceinline__ void flow_offs(const Ctx& c, int line, int j, FlowOff
       for (int r = 1; r < T::R0; ++r) o.wl[q][r - 1] = 8u * (uint32_t)((j + L * q) * r);
   }
   o.h = 8u * (uint32_t)j;
-  o.tm = 8u * line_at<N, AXIS, P>(c, pack_lay<AXIS>(c), line, j).base;
+  if constexpr (flow_pack(K)) o.tm = 8u * line_at<N, AXIS, P>(c, pack_lay<AXIS>(c), line, j).base;
+  else o.tm = 4u * line_at<N, AXIS, P>(c, LAY_R, line, j).base;
 }
 
 // The two halves of load_static of a middle pass, from those offsets: the
 // tables' rows, and what belongs to the slice (T - 1; in the reverse sweep the
 // entrance field).
-template <int N, int AXIS, int P>
+template <int N, int AXIS, int P, bool H1D>
 __device__ __forceinline__ void flow_tables(const Ctx& c, int tab, const FlowOffs<N, P>& o, LineIn<N, P>& in) {
   using T = LineTw<N, P>;
   constexpr uint32_t L = N / P;
@@ -167,22 +174,36 @@ __device__ __forceinline__ void flow_tables(const Ctx& c, int tab, const FlowOff
       for (int r = 1; r < T::R0; ++r) in.tw.wl[q][r - 1] = ld_off<float2>(tw, o.wl[q][r - 1]);
   }
   in.tw.rs2 = rs2_at(tab);
+  if constexpr (H1D) {
 #pragma unroll
-  for (int t = 0; t < P; ++t) in.hh[t] = ld_off<float2>(h, o.h + 8u * L * (uint32_t)t);
+    for (int t = 0; t < P; ++t) in.hh[t] = ld_off<float2>(h, o.h + 8u * L * (uint32_t)t);
+  }
 }
 
 template <int N, int AXIS, int KIND, int P>
 __device__ __forceinline__ void flow_slice_in(const Ctx& c, const PassDesc& pd, int line, int j,
                                               const FlowOffs<N, P>& o, LineIn<N, P>& in) {
   constexpr uint32_t L = N / P;
-  const float2* const tm = c.dbT + (int64_t)pd.slice * c.m;
+  if (flow_exact(KIND) && AXIS == COL) return;
+  if constexpr (flow_pack(KIND)) {
+    const float2* const tm = c.dbT + (int64_t)pd.slice * c.m;
 #pragma unroll
-  for (int t = 0; t < P; ++t) {
-    const float2 q = ld_off<float2>(tm, o.tm + 16u * L * (uint32_t)t);   // 2x2 tiles along the line's axis
-    in.dl[t] = q.x;
-    in.bt[t] = q.y;
+    for (int t = 0; t < P; ++t) {
+      const float2 q = ld_off<float2>(tm, o.tm + 16u * L * (uint32_t)t);   // 2x2 tiles along the line's axis
+      in.dl[t] = q.x;
+      in.bt[t] = q.y;
+    }
+  } else {
+    const float* const dp = c.delta + (int64_t)pd.slice * c.m;
+    const float* const bp = c.beta + (int64_t)pd.slice * c.m;
+    const uint32_t step = 4u * L * (AXIS == ROW ? 1u : (uint32_t)c.nz);
+#pragma unroll
+    for (int t = 0; t < P; ++t) {
+      in.dl[t] = ld_off<float>(dp, o.tm + step * (uint32_t)t);
+      in.bt[t] = ld_off<float>(bp, o.tm + step * (uint32_t)t);
+    }
   }
-  if constexpr (KIND == KIND_REV_MID) {
+  if constexpr (flow_rev(KIND)) {
     const LineAddr a = line_at<N, AXIS, P>(c, pd.load_lay, line, j);
 #pragma unroll
     for (int t = 0; t < P; ++t) in.ps[t] = ld_off<float2>(pd.psi_load, 8u * (a.base + (uint32_t)t * a.stride));
@@ -269,8 +290,7 @@ __device__ __forceinline__ void flow_prop(LineIn<N, P>& in, const LineLds& sh, i
 template <int N, int P, int AXIS, int KIND, int T, int G, bool FRESH, class Prefetch>
 __device__ __forceinline__ void flow_pass(const Ctx& c, const FlowArgs& a, int i, int unit, int line, int j,
                                           const LineLds& sh, const FlowOffs<N, P>& o, LineIn<N, P>& in, int eline,
-                                          FlowEnds<N, P, G>& e, int& dead,
-                                          Prefetch prefetch) {
+                                          FlowEnds<N, P, G>& e, int& dead, Prefetch prefetch) {
   if constexpr (FRESH) {
     fresh(line);
     fresh(j);
@@ -283,13 +303,13 @@ __device__ __forceinline__ void flow_pass(const Ctx& c, const FlowArgs& a, int i
   float2* const wr = a.x + (int64_t)((x + 1) & 3) * c.m;
   float2* const old = a.x + (int64_t)((x + 3) & 3) * c.m;
   const LineAddr xa = flow_at<N, AXIS, P>(c, eline, e.j);
-  const LineAddr fa = line_at<N, AXIS, P>(c, LAY_T, eline, e.j);
+  const LineAddr fa = line_at<N, AXIS, P>(c, KIND == FLOW_STACK ? (int)LAY_R : (int)LAY_T, eline, e.j);   // the working field's
   const uint32_t xo = 8u * xa.base;
   // the reset's share is contiguous (whole 128-byte lines): line by line it cost 0.5 k cycles a pass of
   // 256x256, 1 k of 512x512
   const uint32_t ro = 8u * ((uint32_t)unit * (uint32_t)(T * P) + (threadIdx.x & ~63u) * (uint32_t)P + (threadIdx.x & 63u));
-  PassDesc pd = flow_desc<KIND>(a.ph, a.p0 + i);
-  flow_tables<N, AXIS, P>(c, pd.tab, o, in);
+  const PassDesc pd = flow_desc<KIND, AXIS>(a.ph, a.p0 + i);
+  flow_tables<N, AXIS, P, !flow_exact(KIND)>(c, pd.tab, o, in);
   if constexpr (G > 1) {
     using TW = LineTw<N, P>;
     const float2* const tw = (AXIS == ROW ? c.twz : c.twy) + (uint32_t)pd.tab * (uint32_t)N;
@@ -322,10 +342,27 @@ __device__ __forceinline__ void flow_pass(const Ctx& c, const FlowArgs& a, int i
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the resets of the pass before are complete
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  flow_prop<N, P, G, true, false>(in, sh, j, e, KIND == KIND_REV_MID);
-  mid_line<N, AXIS, TS_PACK, P>(c, pd, line, j, in);
-  prefetch();
-  flow_prop<N, P, G, false, true>(in, sh, j, e, KIND == KIND_REV_MID);
+  constexpr int TS = flow_pack(KIND) ? TS_PACK : TS_RUNTIME;
+  if constexpr (!flow_exact(KIND)) {
+    flow_prop<N, P, G, true, false>(in, sh, j, e, flow_rev(KIND));
+    mid_line<N, AXIS, TS, P>(c, pd, line, j, in);
+    prefetch();
+    flow_prop<N, P, G, false, true>(in, sh, j, e, flow_rev(KIND));
+  } else if constexpr (AXIS == COL) {
+    flow_fft<N, false, P, G, true, false>(in.v, sh, j, in.tw, e);
+#pragma unroll
+    for (int t = 0; t < P; ++t) in.v[t] = cmul_comp_dyn(in.v[t], in.hh[t], in.hl[t], flow_rev(KIND));
+    prefetch();
+    flow_fft<N, true, P, G, false, true>(in.v, sh, j, in.tw, e);
+  } else {
+    constexpr float inv_n = 1.0f / (float)N;
+    flow_fft<N, true, P, G, true, false>(in.v, sh, j, in.tw, e);
+#pragma unroll
+    for (int t = 0; t < P; ++t) in.v[t] = make_float2(in.v[t].x * inv_n, in.v[t].y * inv_n);
+    mid_line<N, AXIS, TS, P>(c, pd, line, j, in);
+    prefetch();
+    flow_fft<N, false, P, G, false, true>(in.v, sh, j, in.tw, e);
+  }
   if (last) {
 #pragma unroll
     for (int t = 0; t < P; ++t) a.ph.field[fa.base + (uint32_t)t * fa.stride] = in.v[t];
@@ -355,11 +392,18 @@ __global__ void __launch_bounds__(T, 2) k_flow(Ctx c_, FlowArgs a_) {
   c.nz = NZ;
   c.m = (int64_t)NY * NZ;
   a.ph.m = c.m;
+  if constexpr (!flow_pack(KIND)) c.dbT = nullptr;
+  else pin(c.dbT);
   pin(c.twz);
   pin(c.twy);
-  pin(c.hz);
-  pin(c.hy);
-  pin(c.dbT);
+  if constexpr (!flow_exact(KIND)) {
+    pin(c.hz);
+    pin(c.hy);
+  }
+  if constexpr (!flow_pack(KIND)) {
+    pin(c.delta);
+    pin(c.beta);
+  }
   pin(a.x);
   pin(a.rot);
   pin(a.nap);
@@ -368,7 +412,7 @@ __global__ void __launch_bounds__(T, 2) k_flow(Ctx c_, FlowArgs a_) {
   pin(a.p0);
   pin(a.ph.s0);
   pin(a.spin_limit);
-  if (KIND == KIND_REV_MID) {
+  if constexpr (flow_rev(KIND)) {
     pin(a.ph.s1);
     pin(a.ph.seg);
     pin(a.ph.leading);
@@ -414,15 +458,23 @@ __global__ void __launch_bounds__(T, 2) k_flow(Ctx c_, FlowArgs a_) {
   FlowOffs<NY, PY> oy;
   // a workgroup that sits out the passes of one axis loads the static inputs of a line that exists
   const int rowl = (UZ == NB || b < UZ) ? row : gz, coll = (UY == NB || b < UY) ? col : gy;
-  flow_offs<NZ, ROW, PZ>(c, rowl, jz, oz);
-  flow_offs<NY, COL, PY>(c, coll, jy, oy);
+  flow_offs<NZ, ROW, PZ, KIND>(c, rowl, jz, oz);
+  flow_offs<NY, COL, PY, KIND>(c, coll, jy, oy);
+  if constexpr (flow_exact(KIND)) {   // one 2-D factor for all slices
+#pragma unroll
+    for (int t = 0; t < PY; ++t) {
+      const uint32_t e = (uint32_t)(jy + t * LY) * NZ + (uint32_t)coll;
+      iny.hh[t] = c.H_hi[e];
+      iny.hl[t] = c.H_lo[e];
+    }
+  }
   int dead = __builtin_amdgcn_readfirstlane(
       (int)__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   auto load_row = [&](int i) {
-    flow_slice_in<NZ, ROW, KIND, PZ>(c, flow_desc<KIND>(a.ph, a.p0 + i), rowl, jz, oz, inz);
+    flow_slice_in<NZ, ROW, KIND, PZ>(c, flow_desc<KIND, ROW>(a.ph, a.p0 + i), rowl, jz, oz, inz);
   };
   auto load_col = [&](int i) {
-    flow_slice_in<NY, COL, KIND, PY>(c, flow_desc<KIND>(a.ph, a.p0 + i), coll, jy, oy, iny);
+    flow_slice_in<NY, COL, KIND, PY>(c, flow_desc<KIND, COL>(a.ph, a.p0 + i), coll, jy, oy, iny);
   };
   // pass 0 is a column pass; past the last pass the prefetch repeats a slice of the launch
   const int n = a.n;

@@ -53,12 +53,12 @@ bool flow_dispatch(int nz, int ny, F&& f) {
   }
 }
 
-template <int KIND>
+template <int K>
 hipError_t flow_launch(const Ctx& c, const FlowArgs& a, hipStream_t st) {
   hipError_t e = hipErrorNotSupported;
   flow_dispatch(c.nz, c.ny, [&](auto z, auto y) {
     constexpr int NZ = decltype(z)::value, NY = decltype(y)::value, T = flow_threads(NZ, NY);
-    hipLaunchKernelGGL((k_flow<NZ, NY, flow_pts<NZ>(), flow_pts<NY>(), KIND, T>), dim3(flow_grid<NZ, NY>()), dim3(T), 0,
+    hipLaunchKernelGGL((k_flow<NZ, NY, flow_pts<NZ>(), flow_pts<NY>(), K, T>), dim3(flow_grid<NZ, NY>()), dim3(T), 0,
                        st, c, a);
     e = hipGetLastError();
   });
@@ -66,13 +66,13 @@ hipError_t flow_launch(const Ctx& c, const FlowArgs& a, hipStream_t st) {
 }
 
 // How many workgroups of the grid's kernel one compute unit holds, and the kernel's grid.
-template <int KIND>
+template <int K>
 hipError_t flow_occupancy(int nz, int ny, int& per_cu, int& grid) {
   hipError_t e = hipErrorNotSupported;
   flow_dispatch(nz, ny, [&](auto z, auto y) {
     constexpr int NZ = decltype(z)::value, NY = decltype(y)::value, T = flow_threads(NZ, NY);
     grid = flow_grid<NZ, NY>();
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_flow<NZ, NY, flow_pts<NZ>(), flow_pts<NY>(), KIND, T>, T,
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_flow<NZ, NY, flow_pts<NZ>(), flow_pts<NY>(), K, T>, T,
                                                      0);
   });
   return e;
