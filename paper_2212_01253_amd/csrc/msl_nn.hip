@@ -1228,6 +1228,30 @@ __global__ void __launch_bounds__(256) k_upsample2(IDX total, int W, int vec, co
   }
 }
 
+// The same for rows of whole 8-byte groups (4 bfloat16 or 2 float32) in aligned arrays: a lane reads
+// 8 bytes and stores 16 to each output row, neighbours side by side (W = groups a row).  Bound by the
+// output's bytes: 67 M bfloat16 elements in 93 us (7.2 TB/s), with one element a lane 165 us; 17 M in 26
+// and 37.  (The adjoint reaches 5.4 TB/s with 8-byte reads and gained nothing from 16-byte ones.)
+template <typename IDX, typename T>
+__global__ void __launch_bounds__(256) k_upsample2_wide(IDX total, int W, const uint2* __restrict__ x,
+                                                        uint4* __restrict__ y) {
+  for (IDX e = (IDX)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (IDX)gridDim.x * blockDim.x) {
+    const IDX r = e / W, w = e - r * W;
+    const uint2 v = x[e];
+    uint4 q;
+    if constexpr (sizeof(T) == 2) {
+      auto lo = [](uint32_t a) { return (a & 0xffffu) | (a << 16); };
+      auto hi = [](uint32_t a) { return (a >> 16) | (a & 0xffff0000u); };
+      q = make_uint4(lo(v.x), hi(v.x), lo(v.y), hi(v.y));
+    } else {
+      q = make_uint4(v.x, v.x, v.y, v.y);
+    }
+    uint4* const o = y + 2 * r * (IDX)W + w;
+    o[0] = q;
+    o[W] = q;
+  }
+}
+
 // Its adjoint: dx[r][w] = (dy[2r][2w] + dy[2r][2w+1]) + (dy[2r+1][2w] + dy[2r+1][2w+1]).
 template <typename IDX>
 __global__ void __launch_bounds__(256) k_upsample2_adj(IDX total, int W, int vec, const float* __restrict__ dy,
@@ -1840,8 +1864,20 @@ msl_status msl_nn_upsample2(int32_t C, int32_t B, int32_t H, int32_t W, const vo
   const int64_t total = (int64_t)C * B * H * W;   // input elements
   const int vec = aligned(y, 2 * es) ? 1 : 0;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const dim3 grid(blocks_for(total));
   const bool small = 4 * total < (1ll << 31);
+  const int per = 8 / es;   // input elements of a group
+  if (W % per == 0 && aligned(x, 8) && aligned(y, 16)) {
+    const int64_t n = total / per;
+    const dim3 gw(blocks_for(n));
+    const uint2* xw = static_cast<const uint2*>(x);
+    uint4* yw = static_cast<uint4*>(y);
+    if (bf16 && small) hipLaunchKernelGGL((k_upsample2_wide<int32_t, uint16_t>), gw, dim3(256), 0, st, (int32_t)n, W / per, xw, yw);
+    else if (bf16) hipLaunchKernelGGL((k_upsample2_wide<int64_t, uint16_t>), gw, dim3(256), 0, st, n, W / per, xw, yw);
+    else if (small) hipLaunchKernelGGL((k_upsample2_wide<int32_t, float>), gw, dim3(256), 0, st, (int32_t)n, W / per, xw, yw);
+    else hipLaunchKernelGGL((k_upsample2_wide<int64_t, float>), gw, dim3(256), 0, st, n, W / per, xw, yw);
+    return launched("upsample kernel");
+  }
+  const dim3 grid(blocks_for(total));
   if (bf16) {
     const uint16_t* xb = static_cast<const uint16_t*>(x);
     uint16_t* yb = static_cast<uint16_t*>(y);
