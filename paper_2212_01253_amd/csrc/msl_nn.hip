@@ -3,17 +3,15 @@
 // convolutional network needs around it (3x3 patch extraction and its adjoint,
 // upsampling, row pooling, ReLU backward, ADAM, loss).
 //
-// The product is tiled for CDNA 64-wide wavefronts: a 256-thread workgroup
-// owns a 64 x 128 tile of C, each of its four wavefronts a 32 x 64 part as two
-// 32 x 32 accumulators of the 32x32x8 bfloat16 MFMA; tiles of A and B pass
-// through LDS with k contiguous, so every lane fetches its four k values of an
-// MFMA operand with one 8-byte read.
+// The plain product gives each 64-wide wavefront a 32 x 32 tile of C, accumulated by the 32x32x8 bfloat16
+// MFMA; the convolutions have kernels of their own.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <algorithm>
 #include <cstdint>
 #include <string>
+#include <type_traits>
 
 #include "msl.h"
 #include "msl_common.hpp"
@@ -45,74 +43,91 @@ struct GemmArgs {
   float* C;
   const float* bias;
   uint16_t* C16;
+  int m0;  // first row of the launch
 };
 
-__global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[TM][KP];  // [m][k]
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[TN][KP];  // [n][k]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
-  f32x16 acc0 = {}, acc1 = {};
+__device__ __forceinline__ void gemm_store(const GemmArgs& g, float* Cz, int m, int n, float v) {
+  const int64_t o = (int64_t)m * g.ldc + n;
+  if (g.beta != 0.0f) v = __builtin_fmaf(g.beta, Cz[o], v);
+  if (g.bias) v += g.bias[m];
+  if (g.relu) v = fmaxf(v, 0.0f);
+  Cz[o] = v;
+  if (g.C16) g.C16[o] = to_bf16(v);
+}
+
+// One wavefront per 32 x 32 tile, operands straight from memory (in practice the caches) into the MFMA
+// lanes: no LDS, no barrier, the next 64 of k fetched during the products.  Bound by the latency of a
+// wavefront's loads along k in small products, by the lanes' requests in large ones.  VA, VB: the
+// operand's k is contiguous and 8-byte aligned (4 values a load); operands whose rows run along m or n are read
+// in whole 64-byte pieces and are the fastest.  Values past the last row or column repeat it (they
+// reach only results that are not stored).  Measured against 64 x 128 tiles staged through LDS, both operands
+// without and with transposition to that order: 256 x 64 x 768 80 -> 9 us, 1024^3 109 -> 22 and 116 -> 17,
+// 4096^3 3.4 -> 1.2 ms and 3.9 -> 0.9 ms, 64 x 10^6 x 64 396 -> 116 us.  The depth runs in steps of 8 into one accumulator.
+template <bool VA, bool VB>
+__global__ void __launch_bounds__(64) k_gemm_bf16(GemmArgs g) {
+  constexpr int U = 8;
+  const int lane = threadIdx.x, m0 = g.m0 + blockIdx.y * 32, n0 = blockIdx.x * 32;
   const int kbeg = blockIdx.z * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
   float* const Cz = g.C + (int64_t)blockIdx.z * g.M * g.ldc;
-  for (int k0 = kbeg; k0 < kend; k0 += TK) {
+  const int ma = min(m0 + (lane & 31), g.M - 1), nb = min(n0 + (lane & 31), g.N - 1);
+  const int64_t sa = g.transA ? g.lda : 1, sb = g.transB ? 1 : g.ldb;   // between neighbouring k
+  const int kq = kbeg + 4 * (lane >> 5);
+  const uint16_t* pa = g.A + (g.transA ? (int64_t)ma : (int64_t)ma * g.lda) + kq * sa;
+  const uint16_t* pb = g.B + (g.transB ? (int64_t)nb * g.ldb : (int64_t)nb) + kq * sb;
+  auto get = [](const uint16_t* q, int64_t s, auto vec) {
+    if constexpr (decltype(vec)::value) return *reinterpret_cast<const bf16x4*>(q);
+    else return bf16x4{(short)q[0], (short)q[s], (short)q[2 * s], (short)q[3 * s]};
+  };
+  f32x16 acc = {};
+  bf16x4 a[U], b[U];
+  auto fetch = [&]() {
 #pragma unroll
-    for (int r = 0; r < (TM * TK) / 256; ++r) {
-      const int e = tid + 256 * r;
-      const int mm = g.transA ? e % TM : e / TK, kk = g.transA ? e / TM : e % TK;
-      const int gm = m0 + mm, gk = k0 + kk;
-      uint16_t val = 0;
-      if (gm < g.M && gk < kend) val = g.A[g.transA ? (int64_t)gk * g.lda + gm : (int64_t)gm * g.lda + gk];
-      As[mm][kk] = val;
+    for (int u = 0; u < U; ++u) {
+      a[u] = get(pa + 8 * u * sa, sa, std::bool_constant<VA>{});
+      b[u] = get(pb + 8 * u * sb, sb, std::bool_constant<VB>{});
     }
+    pa += 8 * U * sa;
+    pb += 8 * U * sb;
+  };
+  const int nfull = (kend - kbeg) / (8 * U);
+  if (nfull > 0) fetch();
+  for (int i = 0; i < nfull; ++i) {
+    bf16x4 x[U], y[U];
 #pragma unroll
-    for (int r = 0; r < (TN * TK) / 256; ++r) {
-      const int e = tid + 256 * r;
-      const int nn = g.transB ? e / TK : e % TN, kk = g.transB ? e % TK : e / TN;
-      const int gk = k0 + kk, gn = n0 + nn;
-      uint16_t val = 0;
-      if (gk < kend && gn < g.N) val = g.B[g.transB ? (int64_t)gn * g.ldb + gk : (int64_t)gk * g.ldb + gn];
-      Bs[nn][kk] = val;
+    for (int u = 0; u < U; ++u) {
+      x[u] = a[u];
+      y[u] = b[u];
     }
-    __syncthreads();
+    if (i + 1 < nfull) fetch();
 #pragma unroll
-    for (int ks = 0; ks < TK; ks += 8) {
-      const int kq = ks + 4 * (lane >> 5);
-      const bf16x4 a = *reinterpret_cast<const bf16x4*>(&As[wm + (lane & 31)][kq]);
-      const bf16x4 b0 = *reinterpret_cast<const bf16x4*>(&Bs[wn + (lane & 31)][kq]);
-      const bf16x4 b1 = *reinterpret_cast<const bf16x4*>(&Bs[wn + 32 + (lane & 31)][kq]);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b0, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b1, acc1, 0, 0, 0);
-    }
-    __syncthreads();
+    for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x[u], y[u], acc, 0, 0, 0);
   }
-  // accumulator element 4i + j of lane l is C[8i + 4(l / 32) + j][l % 32] of the 32 x 32 tile
+  for (int k = nfull * 8 * U; kbeg + k < kend; k += 8) {
+    bf16x4 x = {}, y = {};
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int n = n0 + wn + 32 * h + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + wm + 8 * i + 4 * (lane >> 5) + j;
-        if (m < g.M && n < g.N) {
-          float v = h ? acc1[4 * i + j] : acc0[4 * i + j];
-          const int64_t o = (int64_t)m * g.ldc + n;
-          if (g.beta != 0.0f) v = __builtin_fmaf(g.beta, Cz[o], v);
-          if (g.bias) v += g.bias[m];
-          if (g.relu) v = fmaxf(v, 0.0f);
-          Cz[o] = v;
-          if (g.C16) g.C16[o] = to_bf16(v);
-        }
+    for (int t = 0; t < 4; ++t)
+      if (kq + k + t < kend) {
+        x[t] = (short)pa[t * sa];
+        y[t] = (short)pb[t * sb];
       }
+    pa += 8 * sa;
+    pb += 8 * sb;
+    acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(x, y, acc, 0, 0, 0);
   }
+  const int n = n0 + (lane & 31);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int m = m0 + 8 * i + 4 * (lane >> 5) + j;
+      if (m < g.M && n < g.N) gemm_store(g, Cz, m, n, acc[4 * i + j]);
+    }
 }
 
 // ---------------------------------------------------------------------------
 // The input gradient of a stride-2 convolution into an array without 8-byte alignment, as an implicit
-// product: the tiles, LDS layout and MFMA sequence of k_gemm_bf16, with the patch operand formed while
-// it is loaded.  k runs over (output channel, tap), tap = 3 (dy + 1) + (dx + 1).
+// product of 64 x 128 tiles staged through LDS, with the patch operand formed while it is loaded.
+// k runs over (output channel, tap), tap = 3 (dy + 1) + (dx + 1).
 
 struct ConvArgs {
   int Co, C, B, H, W, s, Ho, Wo;
@@ -1552,6 +1567,20 @@ unsigned blocks_for(int64_t n) {
 
 msl_status need(bool ok, const char* what) { return ok ? MSL_OK : fail(MSL_ERR_ARG, what); }
 
+// A product of `parts` depth ranges, in launches of at most 65535 tile rows.
+msl_status launch_gemm(GemmArgs g, int parts, hipStream_t st) {
+  MSL_TRY(need((g.M + 63) / 64 <= 65535, "gemm: M too large"));
+  const bool va = !g.transA && g.lda % 4 == 0 && aligned(g.A, 8), vb = g.transB && g.ldb % 4 == 0 && aligned(g.B, 8);
+  for (g.m0 = 0; g.m0 < g.M; g.m0 += 65535 * 32) {
+    const dim3 gs((g.N + 31) / 32, std::min((g.M - g.m0 + 31) / 32, 65535), parts);
+    if (va && vb) hipLaunchKernelGGL((k_gemm_bf16<true, true>), gs, dim3(64), 0, st, g);
+    else if (va) hipLaunchKernelGGL((k_gemm_bf16<true, false>), gs, dim3(64), 0, st, g);
+    else if (vb) hipLaunchKernelGGL((k_gemm_bf16<false, true>), gs, dim3(64), 0, st, g);
+    else hipLaunchKernelGGL((k_gemm_bf16<false, false>), gs, dim3(64), 0, st, g);
+  }
+  return MSL_OK;
+}
+
 msl_status launched(const char* what) { return hip_check(hipGetLastError(), what); }
 
 template <int MB, int PX, int R, bool XS, int MODE>
@@ -1667,10 +1696,8 @@ msl_status msl_nn_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t* A, 
   MSL_TRY(check_ptr(C, 4, "C"));
   MSL_TRY(check_ptr(bias, 4, "bias", true));
   MSL_TRY(check_ptr(C16, 2, "C16", true));
-  GemmArgs g{M, N, K, lda, transA ? 1 : 0, ldb, transB ? 1 : 0, ldc, relu ? 1 : 0, K, beta, A, B, C, bias, C16};
-  const dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
-  MSL_TRY(need(grid.y <= 65535, "gemm: M too large"));
-  hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, static_cast<hipStream_t>(hip_stream), g);
+  GemmArgs g{M, N, K, lda, transA ? 1 : 0, ldb, transB ? 1 : 0, ldc, relu ? 1 : 0, K, beta, A, B, C, bias, C16, 0};
+  MSL_TRY(launch_gemm(g, 1, static_cast<hipStream_t>(hip_stream)));
   return launched("gemm kernel");
 }
 
@@ -1688,11 +1715,9 @@ msl_status msl_nn_gemm_bf16_splitk(int32_t M, int32_t N, int32_t K, const uint16
   int kchunk = (K + splits - 1) / splits;
   kchunk = (kchunk + TK - 1) / TK * TK;
   const int parts = (K + kchunk - 1) / kchunk;
-  GemmArgs g{M, N, K, lda, transA ? 1 : 0, ldb, transB ? 1 : 0, N, 0, kchunk, 0.0f, A, B, partials, nullptr, nullptr};
-  const dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM, parts);
-  MSL_TRY(need(grid.y <= 65535, "gemm: M too large"));
+  GemmArgs g{M, N, K, lda, transA ? 1 : 0, ldb, transB ? 1 : 0, N, 0, kchunk, 0.0f, A, B, partials, nullptr, nullptr, 0};
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, st, g);
+  MSL_TRY(launch_gemm(g, parts, st));
   const int64_t mn = (int64_t)M * N;
   hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, mn, parts, partials, M, N, ldc,
                      C);
