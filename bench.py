@@ -225,7 +225,7 @@ def roofline(pass_bytes, launch_s, traffic, prof, ny, nz, pass_gbs, pass_tflops,
            "floor_us": pass_bytes / (HBM_PEAK_GBS * 1e9) * 1e6}
     roof = {"bound": "hbm", "achieved": pass_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": pass_gbs / HBM_PEAK_GBS, "traffic": (traffic / launch_s / 1e9) if traffic else None,
-            "kernel": "k_pass<512,*,1> forward line pass (propagate, transmit, propagate)",
+            "kernel": "forward line pass (propagate, transmit, propagate), one of the launch's middle passes",
             "bytes_per_launch": pass_bytes, "us_per_launch": launch_s * 1e6, "traffic_bytes_per_launch": traffic,
             "rocprof_kernel_us": prof_us, "hbm": hbm,
             "flops_per_launch": fwd_flops_per_voxel_slice(nz) * ny * nz, "achieved_TFLOPs": pass_tflops,

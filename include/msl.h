@@ -85,8 +85,8 @@ typedef enum { MSL_PROP_PARAXIAL = 0, MSL_PROP_EXACT = 1 } msl_propagator;
 typedef enum {
   MSL_SCHED_AUTO = 0,        /* library choice: one launch for the middle passes of a phase, the field
                                 handed over through memory element by element, where that serves
-                                (paraxial calls with a slice pack on grids up to 512 x 512, the
-                                default launch shape, a stream without a compute-unit mask); else one launch per line pass.  The
+                                (grids up to 512 x 512 in either propagator, the default launch shape,
+                                a stream without a compute-unit mask); else one launch per line pass.  The
                                 results are bit for bit those of MSL_SCHED_PER_PASS. */
   MSL_SCHED_PER_PASS = 1,    /* one kernel launch per line pass */
   MSL_SCHED_PERSISTENT = 2   /* one cooperative launch per phase, grid barriers between passes

@@ -58,7 +58,7 @@ msl_status msl_nn_col2im3x3(int32_t C, int32_t B, int32_t H, int32_t W, int32_t 
  * pad16 rounding up to a multiple of 16), or 0 for invalid sizes. */
 int64_t msl_nn_conv3x3_scratch_elems(int32_t Co, int32_t C);
 
-/* 3x3 convolution, zero padding 1, stride 1 or 2, as an implicit matrix-core product on halo tiles
+/* 3x3 convolution, zero padding 1, stride 1 or 2, as an implicit matrix-core product
  * (no patch matrix in memory):
  * y[o][b][i][j] = act(sum_c sum_t w16[o][9c + t] bf16(x[c][b][s i + dy][s j + dx]) + bias[o]),
  * t = 3 (dy + 1) + (dx + 1); x [C][B][H][W] float32 (x_bf16 0) or bfloat16 bits (x_bf16 1: used
@@ -76,12 +76,12 @@ msl_status msl_nn_conv3x3(int32_t Co, int32_t C, int32_t B, int32_t H, int32_t W
 
 /* Its input gradient, also implicit: dx[c][b][y][x] = sum over o and taps t of w16[o][9c + t] dy16[o][b][i][j]
  * where s i + dy = y and s j + dx = x (dy16 bfloat16 [Co][B][H/s][W/s]; dx float32 [C][B][H][W],
- * overwritten).  Runs on halo tiles with the weights repacked into wscratch (required): stride 1 as
+ * overwritten).  Runs on the forward's kernels with the weights repacked into wscratch (required): stride 1 as
  * a convolution of dy16 with the weights transposed and rotated by 180 degrees; stride 2 (dx 8-byte
  * aligned) split by the parity of (y, x) into a 2x2 convolution of dy16 with 4 C rows (zero weights
  * where a parity class has no tap).  A stride-2 call with dx not 8-byte aligned runs as an implicit
  * product over the patch columns instead.  accumulate 1: dx += the gradient instead of dx = (the
- * gradient of a layer whose input also feeds a skip connection; needs the halo path). */
+ * gradient of a layer whose input also feeds a skip connection; not with that implicit product). */
 msl_status msl_nn_conv3x3_adjoint(int32_t Co, int32_t C, int32_t B, int32_t H, int32_t W, int32_t stride,
                                   const uint16_t* w16, const uint16_t* dy16, float* dx, int32_t accumulate,
                                   uint16_t* wscratch, void* hip_stream);
@@ -90,10 +90,8 @@ msl_status msl_nn_conv3x3_adjoint(int32_t Co, int32_t C, int32_t B, int32_t H, i
  * patch value (c, t) at p (x float32 rounded to bfloat16 as in the forward, or with x_bf16 1 bfloat16
  * bits used as is: the same result as float32 x holding those values); the pixel sum is split into at
  * most `splits` parts written to partials (float32 [splits][Co][9C], caller-owned scratch) and then
- * summed in a fixed order into dw (float32 [Co][9C]).  When the output width W/s is a multiple of 8 the parts
- * are ranges of 128/s-pixel halo tiles (as many parts as fill the GPU, at most `splits`), otherwise
- * ranges of pixels of the patch-column product (msl_nn_gemm_bf16_splitk of dy16 and the patch
- * matrix, bit for bit).  1 <= splits <= 4096. */
+ * summed in a fixed order into dw (float32 [Co][9C]).  The parts are ranges of image rows (as many as
+ * fill the GPU, at most `splits`).  1 <= splits <= 4096. */
 msl_status msl_nn_conv3x3_weight_grad(int32_t Co, int32_t C, int32_t B, int32_t H, int32_t W, int32_t stride,
                                      const uint16_t* dy16, const void* x, int32_t x_bf16, float* dw, int32_t splits,
                                      float* partials, void* hip_stream);
