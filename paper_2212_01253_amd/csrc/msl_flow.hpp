@@ -23,16 +23,29 @@
 // Lines of 1024 points take two wavefronts and stay with the per-pass launches.
 //
 // Four exchange fields rotate: pass i reads X[i % 4], writes X[(i + 1) % 4] and
-// then returns its share of X[(i - 1) % 4] to kUnset.
+// returns its share of X[(i - 1) % 4] to kUnset.
 //  * Nobody still reads X[(i - 1) % 4] then: the workgroup has held whole lines
 //    of pass i's input, an element from every line of pass i - 1, and each of
 //    those was stored after its producer had read all it needed of
 //    X[(i - 1) % 4].
-//  * The reset is complete before the workgroup computes pass i + 1 (it waits
-//    for its own stores), X[(i - 1) % 4] is written next in pass i + 2, by
-//    workgroups that have read pass i + 1's output, and read in pass i + 3 by
-//    workgroups that have read pass i + 2's: they see the sentinel or the new
-//    value, never the old one.
+//  * X[(i - 1) % 4] is written next in pass i + 2 and read in pass i + 3.  The new
+//    elements have to come after the resets, and a reader's first look too, or it
+//    could take the old value.
+//  * Where every workgroup takes part in every pass, the resets follow the pass's output and are
+//    complete before the workgroup computes pass i + 1 (it waits for its own
+//    stores): who writes in pass i + 2 has read pass i + 1's output, who reads in
+//    pass i + 3 has read it in pass i + 2.
+//  * Where the axes have different numbers of line groups some workgroups sit out every second
+//    pass: one that sits out pass i + 2 has seen nothing after pass i's output when it looks
+//    for pass i + 2's in pass i + 3, and one that resets in pass i and sits out pass i + 1 tells nobody in
+//    between that its resets are done.  There (flow_resets_early) the resets are issued
+//    once the workgroup holds its input (after the barrier of the first transform's first exchange),
+//    and are complete before any of its output is stored: pass i's output carries the news.
+//    The wait is hidden by the second transform; it is not taken on the other grids, where it
+//    would stand between the last exchange and the stores that everybody waits for.  512x256 with
+//    this order, forward and adjoint per slice (one launch per pass): 4.3 and 6.7 us (5.4 and 9.7), exact
+//    5.9 and 9.1 (10.4 and 17.3); 64x512 3.0 and 4.6 (4.6 and 9.1).
+// flow_check.cpp follows both orders through the passes of all grids.
 // A launch finds all four fields unset but X[0], which its first pass does not
 // read and its pass 1 resets, and leaves them so but for X[n - 1], the last
 // pass's input: the next launch on the same fields starts its rotation there
@@ -232,9 +245,17 @@ struct FlowEnds {
   LineTw<N, P> tw;   // the last stage's twiddles for that lane (w[NPW - 1] only)
 };
 
+// Waits until this wavefront's stores (and loads) are complete.
+__device__ __forceinline__ void flow_wait() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // fft_line within a wavefront (radix P throughout) whose input (IN) or output
-// (OUT) is held as FlowEnds says.
-template <int N, bool INV, int P, int G, bool IN, bool OUT>
+// (OUT) is held as FlowEnds says.  EARLY: the wavefront's stores are complete before its workgroup
+// meets for the last exchange of the output (G > 1).
+template <int N, bool INV, int P, int G, bool IN, bool OUT, bool EARLY>
 __device__ __forceinline__ void flow_fft(float2 (&v)[P], const LineLds& sh, int j, const LineTw<N, P>& tw,
                                          const FlowEnds<N, P, G>& e) {
   if constexpr (G == 1 || (!IN && !OUT)) {
@@ -256,7 +277,10 @@ __device__ __forceinline__ void flow_fft(float2 (&v)[P], const LineLds& sh, int 
 #pragma unroll
     for (int s = 0, NS = P; s < NX; ++s, NS *= P) {
       const bool out = OUT && s == NX - 1;
-      if (out) __syncthreads();
+      if (out) {
+        if constexpr (EARLY) flow_wait();
+        __syncthreads();
+      }
       const LineLds& b = out ? e.sh : sh;
       const float2* const rd = (s & 1) ? b.b : b.a;
 #pragma unroll
@@ -275,19 +299,19 @@ __device__ __forceinline__ void flow_fft(float2 (&v)[P], const LineLds& sh, int 
   }
 }
 
-template <int N, int P, int G, bool IN, bool OUT>
+template <int N, int P, int G, bool IN, bool OUT, bool EARLY>
 __device__ __forceinline__ void flow_prop(LineIn<N, P>& in, const LineLds& sh, int j, const FlowEnds<N, P, G>& e,
                                           bool conj) {
-  flow_fft<N, false, P, G, IN, false>(in.v, sh, j, in.tw, e);
+  flow_fft<N, false, P, G, IN, false, EARLY>(in.v, sh, j, in.tw, e);
 #pragma unroll
   for (int t = 0; t < P; ++t) in.v[t] = cmul_dyn(in.v[t], in.hh[t], conj);
-  flow_fft<N, true, P, G, false, OUT>(in.v, sh, j, in.tw, e);
+  flow_fft<N, true, P, G, false, OUT, EARLY>(in.v, sh, j, in.tw, e);
 }
 
 // One pass of this workgroup's lines (group `unit` of the pass; this lane's
 // line and lane between the transforms, eline and e.j at the ends); in: the
 // slice's inputs, already requested.  prefetch() requests the next pass's.
-template <int N, int P, int AXIS, int KIND, int T, int G, bool FRESH, class Prefetch>
+template <int N, int P, int AXIS, int KIND, int T, int G, bool FRESH, bool EARLY, class Prefetch>
 __device__ __forceinline__ void flow_pass(const Ctx& c, const FlowArgs& a, int i, int unit, int line, int j,
                                           const LineLds& sh, const FlowOffs<N, P>& o, LineIn<N, P>& in, int eline,
                                           FlowEnds<N, P, G>& e, int& dead, Prefetch prefetch) {
@@ -339,30 +363,39 @@ __device__ __forceinline__ void flow_pass(const Ctx& c, const FlowArgs& a, int i
       }
     }
   }
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the resets of the pass before are complete
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  if constexpr (!EARLY) flow_wait();   // the resets of the pass before are complete
+  auto reset = [&]() {
+    if (first) return;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    const float q = __uint_as_float(kUnset);
+#pragma unroll
+    for (int t = 0; t < P; ++t) flow_st(old, ro + 512u * (uint32_t)t, make_float2(q, q));
+  };
   constexpr int TS = flow_pack(KIND) ? TS_PACK : TS_RUNTIME;
   if constexpr (!flow_exact(KIND)) {
-    flow_prop<N, P, G, true, false>(in, sh, j, e, flow_rev(KIND));
+    flow_prop<N, P, G, true, false, EARLY>(in, sh, j, e, flow_rev(KIND));
+    if constexpr (EARLY) reset();
     mid_line<N, AXIS, TS, P>(c, pd, line, j, in);
     prefetch();
-    flow_prop<N, P, G, false, true>(in, sh, j, e, flow_rev(KIND));
+    flow_prop<N, P, G, false, true, EARLY>(in, sh, j, e, flow_rev(KIND));
   } else if constexpr (AXIS == COL) {
-    flow_fft<N, false, P, G, true, false>(in.v, sh, j, in.tw, e);
+    flow_fft<N, false, P, G, true, false, EARLY>(in.v, sh, j, in.tw, e);
+    if constexpr (EARLY) reset();
 #pragma unroll
     for (int t = 0; t < P; ++t) in.v[t] = cmul_comp_dyn(in.v[t], in.hh[t], in.hl[t], flow_rev(KIND));
     prefetch();
-    flow_fft<N, true, P, G, false, true>(in.v, sh, j, in.tw, e);
+    flow_fft<N, true, P, G, false, true, EARLY>(in.v, sh, j, in.tw, e);
   } else {
     constexpr float inv_n = 1.0f / (float)N;
-    flow_fft<N, true, P, G, true, false>(in.v, sh, j, in.tw, e);
+    flow_fft<N, true, P, G, true, false, EARLY>(in.v, sh, j, in.tw, e);
+    if constexpr (EARLY) reset();
 #pragma unroll
     for (int t = 0; t < P; ++t) in.v[t] = make_float2(in.v[t].x * inv_n, in.v[t].y * inv_n);
     mid_line<N, AXIS, TS, P>(c, pd, line, j, in);
     prefetch();
-    flow_fft<N, false, P, G, false, true>(in.v, sh, j, in.tw, e);
+    flow_fft<N, false, P, G, false, true, EARLY>(in.v, sh, j, in.tw, e);
   }
+  if constexpr (EARLY && G == 1) flow_wait();   // (G > 1: before the last exchange)
   if (last) {
 #pragma unroll
     for (int t = 0; t < P; ++t) a.ph.field[fa.base + (uint32_t)t * fa.stride] = in.v[t];
@@ -374,11 +407,7 @@ __device__ __forceinline__ void flow_pass(const Ctx& c, const FlowArgs& a, int i
       flow_st(wr, xo + 8u * (uint32_t)t * xa.stride, v);
     }
   }
-  if (!first) {
-    const float q = __uint_as_float(kUnset);
-#pragma unroll
-    for (int t = 0; t < P; ++t) flow_st(old, ro + 512u * (uint32_t)t, make_float2(q, q));
-  }
+  if constexpr (!EARLY) reset();
 }
 
 // Middle passes of one phase over an NY x NZ grid by workgroups of T threads:
@@ -433,7 +462,8 @@ __global__ void __launch_bounds__(T, 2) k_flow(Ctx c_, FlowArgs a_) {
   constexpr int UZ = NY / GZ, UY = NZ / GY;  // line groups of a row pass, of a column pass
   // the wavefronts of a workgroup part at a pass's last exchange and meet at the next pass's first one;
   // where that one may use a buffer the last exchange is still read from, they meet between the passes
-  constexpr bool FR = PZ == 8 || PY == 8;
+  constexpr bool FR = PZ == 8 || PY == 8, EARLY = flow_resets_early(NZ, NY);
+  static_assert(UZ == flow_row_units(NZ, NY) && UY == flow_col_units(NZ, NY), "the order flow_check.cpp follows");
   constexpr bool kMeet = T > 64 && (NZ != NY || LineTw<NZ, PZ>::NST % 2 == 1);
   constexpr int NB = UZ > UY ? UZ : UY;  // the launch's grid
   const int b = xcd_group(blockIdx.x, gridDim.x);
@@ -482,14 +512,14 @@ __global__ void __launch_bounds__(T, 2) k_flow(Ctx c_, FlowArgs a_) {
   for (int i = 0;;) {
     int nx = i + 1 < n ? i + 1 : i;
     if (UY == NB || b < UY)
-      flow_pass<NY, PY, COL, KIND, T, EY, FR>(c, a, i, b, col, jy, shy, oy, iny, b * GY + ey, endy, dead, [&]() { load_row(nx); });
+      flow_pass<NY, PY, COL, KIND, T, EY, FR, EARLY>(c, a, i, b, col, jy, shy, oy, iny, b * GY + ey, endy, dead, [&]() { load_row(nx); });
     else
       load_row(nx);
     if (++i >= n) break;
     if (kMeet) __syncthreads();
     nx = i + 1 < n ? i + 1 : i;
     if (UZ == NB || b < UZ)
-      flow_pass<NZ, PZ, ROW, KIND, T, EZ, FR>(c, a, i, b, row, jz, shz, oz, inz, b * GZ + ez, endz, dead, [&]() { load_col(nx); });
+      flow_pass<NZ, PZ, ROW, KIND, T, EZ, FR, EARLY>(c, a, i, b, row, jz, shz, oz, inz, b * GZ + ez, endz, dead, [&]() { load_col(nx); });
     else
       load_col(nx);
     if (++i >= n) break;

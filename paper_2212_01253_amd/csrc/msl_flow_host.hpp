@@ -16,6 +16,29 @@ struct FlowArgs {
   int nap;                // pauses before the first look at a pass's input
 };
 
+// Points per lane of the dataflow kernels (default_points_per_lane of the per-pass launches, so that
+// both compute the same bits).
+constexpr int flow_pts(int n) { return n >= 512 ? 8 : 4; }
+
+// Threads per workgroup: one wavefront, or two where both axes have lines of a wavefront each and one
+// of them 512 points (FlowEnds).  One-wavefront workgroups touch the 128-byte tiles of the exchange
+// field in 16-byte pieces there, and 512 lines of 512 points then wait for the memory pipes: 12.2 k
+// cycles a pass of 512x512 against 10.9 k in pairs of lines; at 256x256 the pairs' barriers
+// cost more than the pieces (6.8 k cycles against 5.8 k).  Four lines: 13.9 k.
+constexpr int flow_threads(int nz, int ny) {
+  return (nz == 512 || ny == 512) && nz >= 256 && ny >= 256 ? 128 : 64;
+}
+
+// Lines per workgroup of an n-point axis, and workgroups of a row and of a column pass.
+constexpr int flow_lines(int nz, int ny, int n) { return flow_threads(nz, ny) / (n / flow_pts(n)); }
+constexpr int flow_row_units(int nz, int ny) { return ny / flow_lines(nz, ny, nz); }
+constexpr int flow_col_units(int nz, int ny) { return nz / flow_lines(nz, ny, ny); }
+
+// Whether a pass returns its share of the exchange field of two passes before to unset ahead of its output
+// instead of after it (msl_flow.hpp): where the axes have different numbers of workgroups, so that
+// some sit out every second pass.
+constexpr bool flow_resets_early(int nz, int ny) { return flow_row_units(nz, ny) != flow_col_units(nz, ny); }
+
 constexpr int kFlowMinPasses = 4;   // a launch of fewer passes is not worth its two ends
 
 // What the passes of a launch are: the paraxial middle passes of the forward sweep and the recompute with

@@ -6,24 +6,9 @@
 
 namespace msl {
 
-// Points per lane of the dataflow kernels (default_points_per_lane of the per-pass launches, so that
-// both compute the same bits).
-template <int N>
-constexpr int flow_pts() { return N >= 512 ? 8 : 4; }
-
-// Threads per workgroup: one wavefront, or two where both axes have lines of a wavefront each and one
-// of them 512 points (FlowEnds).  One-wavefront workgroups touch the 128-byte tiles of the exchange
-// field in 16-byte pieces there, and 512 lines of 512 points then wait for the memory pipes: 12.2 k
-// cycles a pass of 512x512 against 10.9 k in pairs of lines; at 256x256 the pairs' barriers
-// cost more than the pieces (6.8 k cycles against 5.8 k).  Four lines: 13.9 k.
-constexpr int flow_threads(int nz, int ny) {
-  return (nz == 512 || ny == 512) && nz >= 256 && ny >= 256 ? 128 : 64;
-}
-
 template <int NZ, int NY>
 constexpr int flow_grid() {
-  constexpr int T = flow_threads(NZ, NY), GZ = T / (NZ / flow_pts<NZ>()), GY = T / (NY / flow_pts<NY>());
-  return NY / GZ > NZ / GY ? NY / GZ : NZ / GY;
+  return flow_row_units(NZ, NY) > flow_col_units(NZ, NY) ? flow_row_units(NZ, NY) : flow_col_units(NZ, NY);
 }
 
 // Calls f.template operator()<NZ, NY>() for the grid; false: no kernel for it.
@@ -58,7 +43,7 @@ hipError_t flow_launch(const Ctx& c, const FlowArgs& a, hipStream_t st) {
   hipError_t e = hipErrorNotSupported;
   flow_dispatch(c.nz, c.ny, [&](auto z, auto y) {
     constexpr int NZ = decltype(z)::value, NY = decltype(y)::value, T = flow_threads(NZ, NY);
-    hipLaunchKernelGGL((k_flow<NZ, NY, flow_pts<NZ>(), flow_pts<NY>(), K, T>), dim3(flow_grid<NZ, NY>()), dim3(T), 0,
+    hipLaunchKernelGGL((k_flow<NZ, NY, flow_pts(NZ), flow_pts(NY), K, T>), dim3(flow_grid<NZ, NY>()), dim3(T), 0,
                        st, c, a);
     e = hipGetLastError();
   });
@@ -72,7 +57,7 @@ hipError_t flow_occupancy(int nz, int ny, int& per_cu, int& grid) {
   flow_dispatch(nz, ny, [&](auto z, auto y) {
     constexpr int NZ = decltype(z)::value, NY = decltype(y)::value, T = flow_threads(NZ, NY);
     grid = flow_grid<NZ, NY>();
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_flow<NZ, NY, flow_pts<NZ>(), flow_pts<NY>(), K, T>, T,
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_flow<NZ, NY, flow_pts(NZ), flow_pts(NY), K, T>, T,
                                                      0);
   });
   return e;
