@@ -150,7 +150,7 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
  * the caller.  MSL_SCHED_AUTO runs the middle passes of a paraxial call as one
  * dataflow launch where its exchange fields (4 ny nz complex64) fit the array
  * beside the tables, any other setting one launch per pass; a wait that ends
- * at the spin limit leaves NaN in field_out. */
+ * at the spin limit leaves NaN in field_out and ckpt. */
 #define MSL_NOALLOC_SCRATCH_BYTES ((size_t)(4 * 64 * 1024 * 8 + 2 * 512 * 512 * 8))
 msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const float* beta,
                                const msl_c64* probe, msl_c64* field_out,
@@ -220,8 +220,9 @@ int32_t msl_set_schedule(int32_t schedule);
  * hip_stream, then returns MSL_OK, or MSL_ERR_HIP if a grid barrier of the
  * persistent schedule or a pass of the one-launch schedule gave up waiting.
  * That wait is bounded (it polls at most the spin limit below, then raises an
- * error word and lets the grid drain); the call's results are then not valid,
- * and its working field holds NaN.  Errors of the per-pass schedule surface as HIP errors instead. */
+ * error word and lets the grid drain); the call's results are then not valid:
+ * every element of the exit wave, and after the one-launch schedule of the checkpoints and gradients
+ * too, is NaN.  Errors of the per-pass schedule surface as HIP errors instead. */
 msl_status msl_workspace_status(void* workspace, size_t ws_bytes, void* hip_stream);
 
 /* Polls the persistent schedule's barrier, or a pass of the one-launch schedule,

@@ -703,6 +703,19 @@ msl_status run_flow(const Call& k, const PhaseSpec& a, int kind, int p0, int n) 
   return hip_check(msl::launch_flow(kind, k.c, f, k.st), "dataflow kernel");
 }
 
+// End of a call: its outputs o to NaN if one of its dataflow launches gave up.
+msl_status end_flow(const Call& k, const msl::FlowOuts& o) {
+  if (!k.flow_rot || (k.flow_rot[0] < 0 && k.flow_rot[1] < 0)) return MSL_OK;   // it made none
+  const unsigned* err = reinterpret_cast<const unsigned*>(k.ws + k.L.bar) + 2;
+  return hip_check(msl::launch_flow_fold(err, o, k.st), "dataflow error kernel");
+}
+
+// The outputs of a forward.
+msl::FlowOuts forward_outs(const msl_geometry& g, msl_c64* field, msl_c64* ckpt, int ckpt_every) {
+  const int64_t m = (int64_t)g.ny * g.nz, nck = ckpt ? (g.n_slices + ckpt_every - 1) / ckpt_every : 0;
+  return {{reinterpret_cast<float*>(field), reinterpret_cast<float*>(ckpt), nullptr, nullptr}, {2 * m, 2 * m * nck, 0, 0}};
+}
+
 // Runs phase a, and phase b beside it when given (independent fields of a
 // square grid), either as one cooperative launch or as launches per pass.
 msl_status run_phases(const Call& k, const PhaseSpec& a, const PhaseSpec* b) {
@@ -1156,7 +1169,7 @@ msl_status msl_workspace_status(void* workspace, size_t ws_bytes, void* hip_stre
   MSL_TRY(hip_check(hipMemcpy(w, workspace, sizeof w, hipMemcpyDeviceToHost), "hipMemcpy"));
   if (w[1] != 0u)
     return fail(MSL_ERR_HIP, "a grid barrier or a dataflow pass gave up waiting (bounded spin) in the last "
-                             "call on this workspace; its results are not valid (the working field holds NaN)");
+                             "call on this workspace; its results are not valid (they hold NaN)");
   return MSL_OK;
 }
 
@@ -1282,7 +1295,8 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
   } else {
     MSL_TRY(pack_slices(k));
   }
-  return run_phase(k, ph);
+  MSL_TRY(run_phase(k, ph));
+  return end_flow(k, forward_outs(*g, field_out, ckpt, ckpt_every));
 }
 
 msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const float* beta, const msl_c64* probe,
@@ -1324,7 +1338,8 @@ msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const 
   ph.rowmajor = 1;
   ph.ckpt = reinterpret_cast<float2*>(ckpt);
   ph.ckpt_every = ckpt ? ckpt_every : 0;
-  return run_phase(k, ph);
+  MSL_TRY(run_phase(k, ph));
+  return end_flow(k, forward_outs(*g, field_out, ckpt, ckpt_every));
 }
 
 msl_status msl_far_field(const msl_geometry* g, const msl_c64* field, float* intensity, void* workspace,
@@ -1440,6 +1455,8 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
     rv.ckpt_c = ck + (int64_t)c * k.c.m;
     return rv;
   };
+  const msl::FlowOuts outs{{grad_delta, grad_beta, reinterpret_cast<float*>(grad_probe), nullptr},
+                           {ns * k.c.m, ns * k.c.m, 2 * k.c.m, 0}};
   if (ckpt_every == 1) {
     // every entrance field is a checkpoint: one reverse sweep reads them
     // directly (row-major), nothing is recomputed
@@ -1455,7 +1472,7 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
     rv.seg_row_major = 1;
     MSL_TRY(run_phase(k, rv));
     MSL_TRY(unpack_odd_range(k, 0, nodd, k.st));
-    return MSL_OK;
+    return end_flow(k, outs);
   }
   // Segment c-1 is recomputed from its checkpoint while the reverse sweep runs
   // over segment c: the two fields are independent, so on square grids they
@@ -1500,7 +1517,7 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
     MSL_TRY(unpack_odd_range(k, seg_odd_b(0), seg_odd_e(0), k.st));
     MSL_TRY(stream_after(k.st, kh.st, h->done));
   }
-  return MSL_OK;
+  return end_flow(k, outs);
 }
 
 size_t msl_batch_workspace_bytes(const msl_instance* inst, int32_t n) {

@@ -13,6 +13,17 @@ __global__ void __launch_bounds__(256) k_flow_init(float4* x, int64_t n4) {
     x[i] = make_float4(q, q, q, q);
 }
 
+// What a launch that gave up has poisoned by itself is only what depends on it: slices done before it and
+// lines done beside it would stay finite.  One launch per call, not per phase (1.5 us of a 64x64x128
+// forward's 273, 6 us of a 128x64x97 gradient's 680).
+__global__ void __launch_bounds__(256) k_flow_fold(const unsigned* err, FlowOuts o) {
+  if ((err[0] | err[1]) == 0u) return;
+  const float q = __builtin_nanf("");
+  for (int k = 0; k < 4; ++k)
+    if (o.p[k])
+      for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < o.n[k]; i += (int64_t)gridDim.x * 256) o.p[k][i] = q;
+}
+
 int log2_of(int n) { return __builtin_ctz((unsigned)n); }
 
 // Pauses (256 cycles each) before the first look at a pass's input: the more a pass exchanges, the
@@ -63,6 +74,11 @@ hipError_t launch_flow_init(float2* x, int64_t m, hipStream_t st) {
   const int64_t n4 = 4 * m / 2, nb = (n4 + 255) / 256;
   hipLaunchKernelGGL(k_flow_init, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(256), 0, st,
                      reinterpret_cast<float4*>(x), n4);
+  return hipGetLastError();
+}
+
+hipError_t launch_flow_fold(const unsigned* err, const FlowOuts& o, hipStream_t st) {
+  hipLaunchKernelGGL(k_flow_fold, dim3(128), dim3(256), 0, st, err, o);
   return hipGetLastError();
 }
 

@@ -55,8 +55,9 @@
 //
 // The wait is bounded as in the persistent schedule: after `spin_limit` polls
 // a wavefront raises the launch's error word and the workspace's status word
-// and stops waiting for good; the unset elements it read are NaN and reach
-// every element within two passes, so such a result cannot pass for valid.
+// and stops waiting for good.  The unset elements it read are NaN, but what was stored before
+// or does not depend on them is not, so the call ends with a kernel that fills its outputs
+// with NaN if an error word is raised (k_flow_fold): such a result cannot pass for valid.
 #pragma once
 
 #include "msl_flow_host.hpp"

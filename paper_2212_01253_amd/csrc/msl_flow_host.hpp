@@ -62,6 +62,14 @@ inline bool flow_takes(int kind, const PassDesc& pd) {
 bool flow_serves(int kind, int ny, int nz);
 // All elements of the exchange fields to kUnset.
 hipError_t launch_flow_init(float2* x, int64_t m, hipStream_t st);
+// The outputs of a call: n floats each, nullptr where there is none.
+struct FlowOuts {
+  float* p[4];
+  int64_t n[4];
+};
+// End of a call that ran dataflow launches: its outputs to NaN if one of them gave up (err: their two error
+// words).
+hipError_t launch_flow_fold(const unsigned* err, const FlowOuts& o, hipStream_t st);
 // The launch.
 hipError_t launch_flow(int kind, const Ctx& c, FlowArgs a, hipStream_t st);
 

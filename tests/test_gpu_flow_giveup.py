@@ -1,0 +1,66 @@
+"""A dataflow launch that gives up waiting (spin limit 0, set from the host: a wavefront that finds its
+input not yet there gives up at once, and every kernel still ends): no output of the call may pass
+for valid, also where it was complete before the wait or does not depend on it."""
+import math
+
+import pytest
+
+from paper_2212_01253_amd import synth
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def M():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2212_01253_amd import msl
+    msl.lib()
+    prev = msl.set_barrier_spin_limit(0)
+    yield msl
+    msl.set_barrier_spin_limit(prev)
+
+
+def case(exact, ny=256, nz=128, ns=40):
+    g = synth.Geometry(ny, nz, ns, 1.0, 1.0, 5.0, 0.1, math.radians(0.25), exact)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    d = 3e-5 * torch.rand((ns, ny, nz), device="cuda", generator=gen)
+    return g, d, d / 20
+
+
+def all_nan(*ts):
+    return all(bool(torch.isnan(torch.view_as_real(t) if t.is_complex() else t).all()) for t in ts)
+
+
+@pytest.mark.parametrize("exact", [0, 1])
+def test_forward_outputs(M, exact):
+    g, d, b = case(exact)
+    ws = M.workspace(g, 8)
+    f, ck = M.forward(g, d, b, ckpt_every=8, ws=ws)
+    with pytest.raises(M.MslError):
+        M.workspace_status(ws)
+    assert all_nan(f, ck)
+
+
+@pytest.mark.parametrize("k", [1, 8, 40])
+@pytest.mark.parametrize("exact", [0, 1])
+def test_gradients(M, exact, k):
+    g, d, b = case(exact)
+    ws = M.workspace(g, k)
+    zero = M.set_barrier_spin_limit(1 << 22)
+    f, ck = M.forward(g, d, b, ckpt_every=k, ws=ws)
+    M.workspace_status(ws)
+    M.set_barrier_spin_limit(zero)
+    out = M.adjoint(g, d, b, ck, k, f, ws=ws)
+    with pytest.raises(M.MslError):
+        M.workspace_status(ws)
+    assert all_nan(*out)
+    assert not all_nan(f) and not all_nan(ck)   # the inputs stay
+
+
+def test_noalloc_outputs(M):
+    g, d, b = case(0)
+    f, ck = M.forward_noalloc(g, d, b, ckpt_every=8)
+    assert all_nan(f, ck)
