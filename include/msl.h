@@ -150,11 +150,16 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
  * the caller.  MSL_SCHED_AUTO runs the middle passes of a paraxial call as one
  * dataflow launch where its exchange fields (4 ny nz complex64) fit the array
  * beside the tables, any other setting one launch per pass; a wait that ends
- * at the spin limit leaves NaN in field_out and ckpt. */
+ * at the spin limit leaves NaN in field_out and ckpt (msl_noalloc_status). */
 #define MSL_NOALLOC_SCRATCH_BYTES ((size_t)(4 * 64 * 1024 * 8 + 2 * 512 * 512 * 8))
 msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const float* beta,
                                const msl_c64* probe, msl_c64* field_out,
                                msl_c64* ckpt, int32_t ckpt_every, void* hip_stream);
+
+/* Outcome of the last msl_forward_noalloc call on the current GPU, as msl_workspace_status
+ * (below) reports that of a call on a workspace: waits for hip_stream, then returns
+ * MSL_OK, or MSL_ERR_HIP if a pass gave up waiting. */
+msl_status msl_noalloc_status(void* hip_stream);
 
 /* Far-field detector intensity of a field [Sec. 1; Fig. 1 caption]:
  * intensity[r][c] = |A|^2 / (ny nz) at fftshifted position (r, c), float32. */

@@ -577,16 +577,16 @@ struct Jobs {
   }
 };
 
-// Start of a call that runs passes: its tables, the probe (into probe_out, if given) and its workspace
-// status word (status: a workspace has one), msl_workspace_status, restarted at 0.
-msl_status start_call(const Call& k, bool need_prop, float2* probe_out, bool status) {
+// Start of a call that runs passes: its tables, the probe (into probe_out, if given) and its status word
+// (msl_workspace_status, msl_noalloc_status) restarted at 0.
+msl_status start_call(const Call& k, bool need_prop, float2* probe_out) {
   const msl_geometry& g = k.g;
   auto P = [&](size_t off) { return reinterpret_cast<float2*>(k.ws + off); };
   const bool par = need_prop && g.propagator == MSL_PROP_PARAXIAL;
   Jobs jobs;
   jobs.tables(g, P(k.L.twz), P(k.L.twy), par ? P(k.L.hz) : nullptr, par ? P(k.L.hy) : nullptr);
   if (probe_out) jobs.probe(g, probe_out);
-  MSL_TRY(jobs.run(status ? reinterpret_cast<unsigned*>(k.ws + k.L.bar) : nullptr, k.st));
+  MSL_TRY(jobs.run(reinterpret_cast<unsigned*>(k.ws + k.L.bar), k.st));
   if (need_prop && !par) {
     const int64_t m = (int64_t)g.ny * g.nz;
     hipLaunchKernelGGL(k_hexact, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, k.st, g.ny, g.nz, g.dy_nm, g.dz_nm,
@@ -1092,6 +1092,7 @@ Layout noalloc_layout(const msl_geometry& g) {
   Layout L{};
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += up(bytes); return r; };
+  L.bar = take(kAlign);  // first, at offset 0, as in a workspace: msl_noalloc_status knows no geometry
   L.twz = take((size_t)msl::DITHER * g.nz * 8);
   L.twy = take((size_t)msl::DITHER * g.ny * 8);
   L.hz = take((size_t)msl::DITHER * g.nz * 8);
@@ -1101,11 +1102,8 @@ Layout noalloc_layout(const msl_geometry& g) {
   L.H_hi = take(exact ? m * 8 : 0);
   L.H_lo = take(exact ? m * 8 : 0);
   L.total = o;
-  // the dataflow schedule's error words and exchange fields, where they fit (xf[0] stays 0 where not)
-  if (!exact && o + kAlign + up(4 * m * 8) <= kNoAllocBytes) {
-    L.bar = take(kAlign);
-    L.xf[0] = take(4 * m * 8);
-  }
+  // the dataflow schedule's exchange fields, where they fit (xf[0] stays 0 where not)
+  if (!exact && o + up(4 * m * 8) <= kNoAllocBytes) L.xf[0] = take(4 * m * 8);
   return L;
 }
 
@@ -1125,6 +1123,18 @@ msl_status noalloc_scratch(char*& out) {
     ptr[dev] = p;
   }
   out = static_cast<char*>(ptr[dev]);
+  return MSL_OK;
+}
+
+// Status word of the last call on a workspace or on the scratch array, both of which hold it at the
+// start, once the stream has run it.
+msl_status call_status(const void* base, hipStream_t st) {
+  MSL_TRY(hip_check(hipStreamSynchronize(st), "hipStreamSynchronize"));
+  unsigned w[2] = {0u, 0u};
+  MSL_TRY(hip_check(hipMemcpy(w, base, sizeof w, hipMemcpyDeviceToHost), "hipMemcpy"));
+  if (w[1] != 0u)
+    return fail(MSL_ERR_HIP, "a grid barrier or a dataflow pass gave up waiting (bounded spin) in the last "
+                             "call here; its results are not valid (they hold NaN)");
   return MSL_OK;
 }
 
@@ -1163,14 +1173,13 @@ msl_status msl_workspace_status(void* workspace, size_t ws_bytes, void* hip_stre
   if (!workspace) return fail(MSL_ERR_WORKSPACE, "workspace is NULL");
   if (!aligned(workspace, kAlign)) return fail(MSL_ERR_WORKSPACE, "workspace is not 256-byte aligned");
   if (ws_bytes < 8192) return fail(MSL_ERR_WORKSPACE, "workspace too small to hold a status word");
-  hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  MSL_TRY(hip_check(hipStreamSynchronize(st), "hipStreamSynchronize"));
-  unsigned w[2] = {0u, 0u};
-  MSL_TRY(hip_check(hipMemcpy(w, workspace, sizeof w, hipMemcpyDeviceToHost), "hipMemcpy"));
-  if (w[1] != 0u)
-    return fail(MSL_ERR_HIP, "a grid barrier or a dataflow pass gave up waiting (bounded spin) in the last "
-                             "call on this workspace; its results are not valid (they hold NaN)");
-  return MSL_OK;
+  return call_status(workspace, static_cast<hipStream_t>(hip_stream));
+}
+
+msl_status msl_noalloc_status(void* hip_stream) {
+  char* base = nullptr;
+  MSL_TRY(noalloc_scratch(base));
+  return call_status(base, static_cast<hipStream_t>(hip_stream));
 }
 
 msl_status msl_set_tuning(const msl_tuning* t) {
@@ -1279,7 +1288,7 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
   k.c.beta = beta;
   float2* f = reinterpret_cast<float2*>(field_out);
   const float2* in = probe ? reinterpret_cast<const float2*>(probe) : f;
-  MSL_TRY(start_call(k, true, probe ? nullptr : f, true));
+  MSL_TRY(start_call(k, true, probe ? nullptr : f));
   // the first pass reads the probe (row-major), the passes work on the tiled
   // working field, the last one writes the exit wave row-major
   PhaseSpec ph = blank_phase(k, msl::PH_FWD_FULL);
@@ -1324,7 +1333,7 @@ msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const 
   const float2* in = reinterpret_cast<const float2*>(probe);   // (the tilted probe is written in place)
   int rot[2] = {-1, -1};
   if (lay.xf[0]) k.flow_rot = rot;
-  MSL_TRY(start_call(k, true, probe ? nullptr : f, lay.xf[0] != 0));
+  MSL_TRY(start_call(k, true, probe ? nullptr : f));
   // No slice pack and no tiled working field (neither would fit a fixed
   // scratch): the passes work on the exit-wave array itself, row-major, and
   // the column passes evaluate the transmission of their slices from the
@@ -1350,7 +1359,7 @@ msl_status msl_far_field(const msl_geometry* g, const msl_c64* field, float* int
   MSL_TRY(check_ws(*g, 0, workspace, ws_bytes));
   Call k = make_call(*g, 0, workspace, static_cast<hipStream_t>(hip_stream));
   k.c.intensity = intensity;
-  MSL_TRY(start_call(k, false, nullptr, true));
+  MSL_TRY(start_call(k, false, nullptr));
   PhaseSpec ph = blank_phase(k, msl::PH_FF);
   ph.in_rm = reinterpret_cast<const float2*>(field);
   ph.field = reinterpret_cast<float2*>(k.ws + k.L.tmp);
@@ -1384,7 +1393,7 @@ msl_status msl_far_field_adjoint(const msl_geometry* g, const msl_c64* field, co
   MSL_TRY(check_ws(*g, 0, workspace, ws_bytes));
   Call k = make_call(*g, 0, workspace, static_cast<hipStream_t>(hip_stream));
   k.c.grad_intensity = grad_intensity;
-  MSL_TRY(start_call(k, false, nullptr, true));
+  MSL_TRY(start_call(k, false, nullptr));
   PhaseSpec ph = blank_phase(k, msl::PH_FFADJ);
   ph.in_rm = reinterpret_cast<const float2*>(field);
   ph.field = reinterpret_cast<float2*>(k.ws + k.L.tmp);
@@ -1416,7 +1425,7 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
   k.c.beta = beta;
   k.c.gdelta = grad_delta;
   k.c.gbeta = grad_beta;
-  MSL_TRY(start_call(k, true, nullptr, true));
+  MSL_TRY(start_call(k, true, nullptr));
   if (flags & MSL_REUSE_SLICE_PACK) {
     if (g->propagator == MSL_PROP_PARAXIAL) k.c.dbT = reinterpret_cast<const float2*>(k.ws + k.L.dbT);
   } else {

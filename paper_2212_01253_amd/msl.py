@@ -25,7 +25,8 @@ EXPORTS = ("msl_abi_version", "msl_workspace_bytes", "msl_checkpoint_count", "ms
            "msl_set_schedule", "msl_last_error", "msl_region_scatter", "msl_region_adam_step",
            "msl_batch_workspace_bytes", "msl_forward_batch", "msl_region_snap", "msl_rotate_object",
            "msl_region_shrinkwrap", "msl_set_tuning", "msl_get_tuning", "msl_autotune_forward",
-           "msl_autotune_batch", "msl_forward_noalloc", "msl_workspace_status", "msl_set_barrier_spin_limit")
+           "msl_autotune_batch", "msl_forward_noalloc", "msl_workspace_status", "msl_noalloc_status",
+           "msl_set_barrier_spin_limit")
 
 TUNE_SLOTS = 11  # MSL_TUNE_SLOTS
 
@@ -117,6 +118,8 @@ def lib():
     L.msl_set_schedule.argtypes = [c_int32]
     L.msl_workspace_status.restype = c_int32
     L.msl_workspace_status.argtypes = [P, c_size_t, P]
+    L.msl_noalloc_status.restype = c_int32
+    L.msl_noalloc_status.argtypes = [P]
     L.msl_set_barrier_spin_limit.restype = c_int32
     L.msl_set_barrier_spin_limit.argtypes = [c_int32]
     T = ctypes.POINTER(CTuning)
@@ -203,8 +206,13 @@ def set_schedule(mode: int) -> int:
 
 def workspace_status(ws):
     """msl_workspace_status: raises MslError if the last phase-running call on ``ws`` is invalid
-    (a persistent-schedule barrier gave up); waits for the current stream."""
+    (a grid barrier or a pass of the one-launch schedule gave up); waits for the current stream."""
     _check(lib().msl_workspace_status(ws.data_ptr(), ws.numel(), _stream()))
+
+
+def noalloc_status():
+    """msl_noalloc_status: ``workspace_status`` of the last ``forward_noalloc`` call on the current GPU."""
+    _check(lib().msl_noalloc_status(_stream()))
 
 
 def set_barrier_spin_limit(polls: int) -> int:
@@ -329,7 +337,8 @@ def forward(g, delta, beta, probe=None, ckpt_every=0, ws=None, out=None, ckpt=No
 
 def forward_noalloc(g, delta, beta, probe=None, ckpt_every=0, out=None, ckpt=None):
     """msl_forward_noalloc: as ``forward`` without a workspace (the library's fixed
-    per-GPU scratch holds its tables); returns (psi_Ns, checkpoints or None)."""
+    per-GPU scratch holds its tables; ``noalloc_status`` says whether its outputs are valid);
+    returns (psi_Ns, checkpoints or None)."""
     cg = geometry(g)
     ny, nz, ns = cg.ny, cg.nz, cg.n_slices
     dev = delta.device

@@ -64,3 +64,16 @@ def test_noalloc_outputs(M):
     g, d, b = case(0)
     f, ck = M.forward_noalloc(g, d, b, ckpt_every=8)
     assert all_nan(f, ck)
+
+
+def test_noalloc_status(M):
+    g, d, b = case(0)
+    M.forward_noalloc(g, d, b)
+    with pytest.raises(M.MslError) as e:
+        M.noalloc_status()
+    assert e.value.status == M.ERR_HIP
+    zero = M.set_barrier_spin_limit(1 << 22)
+    for ny, nz, exact in ((256, 128, 0), (1024, 1024, 0), (512, 512, 1)):   # with a dataflow launch and without
+        M.forward_noalloc(*case(exact, ny, nz, 6))
+        M.noalloc_status()
+    M.set_barrier_spin_limit(zero)
