@@ -349,6 +349,7 @@ def main():
         step(evs[i])
     t_end.record()
     torch.cuda.synchronize()
+    msl.workspace_status(ws)   # (a step that gave up waiting is no measurement)
     total_ms = t_start.elapsed_time(t_end)
     ms = total_ms / args.steps
     pack_ms = [e[0].elapsed_time(e[1]) for e in evs]
@@ -428,6 +429,7 @@ def main():
             step1()
         t_end.record()
         torch.cuda.synchronize()
+        msl.workspace_status(ws1)
         ms1 = t_start.elapsed_time(t_end) / args.steps
         out["every_slice_checkpointed"] = {"ckpt_every": 1, "ms_per_step": ms1, "value": vs / (ms1 / 1e3),
                                            "checkpoint_bytes": ck1.numel() * 8}

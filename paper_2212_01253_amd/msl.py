@@ -435,7 +435,10 @@ def adjoint(g, delta, beta, ckpt, ckpt_every, grad_field, probe=None, ws=None,
 # autograd wrappers
 
 class Multislice(torch.autograd.Function):
-    """psi_Ns = Multislice.apply(delta, beta, geom, probe=None, ckpt_every=32)."""
+    """psi_Ns = Multislice.apply(delta, beta, geom, probe=None, ckpt_every=32).
+
+    Asynchronous, so it does not ask whether a pass gave up waiting (``workspace_status``): every
+    element of the exit wave or of the gradients is NaN then."""
 
     @staticmethod
     def forward(ctx, delta, beta, geom, probe=None, ckpt_every=32):

@@ -89,6 +89,11 @@ class Reconstructor:
         self.meas = torch.as_tensor(amp).to(dev)
         self.probe = None if probe is None else torch.as_tensor(np.asarray(probe, np.complex64)).to(dev)
         self.ws = msl.workspace(self.g, self.k, dev)
+        # the far field and its adjoint work on a workspace of their own (their results do not depend on
+        # the slices), so that self.ws keeps the outcome of the last sweep for check()
+        self.g_far = msl.CGeometry.from_buffer_copy(self.g)
+        self.g_far.n_slices = 1
+        self.ws_far = msl.workspace(self.g_far, 0, dev)
         self.field = torch.empty((ny, nz), dtype=torch.complex64, device=dev)
         self.ck = torch.empty((msl.checkpoint_count(self.g, self.k), ny, nz), dtype=torch.complex64, device=dev)
         self.I = torch.empty((ny, nz), dtype=torch.float32, device=dev)
@@ -118,11 +123,11 @@ class Reconstructor:
         msl.pack_slices(self.g, self.D, self.B, self.ws)
         msl.forward(self.g, self.D, self.B, self.probe, self.k, ws=self.ws, out=self.field, ckpt=self.ck,
                     reuse_pack=True)
-        msl.far_field(self.g, self.field, ws=self.ws, out=self.I)
-        msl.amp_loss(self.g, self.I, self.meas, ws=self.ws, loss=self._loss, gI=self._gI)
+        msl.far_field(self.g_far, self.field, ws=self.ws_far, out=self.I)
+        msl.amp_loss(self.g_far, self.I, self.meas, ws=self.ws_far, loss=self._loss, gI=self._gI)
 
     def _adjoint_calls(self):
-        msl.far_field_adjoint(self.g, self.field, self._gI, ws=self.ws, out=self.gpsi)
+        msl.far_field_adjoint(self.g_far, self.field, self._gI, ws=self.ws_far, out=self.gpsi)
         msl.adjoint(self.g, self.D, self.B, self.ck, self.k, self.gpsi, probe=self.probe, ws=self.ws,
                     gd=self.gd, gb=self.gb, want_probe=False, reuse_pack=True)
 
@@ -155,9 +160,24 @@ class Reconstructor:
         self._run("loss")
         return self._loss
 
+    def check(self):
+        """Raises msl.MslError if the sweep of the last ``loss()``, ``gradient_step()`` or
+        ``stack_gradients()`` gave up waiting (its results are then NaN); waits for it."""
+        msl.workspace_status(self.ws)
+
+    def loss_value(self):
+        """The detector loss of the current theta as a number; raises as ``check()`` does."""
+        value = float(self.loss().item()) * self.scale
+        if math.isnan(value):   # every element of a forward that gave up is NaN, so no other value needs the question
+            self.check()
+        return value
+
     def gradient_step(self):
         """Adjoint of the last ``loss()`` and one ADAM step on theta."""
         self._run("adjoint")
+        self._adam_step()
+
+    def _adam_step(self):
         self.t += 1
         msl.region_adam_step(self.g, self.r, self.adam.c(), self.t, self.gd, self.gb, self.theta, self.m,
                              self.v, self.D, self.B, grad_scale=self.scale)
@@ -185,14 +205,15 @@ class Reconstructor:
         nearest-index filter (the paper applies it after 20 epochs); with wrap_every, every
         wrap_every-th step by the shrink-wrap support (the paper: every 20 epochs).  With
         stall_window, the run also stops (result.stalled) once stall_window iterations pass
-        without the loss falling by a fraction stall_gain below its last such improvement."""
+        without the loss falling by a fraction stall_gain below its last such improvement.
+        A sweep that gave up waiting raises msl.MslError (``check``) before theta takes a step from it."""
         res = ReconResult(threshold=threshold)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         self.set_theta(theta0)
         watch = StallWatch(stall_window, stall_gain)
         for it in range(max_iters + 1):
-            L = float(self.loss().item()) * self.scale
+            L = self.loss_value()
             now = time.perf_counter() - t0
             res.losses.append(L)
             res.times.append(now)
@@ -207,7 +228,9 @@ class Reconstructor:
             if watch.stalled(it, L):
                 res.stalled = True
                 break
-            self.gradient_step()
+            self._run("adjoint")
+            self.check()
+            self._adam_step()
             if snap_levels is not None and snap_every and self.t % snap_every == 0:
                 self.snap(snap_levels)
             if wrap_every and self.t % wrap_every == 0:
@@ -237,9 +260,11 @@ def make_problem(seed_gt=4242, seed_noise=4243, n=256, n_slices=1024, photons=1e
     kd, kb = synth.known_stack(w, region)
     D = torch.from_numpy(w.delta).cuda()
     B = torch.from_numpy(w.beta).cuda()
-    f, _ = msl.forward(g, D, B)
-    I = msl.far_field(g, f).cpu().numpy()
-    del D, B
+    ws = msl.workspace(g)
+    f, _ = msl.forward(g, D, B, ws=ws)
+    msl.workspace_status(ws)
+    I = msl.far_field(g, f, ws=ws).cpu().numpy()
+    del D, B, ws
     counts, s = synth.poisson_counts(I, photons, seed_noise)
     return Problem(g, region, kd, kb, counts, s, synth.box_values(w, region))
 
@@ -250,7 +275,7 @@ def seconds_to_threshold(p: Problem, init, factor=1.10, max_iters=5000, adam: Ad
     R = Reconstructor(p.geom, p.known_delta, p.known_beta, p.region, p.counts, p.scale, ckpt_every=ckpt_every,
                       adam=adam, graphs=graphs)
     R.set_theta(p.truth)
-    L_truth = float(R.loss().item()) * p.scale
+    L_truth = R.loss_value()
     R.stack_gradients()   # the adjoint graph is captured here, before the clock starts
     res = R.run(init, max_iters, factor * L_truth, log_every=log_every)
     return L_truth, res
@@ -318,7 +343,7 @@ def seconds_to_threshold_learned(p: Problem, net, plain_init, factor=1.10, max_i
     R = Reconstructor(p.geom, p.known_delta, p.known_beta, p.region, p.counts, p.scale, ckpt_every=ckpt_every,
                       adam=adam, graphs=graphs)
     R.set_theta(p.truth)
-    L_truth = float(R.loss().item()) * p.scale
+    L_truth = R.loss_value()
     R.stack_gradients()   # the adjoint graph is captured here, before the clock starts
     threshold = factor * L_truth
     base_adam = R.adam
@@ -326,9 +351,9 @@ def seconds_to_threshold_learned(p: Problem, net, plain_init, factor=1.10, max_i
     t0 = time.perf_counter()
     guess = learned_initial_guess(net, p, companions, batch)
     R.set_theta(guess)
-    L_learned = float(R.loss().item()) * p.scale
+    L_learned = R.loss_value()
     R.set_theta(plain_init)
-    L_plain = float(R.loss().item()) * p.scale
+    L_plain = R.loss_value()
     chose = bool(np.isfinite(L_learned) and L_learned < L_plain)
     t_judge = time.perf_counter() - t0
     out = ReconResult(threshold=threshold)

@@ -77,3 +77,39 @@ def test_noalloc_status(M):
         M.forward_noalloc(*case(exact, ny, nz, 6))
         M.noalloc_status()
     M.set_barrier_spin_limit(zero)
+
+
+@pytest.mark.parametrize("graphs", [False, True])
+@pytest.mark.parametrize("where", ["forward", "adjoint"])
+def test_reconstruction_raises_and_keeps_theta(M, where, graphs):
+    # a sweep that gives up is reported where the driver waits for the GPU, and its gradients never
+    # reach theta; with the limit restored the same driver goes on
+    import numpy as np
+    from paper_2212_01253_amd import recon
+    region = {"s0": 0, "ns": 40, "y0": 16, "ny": 16, "z0": 0, "nz": 64, "beta_over_delta": 0.05}
+    g, d, b = case(0, 64, 64)
+    zero = M.set_barrier_spin_limit(1 << 22)
+    R = recon.Reconstructor(g, d.cpu().numpy(), b.cpu().numpy(), region, np.full((64, 64), 10.0), 1.0, ckpt_every=8,
+                            graphs=graphs)
+    theta = np.full((40, 16, 64), 1e-5, np.float32)
+    full = R.run(theta, 3).losses
+    R.set_theta(theta)
+    step = R._run
+
+    def failing(which):
+        # captured launches keep the limit they were captured with: the call that fails is run eagerly
+        if which == ("loss" if where == "forward" else "adjoint") and R.t >= 1:
+            M.set_barrier_spin_limit(0)
+            (R._loss_calls if which == "loss" else R._adjoint_calls)()
+            M.set_barrier_spin_limit(1 << 22)
+        else:
+            step(which)
+
+    R._run = failing
+    with pytest.raises(M.MslError) as e:
+        R.run(theta, 3)
+    assert e.value.status == M.ERR_HIP and R.t == 1
+    assert bool(torch.isfinite(R.theta).all()) and bool(torch.isfinite(R.m).all())
+    R._run = step
+    assert R.run(theta, 3).losses == full
+    M.set_barrier_spin_limit(zero)
