@@ -86,8 +86,14 @@ typedef enum {
   MSL_SCHED_AUTO = 0,        /* library choice: one launch for the middle passes of a phase, the field
                                 handed over through memory element by element, where that serves
                                 (grids up to 512 x 512 in either propagator, the default launch shape,
-                                a stream without a compute-unit mask); else one launch per line pass.  The
-                                results are bit for bit those of MSL_SCHED_PER_PASS. */
+                                a stream of default priority without a compute-unit mask); else one launch
+                                per line pass.  The results are bit for bit those of MSL_SCHED_PER_PASS.
+                                Such a launch needs all its workgroups on the GPU at once.  As many
+                                calls as this process has hardware queues have room together, but launches
+                                of other processes, or of MSL_SCHED_PERSISTENT, on the same GPU are not
+                                counted: calls that share it with them may each hold a part of it until their
+                                waits end at the spin limit (msl_workspace_status).  Processes that share
+                                a GPU set MSL_SCHED_PER_PASS, which waits for nothing. */
   MSL_SCHED_PER_PASS = 1,    /* one kernel launch per line pass */
   MSL_SCHED_PERSISTENT = 2   /* one cooperative launch per phase, grid barriers between passes
                                 (square grids, ny == nz; other shapes run per pass) */

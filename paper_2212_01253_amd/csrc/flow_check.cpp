@@ -1,4 +1,4 @@
-// Host-only check of the dataflow schedule's ordering (msl_flow.hpp).
+// Host-only check of the dataflow schedule's ordering (msl_flow.hpp) and of its rule of residency (flow_admits).
 //
 // Follows the wavefronts of a launch through its passes, on every grid the schedule serves, and keeps
 // for each the set of events that are ordered before its current point: by its own
@@ -118,6 +118,35 @@ struct Model {
   }
 };
 
+// Launches that the rule admits, dealt to compute units in the worst way: workgroups of the given
+// shares of a compute unit, each to the fullest one that would still take the smallest, until none takes the next.
+// Returns whether all of `queues` launches of every mix of two kinds found room.
+bool all_fit(int queues, int cus, int per_a, int grid_a, int per_b, int grid_b) {
+  if (!msl::flow_admits(queues, cus, per_a, grid_a) || !msl::flow_admits(queues, cus, per_b, grid_b)) return true;
+  const int unit = per_a * per_b;   // a compute unit's resource; a workgroup of a takes per_b of it, of b per_a
+  for (int na = 0; na <= queues; ++na) {
+    int left[2] = {na * grid_a, (queues - na) * grid_b};
+    const int share[2] = {per_b, per_a};
+    std::vector<int> used(cus, 0);
+    for (int c = 0; c < cus; ++c)   // as many units as possible spoiled with a remainder too small for the larger
+      for (int k : {share[0] < share[1] ? 0 : 1, share[0] < share[1] ? 1 : 0}) {
+        const int big = share[0] > share[1] ? share[0] : share[1];
+        while (left[k] > 0 && used[c] + share[k] <= unit && unit - used[c] >= big) {
+          used[c] += share[k];
+          --left[k];
+        }
+      }
+    for (int k = 0; k < 2; ++k)
+      for (int c = 0; c < cus; ++c)
+        while (left[k] > 0 && used[c] + share[k] <= unit) {
+          used[c] += share[k];
+          --left[k];
+        }
+    if (left[0] + left[1] > 0) return false;
+  }
+  return true;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -132,6 +161,17 @@ int main(int argc, char** argv) {
         ++unsafe;
       }
     }
+  for (int queues : {4, 5, 8, 12, 16, 24, 32})
+    for (int cus : {32, 64, 128, 256})
+      for (int pa = 4; pa <= 16; ++pa)
+        for (int pb = pa; pb <= 16; ++pb)
+          for (int ga = 16; ga <= 256; ga *= 2)
+            for (int gb = 16; gb <= 256; gb *= 2)
+              if (!all_fit(queues, cus, pa, ga, pb, gb)) {
+                std::printf("%d queues, %d compute units: %d workgroups at %d and %d at %d do not fit\n", queues, cus, ga, pa,
+                            gb, pb);
+                ++unsafe;
+              }
   if (unsafe) return 1;
   std::printf("OK\n");
   return 0;

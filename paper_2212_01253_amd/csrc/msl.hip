@@ -515,6 +515,7 @@ struct Call {
   char* ws;
   hipStream_t st;
   int* flow_rot;  // per exchange set, where its rotation stands (FlowArgs::rot), -1: not filled yet; or nullptr
+  bool whole;     // whole_device(st), asked once a call
 };
 
 Call make_call(const msl_geometry& g, const Layout& lay, void* ws, hipStream_t st) {
@@ -648,8 +649,14 @@ bool use_persistent(const Call& k, int np) {
          (g_schedule == MSL_SCHED_AUTO && msl::persistent_preferred(k.c, np));
 }
 
-// Whether kernels of the stream may run on every compute unit (hipExtStreamCreateWithCUMask).
+// Whether kernels of the stream may run on every compute unit (hipExtStreamCreateWithCUMask) and the
+// stream is of the default priority (streams of another one have hardware queues of their own).
 bool whole_device(hipStream_t st) {
+  int prio = 0;
+  if (hipStreamGetPriority(st, &prio) != hipSuccess || prio != 0) {
+    (void)hipGetLastError();
+    return false;
+  }
   int dev = 0, cus = 0;
   uint32_t mask[32] = {};
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -665,7 +672,7 @@ bool whole_device(hipStream_t st) {
 
 // The dataflow kind (msl::FlowKind) that takes the middle passes of phase a, or -1: the default schedule at
 // the default launch shape (a set one asks for the per-pass kernels it describes), exchange fields in the
-// call's scratch, a grid it serves, and a stream that may use every compute unit.
+// call's scratch, a grid it serves, and a stream of the default priority that may use every compute unit.
 int flow_kind(const Call& k, const PhaseSpec& a) {
   if (!k.flow_rot || g_schedule != MSL_SCHED_AUTO) return -1;
   int kind = -1;
@@ -678,7 +685,7 @@ int flow_kind(const Call& k, const PhaseSpec& a) {
     const int e = __builtin_ctz((unsigned)n);
     if (n > 512 || g_lines_per_group[e] > 0 || g_points_per_lane[e] > 0) return -1;
   }
-  return msl::flow_serves(kind, k.c.ny, k.c.nz) && whole_device(k.st) ? kind : -1;
+  return k.whole && msl::flow_serves(kind, k.c.ny, k.c.nz) ? kind : -1;
 }
 
 // Passes p0 .. p0 + n - 1 of phase a, all of its middle kind, as one dataflow launch.
@@ -1284,6 +1291,7 @@ msl_status msl_forward(const msl_geometry* g, const float* delta, const float* b
   Call k = make_call(*g, 0, workspace, static_cast<hipStream_t>(hip_stream));
   int rot[2] = {-1, -1};
   k.flow_rot = rot;
+  k.whole = whole_device(k.st);
   k.c.delta = delta;
   k.c.beta = beta;
   float2* f = reinterpret_cast<float2*>(field_out);
@@ -1333,6 +1341,7 @@ msl_status msl_forward_noalloc(const msl_geometry* g, const float* delta, const 
   const float2* in = reinterpret_cast<const float2*>(probe);   // (the tilted probe is written in place)
   int rot[2] = {-1, -1};
   if (lay.xf[0]) k.flow_rot = rot;
+  k.whole = whole_device(k.st);
   MSL_TRY(start_call(k, true, probe ? nullptr : f));
   // No slice pack and no tiled working field (neither would fit a fixed
   // scratch): the passes work on the exit-wave array itself, row-major, and
@@ -1421,6 +1430,7 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
   Call k = make_call(*g, ckpt_every, workspace, static_cast<hipStream_t>(hip_stream));
   int rot[2] = {-1, -1};
   k.flow_rot = rot;
+  k.whole = whole_device(k.st);
   k.c.delta = delta;
   k.c.beta = beta;
   k.c.gdelta = grad_delta;
@@ -1513,6 +1523,7 @@ msl_status msl_adjoint(const msl_geometry* g, const float* delta, const float* b
     std::lock_guard<std::mutex> lock(h->mu);
     Call kh = k;
     kh.st = h->s;
+    kh.whole = true;   // (the library's own stream)
     for (int c = nck - 1; c >= 0; --c) {
       if (c < nck - 1) MSL_TRY(hip_check(hipStreamWaitEvent(k.st, h->join, 0), "hipStreamWaitEvent"));
       MSL_TRY(stream_after(kh.st, k.st, h->fork));

@@ -34,10 +34,8 @@ int flow_nap(int64_t m) { return m <= 8192 ? 0 : (m <= 32768 ? 1 : (m <= 131072 
 
 }  // namespace
 
-// Every workgroup of a launch has to be resident for its passes to end.  Kernels of other kinds end by
-// themselves and only delay that; launches of this schedule on other streams wait like this one, so
-// as many as there are hardware queues (each runs one kernel at a time: GPU_MAX_HW_QUEUES, 4 unless set)
-// must fit on the device at once.
+// (flow_admits)  Streams of one priority share GPU_MAX_HW_QUEUES hardware queues (4 unless set), each of which
+// runs one kernel at a time; flow_kind sees to the priority.  Other processes' launches are not seen.
 bool flow_serves(int kind, int ny, int nz) {
   struct Fits {
     signed char known[FLOW_KINDS][11][11];   // 0: not asked yet, 1: fits, -1: does not
@@ -63,7 +61,7 @@ bool flow_serves(int kind, int ny, int nz) {
     }
     const bool ok = e == hipSuccess &&
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                    (int64_t)queues * grid <= (int64_t)cus * per_cu;
+                    flow_admits(queues, cus, per_cu, grid);
     if (!ok) (void)hipGetLastError();
     k = ok ? 1 : -1;
   }

@@ -39,6 +39,18 @@ constexpr int flow_col_units(int nz, int ny) { return nz / flow_lines(nz, ny, ny
 // some sit out every second pass.
 constexpr bool flow_resets_early(int nz, int ny) { return flow_row_units(nz, ny) != flow_col_units(nz, ny); }
 
+// Whether launches of `grid` workgroups, `per_cu` of which one compute unit holds, may run on a
+// device of `cus` compute units.  Every workgroup of a launch has to be resident for its passes to end.
+// Kernels of other kinds end by themselves and only delay that; launches of this schedule on other
+// streams wait like this one, and they may be of any kind and grid (an adjoint runs two kinds side by
+// side), so what has to fit is any mix of as many as there are hardware queues.  A compute unit holds any
+// kFlowPerCu workgroups together, since it holds that many of each (none takes more than
+// 1 / kFlowPerCu of a resource: two wavefronts per SIMD by the launch bounds, 16 KiB of LDS).
+constexpr int kFlowPerCu = 4;
+constexpr bool flow_admits(int queues, int cus, int per_cu, int grid) {
+  return per_cu >= kFlowPerCu && (int64_t)queues * grid <= (int64_t)cus * kFlowPerCu;
+}
+
 constexpr int kFlowMinPasses = 4;   // a launch of fewer passes is not worth its two ends
 
 // What the passes of a launch are: the paraxial middle passes of the forward sweep and the recompute with
