@@ -85,7 +85,7 @@ typedef enum { MSL_PROP_PARAXIAL = 0, MSL_PROP_EXACT = 1 } msl_propagator;
 typedef enum {
   MSL_SCHED_AUTO = 0,        /* library choice: one launch for the middle passes of a phase, the field
                                 handed over through memory element by element, where that serves
-                                (grids up to 512 x 512 in either propagator, the default launch shape,
+                                (grids up to 512 x 512 in either propagator, the default points per lane,
                                 a stream of default priority without a compute-unit mask); else one launch
                                 per line pass.  The results are bit for bit those of MSL_SCHED_PER_PASS.
                                 Such a launch needs all its workgroups on the GPU at once.  As many
@@ -260,7 +260,8 @@ int32_t msl_set_barrier_spin_limit(int32_t polls);
  * 2^e = 64: 32, 128: 16, 256: 8, 512: 4, 1024: 2; at 4 points per lane
  * 2^e = 16: 64, 32: 32, 64: 16, 128: 8, 256: 4, 512: 2, 1024: 1.
  * The lines per workgroup only deal lines to the hardware: at one P every
- * allowed value gives bit-identical results.
+ * allowed value gives bit-identical results.  The one-launch schedule (MSL_SCHED_AUTO) has its own,
+ * so they then concern the passes around it.
  * batch_streams: how many grid-size groups msl_forward_batch runs side by side
  * (1..4; 0 = 4).  The setting is process-wide, applies to later calls, and is
  * not synchronised with calls running on other threads. */

@@ -670,9 +670,10 @@ bool whole_device(hipStream_t st) {
   return n >= cus;
 }
 
-// The dataflow kind (msl::FlowKind) that takes the middle passes of phase a, or -1: the default schedule at
-// the default launch shape (a set one asks for the per-pass kernels it describes), exchange fields in the
-// call's scratch, a grid it serves, and a stream of the default priority that may use every compute unit.
+// The dataflow kind (msl::FlowKind) that takes the middle passes of phase a, or -1: the default schedule,
+// at the points per lane of its kernels (others give other bits; the lines per workgroup that are set only
+// deal lines of the per-pass kernels), exchange fields in the call's scratch, a grid it serves, and a
+// stream of the default priority that may use every compute unit.
 int flow_kind(const Call& k, const PhaseSpec& a) {
   if (!k.flow_rot || g_schedule != MSL_SCHED_AUTO) return -1;
   int kind = -1;
@@ -682,8 +683,7 @@ int flow_kind(const Call& k, const PhaseSpec& a) {
     kind = a.exact ? msl::FLOW_XREV : (k.c.dbT ? msl::FLOW_REV : -1);
   if (kind < 0 || (a.rowmajor != 0) != (kind == msl::FLOW_STACK)) return -1;
   for (const int n : {k.c.ny, k.c.nz}) {
-    const int e = __builtin_ctz((unsigned)n);
-    if (n > 512 || g_lines_per_group[e] > 0 || g_points_per_lane[e] > 0) return -1;
+    if (n > 512 || points_per_lane(n) != msl::flow_pts(n)) return -1;
   }
   return k.whole && msl::flow_serves(kind, k.c.ny, k.c.nz) ? kind : -1;
 }

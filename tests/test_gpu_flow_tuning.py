@@ -1,0 +1,51 @@
+"""Which launch shapes leave the dataflow schedule in place: any number of lines per workgroup (it has its
+own), and the points per lane its kernels have, set or default; other points per lane run per pass.
+Whether a call made a dataflow launch shows at spin limit 0 (set from the host: its waits give up at
+once, every kernel ends), where only such a launch can fail.  Results are compared bit for bit."""
+import math
+
+import pytest
+
+from paper_2212_01253_amd import synth
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def M():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2212_01253_amd import msl
+    msl.lib()
+    before = msl.get_tuning()
+    yield msl
+    msl.set_schedule(0)
+    msl.restore_tuning(before)
+
+
+@pytest.mark.parametrize("lines,points,flow", [
+    ({}, {}, True), ({256: 1, 128: 4}, {}, True), ({256: 4}, {256: 4, 128: 4}, True), ({}, {256: 4}, True),
+    ({}, {256: 8}, False), ({128: 2}, {128: 8}, False), ({512: 2, 64: 16}, {512: 4}, True)])
+def test_shapes(M, lines, points, flow):
+    g = synth.Geometry(256, 128, 40, 1.0, 1.0, 5.0, 0.1, math.radians(0.25), 0)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    d = 3e-5 * torch.rand((40, 256, 128), device="cuda", generator=gen)
+    M.set_tuning(lines, points_per_lane=points)
+    ws = M.workspace(g, 0)
+    M.set_schedule(1)
+    ref, _ = M.forward(g, d, d / 20, ws=ws)
+    M.set_schedule(0)
+    f, _ = M.forward(g, d, d / 20, ws=ws)
+    assert torch.equal(f, ref)
+    prev = M.set_barrier_spin_limit(0)
+    try:
+        M.forward(g, d, d / 20, ws=ws)
+        if flow:
+            with pytest.raises(M.MslError):
+                M.workspace_status(ws)
+        else:
+            M.workspace_status(ws)
+    finally:
+        M.set_barrier_spin_limit(prev)
