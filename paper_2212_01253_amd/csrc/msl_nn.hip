@@ -876,24 +876,29 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
 // product's depth, both operands lie in memory as the MFMA wants them: a lane's eight depth
 // values are eight neighbouring pixels of one channel, one 16-byte read.  A wavefront owns 32
 // input x 32 output channels and all nine taps (144 accumulators) and walks down the rows of a strip
-// of 32 pixels: per row of the input it forms the three column shifts in registers
-// (v_alignbit with the pixels left and right of the eight) and multiplies each with the output
-// gradients of the three rows that meet it, which it keeps from row to row; nothing passes through
+// of 32 pixels: per row of the gradient it multiplies with the three input rows that meet it, which it
+// keeps from row to row, under the three column shifts, formed in registers (v_alignbit with
+// the pixels left and right of the eight); nothing passes through
 // LDS, and the reads of a row are in flight while the row before is multiplied.  The four
 // wavefronts of a workgroup take different strips and row ranges (units) of the same channels and
 // add their sums in LDS at the end, so a workgroup writes one part.
 //
+// A tap's sum takes every input value it meets and no other: an input value never meets a zero that stands for a
+// gradient row or column that is not there (another unit's, beyond the row's end), since an infinity
+// or a NaN would turn that tap's sum into NaN.
+//
 // Bound by the planes' scattered 64-byte pieces (32 to 64 planes per wavefront), not by latency: one
 // wavefront per SIMD with seven rows in flight measured the same (96 -> 32 channels at 32x256x256 372 us)
-// or slower (384 -> 128 at 32x64x64 387 against 263).  Against the halo kernel: 32 -> 32 channels at
-// 32x256x256 240 -> 121 us, 96 -> 32 580 -> 394, 64 -> 64 at 32x128x128 209 -> 78, 384 -> 128 at 32x64x64
-// 470 -> 281, 256 -> 256 at 32x32x32 203 -> 78; against the patch-column product that served widths
-// not a multiple of 8: 150 -> 12 channels at 8x200x66 294 -> 56 us.
+// or slower (384 -> 128 at 32x64x64 387 against 263).  Walking down the input's rows and keeping the
+// gradient's instead (two half-used rows more per unit): 32 -> 32 channels at 32x256x256 117 us against 106 so,
+// 96 -> 32 396 and 367, 64 -> 64 at 32x128x128 79 and 70, 384 -> 128 at 32x64x64 279 and 268, 256 -> 256 at
+// 32x32x32 81 and 71 (bfloat16 input; halo kernel: 240, 580, 209, 470, 203); widths not a multiple of 8,
+// 150 -> 12 channels at 8x200x66, 59 us (patch-column product: 294).
 //
 // Stride 2: a strip is 32 pixels of the gradient over 64 of the input, whose even and odd columns are
 // parted in registers (the middle tap takes the even ones, the right tap the odd ones, the left tap the
 // odd ones shifted by one); an even input row meets one gradient row, an odd one two (32 -> 64 channels
-// at 32x256x256 162 -> 89 us, 128 -> 256 at 32x64x64 159 -> 59).
+// at 32x256x256 162 -> 90 us, 128 -> 256 at 32x64x64 159 -> 63).
 //
 // Parts are [tap][o][c]; k_sum_wgrad adds them.  The rows of a unit cost two more input rows at its
 // ends, so units are tall where there are enough of them.
@@ -936,7 +941,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
 #pragma unroll
   for (int t = 0; t < 9; ++t) acc[t] = f32x16{};
   const int u1 = min(a.units, (part + 1) * a.per_part);
-  for (int u = part * a.per_part + wave; u < u1; u += 4) {
+  for (int u = part * a.per_part + __builtin_amdgcn_readfirstlane(wave); u < u1; u += 4) {
     int t = u;
     const int sx = t % a.strips;
     t /= a.strips;
@@ -953,8 +958,20 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
       u32x4 v[2 * S];
       uint32_t edge;
     };
-    XRow xr[2];
-    u32x4 dr[4][2];
+    XRow xr[S == 1 ? 4 : 2];
+    u32x4 dr[S == 1 ? 2 : 4][2];
+    // v, the pixels left of chunk k's gradient columns, zero where there is no such column (right of the last
+    // one it would be the row's last pixel)
+    auto left_of_row = [&](u32x4 v, int k) {
+      const int n = a.Wo - (px + 8 * k);   // gradient columns of the chunk that are there
+      if constexpr (RD == ROW_VEC) {
+        if (n <= 0) v.x &= 0xffff0000u;    // (the chunk is whole or outside, and only its first pixel is a row's)
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] &= n <= 2 * i ? 0u : (n == 2 * i + 1 ? 0x0000ffffu : 0xffffffffu);
+      }
+      return v;
+    };
     auto load_x = [&](int y, XRow& q) {
       const bool in = c_ok && y >= 0 && y < a.H;
       const uint32_t row = (uint32_t)(y - (S * y0 - 1)) * (uint32_t)a.W * ES;
@@ -982,8 +999,8 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
       }
     };
     if constexpr (S == 1) {
-      // row y of the input meets gradient rows y + 1, y, y - 1 (taps ky = 0, 1, 2)
-      auto products = [&](const XRow& q, const u32x4 (&up)[2], const u32x4 (&mid)[2], const u32x4 (&down)[2]) {
+      // gradient row d meets input row q under kernel row ky
+      auto products = [&](int ky, const XRow& q, const u32x4 (&d)[2]) {
         // lower half of the lanes: left neighbour the edge, right one the upper half's first pixels; upper
         // half: left the lower half's last pixels, right the edge
         const uint32_t left = __builtin_amdgcn_permlane32_swap(q.edge, q.v[1].w, false, false)[0];
@@ -994,37 +1011,35 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
           const uint32_t l = k ? q.v[0].w : left, r = k ? right : q.v[1].x;
           const uint32_t m0 = __builtin_amdgcn_alignbit(v.y, v.x, 16), m1 = __builtin_amdgcn_alignbit(v.z, v.y, 16),
                          m2 = __builtin_amdgcn_alignbit(v.w, v.z, 16);
-          const u32x4 lo = {__builtin_amdgcn_alignbit(v.x, l, 16), m0, m1, m2};
+          const u32x4 lo = left_of_row(u32x4{__builtin_amdgcn_alignbit(v.x, l, 16), m0, m1, m2}, k);
           const u32x4 hi = {m0, m1, m2, __builtin_amdgcn_alignbit(r, v.w, 16)};
           const bf16x8 xs[3] = {__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, hi)};
-          const bf16x8 d[3] = {__builtin_bit_cast(bf16x8, up[k]), __builtin_bit_cast(bf16x8, mid[k]),
-                               __builtin_bit_cast(bf16x8, down[k])};
 #pragma unroll
-          for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx)
-              acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[ky], xs[kx], acc[3 * ky + kx], 0, 0, 0);
+          for (int kx = 0; kx < 3; ++kx)
+            acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, d[k]), xs[kx],
+                                                                     acc[3 * ky + kx], 0, 0, 0);
         }
       };
-      // rows y = y0 - 1 .. y1 of the input; slot of gradient row y0 + q: (q + 2) & 3
-      load_d(y0 - 2, dr[0]);
-      load_d(y0 - 1, dr[1]);
-      load_d(y0, dr[2]);
+      // gradient rows y = y0 .. y1 - 1, each with the three input rows it meets; input row y0 - 1 + q in slot q & 3
       load_x(y0 - 1, xr[0]);
-      for (int y = y0 - 1; y <= y1; y += 4) {
+      load_x(y0, xr[1]);
+      load_x(y0 + 1, xr[2]);
+      load_d(y0, dr[0]);
+      for (int y = y0; y < y1; y += 4) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {   // row y + s: gradient rows in slots s + 2 (up), s + 1, s
-          if (y + s <= y1) {
-            load_x(y + s + 1, xr[(s + 1) & 1]);
-            load_d(y + s + 2, dr[(s + 3) & 3]);
-            products(xr[s & 1], dr[(s + 2) & 3], dr[(s + 1) & 3], dr[s & 3]);
+        for (int s = 0; s < 4; ++s) {
+          if (y + s < y1) {
+            load_x(y + s + 2, xr[(s + 3) & 3]);
+            load_d(y + s + 1, dr[(s + 1) & 1]);
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) products(ky, xr[(s + ky) & 3], dr[s & 1]);
           }
         }
       }
     } else {
       // input row 2 y (odd 0) or 2 y + 1 (odd 1) with gradient row d under kernel row 1 or 2, and the odd
-      // row with gradient row e under kernel row 0
-      auto products = [&](const XRow& q, int odd, const u32x4 (&d)[2], const u32x4 (&e)[2]) {
+      // row with gradient row e under kernel row 0; in_d, in_e: the gradient row is in the unit
+      auto products = [&](const XRow& q, int odd, const u32x4 (&d)[2], bool in_d, const u32x4 (&e)[2], bool in_e) {
         u32x4 ev[2], od[2];
 #pragma unroll
         for (int k = 0; k < 2; ++k)
@@ -1040,16 +1055,17 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
           const u32x4 v = od[k];
-          const u32x4 lo = {__builtin_amdgcn_alignbit(v.x, k ? od[0].w : left, 16), __builtin_amdgcn_alignbit(v.y, v.x, 16),
-                            __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16)};
+          const u32x4 lo = left_of_row(
+              u32x4{__builtin_amdgcn_alignbit(v.x, k ? od[0].w : left, 16), __builtin_amdgcn_alignbit(v.y, v.x, 16),
+                    __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16)}, k);
           const bf16x8 xs[3] = {__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, ev[k]),
                                 __builtin_bit_cast(bf16x8, v)};
           const bf16x8 g = __builtin_bit_cast(bf16x8, d[k]);
 #pragma unroll
           for (int kx = 0; kx < 3; ++kx) {
             const int t = odd ? 6 + kx : 3 + kx;
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, xs[kx], acc[t], 0, 0, 0);
-            if (odd) acc[kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, e[k]), xs[kx], acc[kx], 0, 0, 0);
+            if (in_d) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, xs[kx], acc[t], 0, 0, 0);
+            if (odd && in_e) acc[kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, e[k]), xs[kx], acc[kx], 0, 0, 0);
           }
         }
       };
@@ -1063,9 +1079,10 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
         for (int s = 0; s < 4; ++s) {   // gradient row y + s in slot s
           if (y + s < y1) {
             load_d(y + s + 2, dr[(s + 2) & 3]);
-            products(xr[1], 1, dr[s], dr[(s + 1) & 3]);      // input row 2 (y + s) + 1
+            const bool next = y + s + 1 < y1;
+            products(xr[1], 1, dr[s], y + s >= y0, dr[(s + 1) & 3], next);      // input row 2 (y + s) + 1
             load_x(2 * (y + s) + 3, xr[1]);
-            if (y + s + 1 < y1) products(xr[0], 0, dr[(s + 1) & 3], dr[s]);   // input row 2 (y + s) + 2
+            if (next) products(xr[0], 0, dr[(s + 1) & 3], true, dr[s], false);   // input row 2 (y + s) + 2
             load_x(2 * (y + s) + 4, xr[0]);
           }
         }
