@@ -91,7 +91,9 @@ msl_status msl_nn_conv3x3_adjoint(int32_t Co, int32_t C, int32_t B, int32_t H, i
  * bits used as is: the same result as float32 x holding those values); the pixel sum is split into at
  * most `splits` parts written to partials (float32 [splits][Co][9C], caller-owned scratch) and then
  * summed in a fixed order into dw (float32 [Co][9C]).  The parts are ranges of image rows (as many as
- * fill the GPU, at most `splits`).  1 <= splits <= 4096. */
+ * fill the GPU, at most `splits`), so the order of summation, and with it the last bits, is not that of
+ * msl_nn_gemm_bf16_splitk over the patch matrix.  1 <= splits <= 4096; fewer than 2^30 strips of 32 gradient
+ * pixels by up to 32 rows. */
 msl_status msl_nn_conv3x3_weight_grad(int32_t Co, int32_t C, int32_t B, int32_t H, int32_t W, int32_t stride,
                                      const uint16_t* dy16, const void* x, int32_t x_bf16, float* dw, int32_t splits,
                                      float* partials, void* hip_stream);

@@ -893,7 +893,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_rows(RowsArgs a) {
 // gradient's instead (two half-used rows more per unit): 32 -> 32 channels at 32x256x256 117 us against 106 so,
 // 96 -> 32 396 and 367, 64 -> 64 at 32x128x128 79 and 70, 384 -> 128 at 32x64x64 279 and 268, 256 -> 256 at
 // 32x32x32 81 and 71 (bfloat16 input; halo kernel: 240, 580, 209, 470, 203); widths not a multiple of 8,
-// 150 -> 12 channels at 8x200x66, 59 us (patch-column product: 294).
+// 150 -> 12 channels at 8x200x66, 55 us (patch-column product: 294).
 //
 // Stride 2: a strip is 32 pixels of the gradient over 64 of the input, whose even and odd columns are
 // parted in registers (the middle tap takes the even ones, the right tap the odd ones, the left tap the
@@ -950,7 +950,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
     // of the lanes) and right of it (upper half) come in `edge`, where the shifted operands want them
     const int px = sx * kWgStrip + 16 * half;
     // eight pixels before the lane's (load8 reads as far back at a row's end), in input row S y0 - 1 and in
-    // gradient row y0: offsets from there within the unit's rows fit 32 bits (the host sees to it)
+    // gradient row y0
     const char* const xu = xc + ((int64_t)b * plane + (int64_t)(S * y0 - 1) * a.W + S * px - 8) * ES;
     const char* const du = dc + ((int64_t)b * oplane + (int64_t)y0 * a.Wo + px - 8) * 2;
     const uint32_t eo = (half ? 24u : 7u) * ES;   // the edge pixel (stride 1; stride 2: the lower half's)
@@ -974,28 +974,28 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
     };
     auto load_x = [&](int y, XRow& q) {
       const bool in = c_ok && y >= 0 && y < a.H;
-      const uint32_t row = (uint32_t)(y - (S * y0 - 1)) * (uint32_t)a.W * ES;
+      const char* const row = xu + (int64_t)(y - (S * y0 - 1)) * a.W * ES;
       q.edge = 0u;
 #pragma unroll
       for (int k = 0; k < 2 * S; ++k) {
         const int p = S * px + 8 * k;
         q.v[k] = u32x4{0u, 0u, 0u, 0u};
-        if (in && p < a.W) q.v[k] = load8<XBF16, RD>(xu, row + 8u * (uint32_t)(k + 1) * ES, p, a.W);
+        if (in && p < a.W) q.v[k] = load8<XBF16, RD>(row, 8u * (uint32_t)(k + 1) * ES, p, a.W);
       }
       if (S == 1) {
-        if (in) q.edge = load1<XBF16>(xu, row + eo, half ? px + 16 : px - 1, a.W) << (half ? 0 : 16);
+        if (in) q.edge = load1<XBF16>(row, eo, half ? px + 16 : px - 1, a.W) << (half ? 0 : 16);
       } else {
-        if (in && !half) q.edge = load1<XBF16>(xu, row + eo, 2 * px - 1, a.W) << 16;
+        if (in && !half) q.edge = load1<XBF16>(row, eo, 2 * px - 1, a.W) << 16;
       }
     };
     auto load_d = [&](int y, u32x4 (&q)[2]) {
       const bool in = o_ok && y >= y0 && y < y1;
-      const uint32_t row = (uint32_t)(y - y0) * (uint32_t)a.Wo * 2u;
+      const char* const row = du + (int64_t)(y - y0) * a.Wo * 2;
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int p = px + 8 * k;
         q[k] = u32x4{0u, 0u, 0u, 0u};
-        if (in && p < a.Wo) q[k] = load8<true, RD>(du, row + 16u * (uint32_t)(k + 1), p, a.Wo);
+        if (in && p < a.Wo) q[k] = load8<true, RD>(row, 16u * (uint32_t)(k + 1), p, a.Wo);
       }
     };
     if constexpr (S == 1) {
@@ -1122,10 +1122,12 @@ __global__ void __launch_bounds__(256, 2) k_conv_wgrad_rows(WrowsArgs a) {
 }
 
 // dw[(o C + c) 9 + t] = sum over the parts of P[part][t][o][c], in the order of k_sum_parts.
-__global__ void __launch_bounds__(256) k_sum_wgrad(int n, int parts, const float* __restrict__ P, float* __restrict__ dw) {
+// From element e0 on.
+__global__ void __launch_bounds__(256) k_sum_wgrad(int64_t n, int64_t e0, int parts, const float* __restrict__ P,
+                                                   float* __restrict__ dw) {
   __shared__ float part_sum[16][17];
   const int ei = threadIdx.x & 15, sl = threadIdx.x >> 4;
-  const int64_t mn = (int64_t)9 * n, e = (int64_t)blockIdx.x * 16 + ei;
+  const int64_t mn = 9 * n, e = e0 + (int64_t)blockIdx.x * 16 + ei;
   float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
   if (e < mn) {
     int s = sl;
@@ -1838,10 +1840,9 @@ msl_status msl_nn_conv3x3_weight_grad(int32_t Co, int32_t C, int32_t B, int32_t 
   const int want = (int)std::max<int64_t>(1, (kWgradGroups + nco - 1) / nco);   // parts that fill the GPU
   w.rh = 32;
   while (w.rh > 4 && (int64_t)B * w.strips * ((w.Ho + w.rh - 1) / w.rh) < 4 * want) w.rh /= 2;
-  while (w.rh > 1 && (int64_t)(stride * (w.rh + 1) + 1) * W >= (1ll << 30)) w.rh /= 2;   // 32-bit offsets in a unit
   w.chunks = (w.Ho + w.rh - 1) / w.rh;
   const int64_t units = (int64_t)B * w.strips * w.chunks;
-  MSL_TRY(need(units < (1ll << 30) && (int64_t)(2 * stride + 1) * W < (1ll << 30) && (int64_t)C * Co < (1 << 27), "conv weight gradient: sizes too large"));
+  MSL_TRY(need(units < (1ll << 30), "conv weight gradient: sizes too large"));
   w.units = (int)units;
   int parts = (int)std::min<int64_t>({(int64_t)splits, (int64_t)want, (units + 3) / 4});
   w.per_part = (int)((units + 4 * (int64_t)parts - 1) / (4 * (int64_t)parts)) * 4;
@@ -1862,7 +1863,10 @@ msl_status msl_nn_conv3x3_weight_grad(int32_t Co, int32_t C, int32_t B, int32_t 
   else if (w.Wo >= 8) launch(std::integral_constant<int, ROW_ANY>{});
   else launch(std::integral_constant<int, ROW_SHORT>{});
   const int64_t mn = (int64_t)Co * C * 9;
-  hipLaunchKernelGGL(k_sum_wgrad, dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, Co * C, parts, partials, dw);
+  constexpr int64_t most = 1 << 27;   // elements of a launch (its threads have to fit 32 bits)
+  for (int64_t e0 = 0; e0 < mn; e0 += most)
+    hipLaunchKernelGGL(k_sum_wgrad, dim3((unsigned)((std::min(mn - e0, most) + 15) / 16)), dim3(256), 0, st, (int64_t)Co * C,
+                       e0, parts, partials, dw);
   return launched("conv weight gradient kernels");
 }
 
