@@ -1625,6 +1625,13 @@ msl_status launch_rows_t(RowsArgs a, bool xbf16, hipStream_t st) {
   return launched("conv kernel");
 }
 
+// Whether the register rows take a convolution of M product rows over images of H x W at stride s: they
+// address 16 channels with 32 bits, a grid has 65535 blocks of 64 rows, and 32-pixel blocks waste half in rows
+// of 16 and less.
+bool rows_take(int64_t M, int B, int H, int W, int s) {
+  return W / s > 16 && (int64_t)B * H * W < (1ll << 26) && M <= 65535 * 64ll;
+}
+
 // Convolution of M output rows on register rows; pack: the weights' mode (k_pack_rows).
 msl_status launch_conv_rows(RowsArgs a, int Co, int C, int stride, int pack, const uint16_t* w16, uint16_t* wscratch, bool xbf16,
                             hipStream_t st) {
@@ -1759,8 +1766,7 @@ msl_status msl_nn_conv3x3(int32_t Co, int32_t C, int32_t B, int32_t H, int32_t W
   MSL_TRY(check_ptr(y, y_bf16 ? 2 : 4, "y"));
   MSL_TRY(check_ptr(wscratch, 16, "wscratch"));
   MSL_TRY(need((int64_t)C * 9 < (1 << 30) && (int64_t)B * H * W < (1ll << 40), "conv: sizes too large"));
-  // k_conv_rows addresses 16 channels with 32 bits; its 32-pixel blocks waste half in rows of 16 and less
-  if (W / stride > 16 && (int64_t)B * H * W < (1ll << 26)) {
+  if (rows_take(Co, B, H, W, stride)) {
     RowsArgs r{};
     r.M = Co; r.C = C; r.B = B; r.H = H; r.W = W; r.Ho = H / stride; r.Wo = W / stride;
     r.relu = relu ? 1 : 0;
@@ -1789,7 +1795,7 @@ msl_status msl_nn_conv3x3_adjoint(int32_t Co, int32_t C, int32_t B, int32_t H, i
     // sub-pixel form, a 2x2 convolution over dy with 4 C rows (see k_conv_halo)
     MSL_TRY(check_ptr(wscratch, 16, "wscratch"));
     MSL_TRY(need((int64_t)C * 9 < (1 << 30) && (int64_t)B * H * W < (1ll << 40), "conv adjoint: sizes too large"));
-    if (W / stride > 16 && (int64_t)B * H * W < (1ll << 26)) {
+    if (rows_take(stride == 1 ? C : 4ll * C, B, H, W, stride)) {
       RowsArgs r{};
       r.M = stride == 1 ? C : 4 * C; r.C = Co; r.B = B;
       r.H = r.Ho = H / stride; r.W = r.Wo = W / stride;   // both grids are dy's
