@@ -746,7 +746,7 @@ msl_status run_phases(const Call& k, const PhaseSpec& a, const PhaseSpec* b) {
     if (f0 < npa && msl::phase_pass(a, f0).axis != msl::COL) ++f0;  // a dataflow launch begins with a column pass
     f1 = f0;
     while (f1 < npa && takes(f1)) ++f1;
-    if (f1 - f0 < msl::kFlowMinPasses) f0 = f1 = npa;
+    if (f1 - f0 < msl::flow_min_passes(k.g.n_slices, a.exact != 0)) f0 = f1 = npa;
   }
   for (int p = 0; p < npa; ++p) {
     if (p == f0) {

@@ -51,7 +51,12 @@ constexpr bool flow_admits(int queues, int cus, int per_cu, int grid) {
   return per_cu >= kFlowPerCu && (int64_t)queues * grid <= (int64_t)cus * kFlowPerCu;
 }
 
-constexpr int kFlowMinPasses = 4;   // a launch of fewer passes is not worth its two ends
+// The fewest passes that are worth a launch's two ends: 4, but 6 in calls of fewer than 16 slice passes, which
+// also pay for the fill of the exchange fields and the call's error kernel.  Forward of 64x64, 256x256 and
+// 512x512 with 4 middle passes 34.5, 39.0 and 59.4 us against 34.0, 39.0 and 55.7 one launch each, with 7 37, 48 and 71
+// against 46, 49 and 73; gradient of 8 slices of 256x256, a checkpoint every 4, 169 against 159, of 64 slices
+// 911 against 990.
+constexpr int flow_min_passes(int n_slices, bool exact) { return (exact ? 2 : 1) * n_slices < 16 ? 6 : 4; }
 
 // What the passes of a launch are: the paraxial middle passes of the forward sweep and the recompute with
 // the transmission from the slice pack or (FLOW_STACK) from the caller's stacks, those of the reverse
