@@ -545,14 +545,16 @@ Call make_call(const msl_geometry& g, const Layout& lay, void* ws, hipStream_t s
 
 Call make_call(const msl_geometry& g, int k, void* ws, hipStream_t st) { return make_call(g, layout(g, k), ws, st); }
 
-// The jobs of a list, in launches of up to kMaxJobs.
-struct Jobs {
-  std::vector<Job> q;
-  int64_t most = 0;   // threads of the largest job
+// Launches the jobs it is given, up to kMaxJobs at a time (no memory but its own: a call that may not
+// allocate starts with it).
+class Jobs {
+ public:
+  Jobs(unsigned* bar, hipStream_t st) : st_(st) { l_.bar = bar; }
   void add(const Job& j) {
-    q.push_back(j);
+    if (l_.n == kMaxJobs) launch();
+    l_.j[l_.n++] = j;
     const int64_t t = j.kind == JOB_PROBE ? (int64_t)j.n * j.nz : 2 * (int64_t)j.n;
-    if (t > most) most = t;
+    if (t > most_) most_ = t;
   }
   void tables(const msl_geometry& g, float2* twz, float2* twy, float2* hz, float2* hy) {
     const double kk = 2.0 * M_PI / g.wavelength_nm;
@@ -565,17 +567,23 @@ struct Jobs {
     const double q_ = 2.0 * M_PI / g.wavelength_nm * std::sin(g.alpha_i_rad) * g.dy_nm;
     add({out, q_, 0.0, 0.0, JOB_PROBE, g.ny, g.nz});
   }
-  msl_status run(unsigned* bar, hipStream_t st) const {
-    const unsigned gx = (unsigned)std::min<int64_t>((most + 255) / 256, 256);   // (tables need at most 8)
-    for (size_t i = 0; i < q.size(); i += kMaxJobs) {
-      JobList l{};
-      l.n = (int)std::min<size_t>(kMaxJobs, q.size() - i);
-      for (int j = 0; j < l.n; ++j) l.j[j] = q[i + j];
-      l.bar = i == 0 ? bar : nullptr;
-      hipLaunchKernelGGL(k_jobs, dim3(gx, l.n), dim3(256), 0, st, l);
-    }
+  // Launches what is left.
+  msl_status run() {
+    if (l_.n > 0) launch();
     return hip_check(hipGetLastError(), "table kernels");
   }
+
+ private:
+  void launch() {
+    const unsigned gx = (unsigned)std::min<int64_t>((most_ + 255) / 256, 256);   // (tables need at most 8)
+    hipLaunchKernelGGL(k_jobs, dim3(gx, l_.n), dim3(256), 0, st_, l_);
+    l_.n = 0;
+    l_.bar = nullptr;   // (the first launch clears it)
+    most_ = 0;
+  }
+  JobList l_{};
+  int64_t most_ = 0;   // threads of the largest job
+  hipStream_t st_;
 };
 
 // Start of a call that runs passes: its tables, the probe (into probe_out, if given) and its status word
@@ -584,10 +592,10 @@ msl_status start_call(const Call& k, bool need_prop, float2* probe_out) {
   const msl_geometry& g = k.g;
   auto P = [&](size_t off) { return reinterpret_cast<float2*>(k.ws + off); };
   const bool par = need_prop && g.propagator == MSL_PROP_PARAXIAL;
-  Jobs jobs;
+  Jobs jobs(reinterpret_cast<unsigned*>(k.ws + k.L.bar), k.st);
   jobs.tables(g, P(k.L.twz), P(k.L.twy), par ? P(k.L.hz) : nullptr, par ? P(k.L.hy) : nullptr);
   if (probe_out) jobs.probe(g, probe_out);
-  MSL_TRY(jobs.run(reinterpret_cast<unsigned*>(k.ws + k.L.bar), k.st));
+  MSL_TRY(jobs.run());
   if (need_prop && !par) {
     const int64_t m = (int64_t)g.ny * g.nz;
     hipLaunchKernelGGL(k_hexact, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, k.st, g.ny, g.nz, g.dy_nm, g.dz_nm,
@@ -1570,7 +1578,7 @@ msl_status msl_forward_batch(const msl_instance* inst, int32_t n, void* workspac
   // per instance: tables, probe, pool pack, record
   std::vector<BatchRec> recs(n);
   std::vector<PhaseSpec> phs(n);
-  Jobs jobs;
+  Jobs jobs(nullptr, st);
   for (int r = 0; r < n; ++r) {
     const int i = order[r];
     const msl_instance& x = inst[i];
@@ -1628,7 +1636,7 @@ msl_status msl_forward_batch(const msl_instance* inst, int32_t n, void* workspac
     ph.in_rm = in;
     ph.out_rm = f;
   }
-  MSL_TRY(jobs.run(nullptr, st));
+  MSL_TRY(jobs.run());
   for (int r0 = 0; r0 < n; r0 += kRecChunk) {
     RecChunk ch{};
     ch.n = std::min(kRecChunk, n - r0);
