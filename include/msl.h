@@ -86,7 +86,8 @@ typedef enum {
   MSL_SCHED_AUTO = 0,        /* library choice: one launch for the middle passes of a phase, the field
                                 handed over through memory element by element, where that serves
                                 (grids up to 512 x 512 in either propagator, the default points per lane,
-                                a stream of default priority without a compute-unit mask); else one launch
+                                a stream of default priority without a compute-unit mask, none set
+                                for the process by HSA_CU_MASK or ROC_GLOBAL_CU_MASK); else one launch
                                 per line pass.  The results are bit for bit those of MSL_SCHED_PER_PASS.
                                 Such a launch needs all its workgroups on the GPU at once.  As many
                                 calls as this process has hardware queues have room together, but launches

@@ -59,7 +59,9 @@ bool flow_serves(int kind, int ny, int nz) {
       case FLOW_XREV: e = flow_occupancy<FLOW_XREV>(nz, ny, per_cu, grid); break;
       default: break;
     }
-    const bool ok = e == hipSuccess &&
+    // (masks of the whole process, which neither the device's nor the stream's attributes show)
+    const bool masked = std::getenv("HSA_CU_MASK") || std::getenv("ROC_GLOBAL_CU_MASK");
+    const bool ok = e == hipSuccess && !masked &&
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                     flow_admits(queues, cus, per_cu, grid);
     if (!ok) (void)hipGetLastError();

@@ -60,3 +60,28 @@ def test_shapes(M, lines, points, flow):
     f, _ = M.forward(g, d, d / 20, ws=ws)
     assert torch.equal(f, ref)
     assert forward_fails(M, g, d, ws) == flow
+
+
+MASKED = """
+import math, torch
+from paper_2212_01253_amd import msl, synth
+g = synth.Geometry(256, 128, 40, 1.0, 1.0, 5.0, 0.1, math.radians(0.25), 0)
+d = 3e-5 * torch.rand((40, 256, 128), device="cuda")
+ws = msl.workspace(g, 0)
+msl.set_barrier_spin_limit(0)
+msl.forward(g, d, d / 20, ws=ws)
+msl.workspace_status(ws)
+print("per pass")
+"""
+
+
+def test_process_wide_mask(M):
+    # a process whose queues are masked by the environment runs per pass (the mask here leaves every unit in)
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    n = torch.cuda.get_device_properties(0).multi_processor_count
+    r = subprocess.run([sys.executable, "-c", MASKED], cwd=root, env={**os.environ, "HSA_CU_MASK": f"0:0-{n - 1}"},
+                       capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0 and r.stdout.strip() == "per pass", r.stdout + r.stderr
