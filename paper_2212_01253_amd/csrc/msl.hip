@@ -1117,7 +1117,8 @@ Layout noalloc_layout(const msl_geometry& g) {
   L.H_hi = take(exact ? m * 8 : 0);
   L.H_lo = take(exact ? m * 8 : 0);
   L.total = o;
-  // the dataflow schedule's exchange fields, where they fit (xf[0] stays 0 where not)
+  // the dataflow schedule's exchange fields, where they fit (xf[0] stays 0 where not); the exact propagator's
+  // row-major passes have no dataflow kernel
   if (!exact && o + up(4 * m * 8) <= kNoAllocBytes) L.xf[0] = take(4 * m * 8);
   return L;
 }
